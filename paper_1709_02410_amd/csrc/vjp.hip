@@ -154,15 +154,30 @@ struct VjpBody {
     }
 };
 
+// One wave per quantity of 64 consecutive blobs (coalesced over the blobs),
+// then the chain rule of the regularisation by the first wave.  Bound by the
+// reads of the partials (0.53 GB at 5e4 blobs in FP32C).  One thread per blob
+// for all nine sums, as before, ran N / 256 workgroups of a serial chain:
+// 547 us against 133 us there, and 36 us against 4.1 us at 1000 blobs
+// (FP64).
 template <typename R>
-__global__ void sym_vjp_epilogue(const double* __restrict__ tpart, const R* __restrict__ spart,
-                                 const double* __restrict__ pos, const double* __restrict__ f,
-                                 const double* __restrict__ g, int64_t N, int ng, int C, int Hmax, int G,
-                                 double inv_a, double mu0, double* __restrict__ grad_pos, double* __restrict__ grad_f) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+__global__ __launch_bounds__(64 * kQ) void sym_vjp_epilogue(const double* __restrict__ tpart,
+                                                            const R* __restrict__ spart,
+                                                            const double* __restrict__ pos,
+                                                            const double* __restrict__ f,
+                                                            const double* __restrict__ g, int64_t N, int ng, int C,
+                                                            int Hmax, int nseg, int G, double inv_a, double mu0,
+                                                            double* __restrict__ grad_pos,
+                                                            double* __restrict__ grad_f) {
+    __shared__ double sum[kQ][64];
+    const int x = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + x;
+    sum[q][x] = i < N ? sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G, 0, 1, nseg) : 0.0;
+    __syncthreads();
+    if (q != 0 || i >= N) return;
     double s[kQ];
-    for (int q = 0; q < kQ; ++q) s[q] = sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G);
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) s[k] = sum[k][x];
     const double z = pos[3 * i + 2] * inv_a;
     const double B = z < 1.0 ? z : 1.0;
     if (grad_pos) {
@@ -313,8 +328,8 @@ int vjp(const double* pos, const double* f, const double* g, double* grad_pos, d
                 launch_vjp_sym<float, 4>((const float*)rec, ng, C, ipw, Hmax, tpart, (float*)spart, st);
             RPYW_HIP(hipGetLastError());
             profile_end(st, ev, (double)N * (double)N);
-            hipLaunchKernelGGL(sym_vjp_epilogue<float>, dim3(g1), dim3(kBlock), 0, st, tpart, (const float*)spart, pos,
-                               f, g, N, ng, C, Hmax, G, 1.0 / a, m0, grad_pos, grad_f);
+            hipLaunchKernelGGL(sym_vjp_epilogue<float>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart,
+                               (const float*)spart, pos, f, g, N, ng, C, Hmax, 1, G, 1.0 / a, m0, grad_pos, grad_f);
         } else {
             hipLaunchKernelGGL(pack_kernel<double>, dim3(gpk), dim3(kBlock), 0, st, pos, f, N, 2, rw, 1.0 / a,
                                (double*)rec, B, g, 0.0, 0.0, npad);
@@ -326,8 +341,8 @@ int vjp(const double* pos, const double* f, const double* g, double* grad_pos, d
                 launch_vjp_sym<double, 4>((const double*)rec, ng, C, ipw, Hmax, tpart, (double*)spart, st);
             RPYW_HIP(hipGetLastError());
             profile_end(st, ev, (double)N * (double)N);
-            hipLaunchKernelGGL(sym_vjp_epilogue<double>, dim3(g1), dim3(kBlock), 0, st, tpart, (const double*)spart,
-                               pos, f, g, N, ng, C, Hmax, G, 1.0 / a, m0, grad_pos, grad_f);
+            hipLaunchKernelGGL(sym_vjp_epilogue<double>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart,
+                               (const double*)spart, pos, f, g, N, ng, C, Hmax, 1, G, 1.0 / a, m0, grad_pos, grad_f);
         }
         RPYW_HIP(hipGetLastError());
         ar.used = mark;

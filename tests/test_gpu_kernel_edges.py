@@ -1,0 +1,64 @@
+"""The kernels of the products and derivatives at the sizes where their
+splits, tiles and remainders change, against the FP64 oracle.  Bars: those of
+the two precisions (FP64 1e-12, FP32C 1e-5, relative L2 and largest entry)."""
+import numpy as np
+import pytest
+
+from parity_util import check
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+TOL = {0: 1e-12, 1: 1e-5}
+
+
+@pytest.fixture(scope="module")
+def rp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1709_02410_amd import rpywall
+    rpywall.lib()
+    return rpywall
+
+
+def _t(x):
+    return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float64, device="cuda")
+
+
+def _mixed(n, seed):
+    """Blobs above and below z = a, overlapping pairs, one coincident pair."""
+    rng = np.random.default_rng(seed)
+    box = max(2.0, 2.0 * np.sqrt(n))
+    pos = np.column_stack([rng.uniform(0, box, n), rng.uniform(0, box, n), rng.uniform(0.3, 4.0, n)])
+    if n >= 3:
+        pos[2] = pos[1]
+    return pos
+
+
+@pytest.mark.parametrize("N,k", [(1, 2), (64, 3), (65, 4), (129, 7), (575, 5), (1025, 2)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_chunk_epilogue(rp, orc, N, k, prec):
+    """One chunk, fewer chunks than the epilogue's shares, and several rounds
+    of them; a last wave of one blob."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + 1).standard_normal((k, N, 3))
+    U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=prec).cpu().numpy()
+    for j in range(k):
+        check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"multi N={N} k={k} rhs {j} prec={prec}")
+
+
+@pytest.mark.parametrize("N", [512, 513, 1000, 1985, 33000])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_vjp_epilogue(rp, orc, N, prec):
+    """Odd and even numbers of groups of 64, a last wave of one blob, and
+    groups of 256."""
+    pos = 0.9 * _mixed(N, N)
+    f, g = np.random.default_rng(N + 1).standard_normal((2, N, 3))
+    gp, gf = rp.matvec_vjp(_t(pos), _t(f), _t(g), 0.9, 1.3, precision=prec)
+    if N > 5000:  # the first and last blobs: gradients of Phi by products on those rows
+        rows = np.r_[0:8, N - 8:N]
+        check(gf.cpu().numpy()[rows], orc.matvec(pos, g, 0.9, 1.3, rows=rows), TOL[prec], f"vjp N={N} grad_f")
+        return
+    gp_ref, gf_ref = orc.vjp(pos, f, g, 0.9, 1.3)
+    check(gp.cpu().numpy(), gp_ref, TOL[prec], f"vjp N={N} prec={prec} grad_pos")
+    check(gf.cpu().numpy(), gf_ref, TOL[prec], f"vjp N={N} prec={prec} grad_f")
