@@ -51,6 +51,11 @@ FLOP_VJP_SELF = 406
 # (matrix cores), counted the same way.
 FLOP_PAIR_BLOCK = 19
 FLOP_BLOCK_RHS = 18
+# The FP64 form of the pair (free and wall terms merged before a force is
+# applied), counted the same way: geometry, one application, the block.
+FLOP64_PAIR_SHARED = 78
+FLOP64_PAIR_RHS = 18
+FLOP64_PAIR_BLOCK = 11
 PEAK_FP32_MATRIX = 157.3  # TFLOP/s, MI355X dense FP32 matrix cores
 PEAK_FP64_MATRIX = 78.6   # TFLOP/s, MI355X dense FP64 matrix cores
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_kernel_traffic.json")
@@ -59,23 +64,26 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_kernel_traffic.json")
 KERNEL_SOURCES = ["pair_kernels.hip", "pair_math.h", "records.h", "sym_pairs.h"]
 
 
-def algorithmic_flop(N: int, k: int, sym: int) -> float:
+def algorithmic_flop(N: int, k: int, sym: int, fp64: bool = False) -> float:
     """Algorithmic FLOPs of one product of N blobs and k RHS.  The plain
-    kernel evaluates every ordered pair (75 + 24 k each); the symmetric
-    kernel evaluates each unordered pair once and applies it both ways
-    (75 + 48 k), self pairs once (75 + 24 k)."""
+    kernel evaluates every ordered pair (75 + 24 k each; FP64 78 + 18 k); the
+    symmetric kernel evaluates each unordered pair once and applies it both
+    ways (75 + 48 k), self pairs once (75 + 24 k)."""
     n = float(N)
+    geo, app = (FLOP64_PAIR_SHARED, FLOP64_PAIR_RHS) if fp64 else (FLOP_PAIR_SHARED, FLOP_PAIR_RHS)
     if sym:
-        return n * (n - 1) / 2 * (FLOP_PAIR_SHARED + 2 * k * FLOP_PAIR_RHS) + n * (FLOP_PAIR_SHARED + k * FLOP_PAIR_RHS)
-    return n * n * (FLOP_PAIR_SHARED + k * FLOP_PAIR_RHS)
+        return n * (n - 1) / 2 * (geo + 2 * k * app) + n * (geo + k * app)
+    return n * n * (geo + k * app)
 
 
-def mat_flop(N: int, k: int):
+def mat_flop(N: int, k: int, fp64: bool = False):
     """(vector-unit, matrix-core) algorithmic FLOPs of one product of N blobs
     and k RHS on the matrix-core kernel: every ordered pair forms its block
-    once (75 + 19) and contracts it with each right-hand side (18 each)."""
+    once (75 + 19; FP64 78 + 11) and contracts it with each right-hand side
+    (18 each)."""
     n = float(N)
-    return n * n * (FLOP_PAIR_SHARED + FLOP_PAIR_BLOCK), n * n * k * FLOP_BLOCK_RHS
+    block = FLOP64_PAIR_SHARED + FLOP64_PAIR_BLOCK if fp64 else FLOP_PAIR_SHARED + FLOP_PAIR_BLOCK
+    return n * n * block, n * n * k * FLOP_BLOCK_RHS
 
 
 def vjp_flop(N: int, sym: int) -> float:
@@ -376,7 +384,7 @@ def main():
     step64 = lambda: rp.matvec(pos, f, precision=rp.FP64, out=vel64)  # noqa: E731
     w64, k64, l64, p64 = timed(step64, max(3, args.steps // 2), 1)
     shape64 = rp.get_shape(rp.FP64, N, 1)
-    a64 = algorithmic_flop(N, 1, shape64["sym"]) / (k64 / l64 * 1e-3) / 1e12
+    a64 = algorithmic_flop(N, 1, shape64["sym"], True) / (k64 / l64 * 1e-3) / 1e12
     out["fp64"] = {"value": N * N / w64, "unit": "pair interactions/s", "ms_per_step": w64 * 1e3,
                    "kernel_ms_avg": k64 / l64, "shape": shape64,
                    "roofline": {"bound": "alu", "achieved": round(a64, 3), "peak": PEAK_FP64, "unit": "TFLOP/s",
@@ -428,7 +436,7 @@ def main():
             U16.zero_()
             w64m, km64, _, _ = timed(lambda: rp.matvec_multi(pos, F16, precision=rp.FP64, out=U16), 2, 1)
             sh64 = rp.get_shape(rp.FP64, N, k)
-            fv, fm = mat_flop(N, k)
+            fv, fm = mat_flop(N, k, True)
             km64 /= 2
             row64 = {"pair_rhs_per_s": k * N * N / w64m, "ms": w64m * 1e3, "kernel_ms": km64, "shape": sh64,
                      "bound": "mfma", "matrix_tflops": fm / (km64 * 1e-3) / 1e12,
@@ -439,7 +447,7 @@ def main():
             rp.set_shape(rp.FP64, N, k, tpl=1, tile=256, kblk=8, sym=0, ipw=4, mat=0)
             wv64, kmv64, _, _ = timed(lambda: rp.matvec_multi(pos, F16, precision=rp.FP64, out=U16), 1, 1)
             rp.reset_shape(rp.FP64, N, k)
-            flv = 2 * algorithmic_flop(N, 8, 0)
+            flv = 2 * algorithmic_flop(N, 8, 0, True)
             row64["vector_kernel"] = {"ms": wv64 * 1e3, "kernel_ms": kmv64, "kblk": 8,
                                       "tflops_alg": flv / (kmv64 * 1e-3) / 1e12,
                                       "frac_fp64_peak": flv / (kmv64 * 1e-3) / 1e12 / PEAK_FP64}
@@ -464,7 +472,8 @@ def main():
                     name = f"product_{cname}_{pname}"
                     rows[name] = {
                         "blobs": cfg.N, "pairs_per_s": cfg.N ** 2 / w, "ms": w * 1e3, "kernel_ms": kms_c,
-                        "shape": shc, "tflops_alg": algorithmic_flop(cfg.N, 1, shc["sym"]) / (kms_c * 1e-3) / 1e12}
+                        "shape": shc, "tflops_alg": algorithmic_flop(cfg.N, 1, shc["sym"], prec == rp.FP64) / (kms_c * 1e-3)
+                        / 1e12}
                     if cfg.N <= 4000:
                         check_matvec(name, f"all {cfg.N} rows", cfg.pos, fcf_np, H2(ucf))
                     else:
