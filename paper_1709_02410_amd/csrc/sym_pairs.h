@@ -118,14 +118,16 @@ struct Vec<double> {
 };
 
 // Inputs of the records when the kernel forms them itself (make_record):
-// positions [N][3], kb right-hand sides [kb][N][3], 1 / a and the periodic
-// cell in units of a (zeros for the open domain).
+// positions [N][3], kb right-hand sides [kb][N][3] (with F2, kb = 2, the
+// second one [N][3] there), 1 / a and the periodic cell in units of a (zeros
+// for the open domain).
 struct PackSrc {
     const double* pos;
     const double* F;
     int64_t N;
     int kb;
     double inv_a, lx, ly;
+    const double* F2 = nullptr;
 };
 
 // The target a lane holds: scaled position (FP32: plus low parts) and the
@@ -312,7 +314,7 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
     if constexpr (FP) {
         R rr[L::RW];
         double bd;
-        make_record<R>(ps.pos, ps.F, ps.N, ps.kb, L::RW, ps.inv_a, nullptr, ps.lx, ps.ly, (int64_t)P * G + w * 64 + l,
+        make_record<R>(ps.pos, ps.F, ps.N, ps.kb, L::RW, ps.inv_a, ps.F2, ps.lx, ps.ly, (int64_t)P * G + w * 64 + l,
                        rr, &bd);
         me.load(rr);
     } else {
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
                 if constexpr (FP) {
                     R rr[L::RW];
                     double bd;
-                    make_record<R>(ps.pos, ps.F, ps.N, ps.kb, L::RW, ps.inv_a, nullptr, ps.lx, ps.ly,
+                    make_record<R>(ps.pos, ps.F, ps.N, ps.kb, L::RW, ps.inv_a, ps.F2, ps.lx, ps.ly,
                                    (int64_t)Q * G + threadIdx.x, rr, &bd);
 #pragma unroll
                     for (int v = 0; v < L::NV; ++v) {

@@ -251,21 +251,86 @@ __global__ __launch_bounds__(64) void divergence_kernel(const double* __restrict
 namespace {
 
 // Symmetric VJP plan: groups of G blobs as for the product (64 only up to
-// kSym64MaxN), 9 quantities per blob.
-bool vjp_sym_plan(int64_t N, int prec, int ipw, int G, int* ng, int* C, int* Hmax, size_t* tb, size_t* sb) {
-    if (G == 64 && N > kSym64MaxN) return false;
-    *ng = (int)((N + G - 1) / G);
-    *Hmax = *ng / 2;
-    *C = (*Hmax + 1 + ipw - 1) / ipw;
-    *tb = align_up((size_t)*ng * *C * kQ * G * sizeof(double));
-    *sb = align_up((size_t)*ng * (*Hmax + 1) * kQ * G * real_size(prec));
-    return *tb <= kSymPartialMaxBytes && *sb <= kSymPartialMaxBytes;
+// kSym64MaxN), 9 quantities per blob.  FP64 splits the passes of few items as
+// the product does, first over the four waves of a workgroup (ns), then over
+// workgroups (nseg): 136 items of 64 steps left the GPU nearly empty at 1000
+// blobs: 85 us a call before, 27 us now, with the records formed in the pair
+// kernel (5000 blobs 317 -> 180 us).  Its 2 waves per SIMD (registers) fill
+// the GPU with kVjpWaves; beyond that a split only adds partials.  FP32C is
+// not split: it sums a pass in FP32, so another split is another rounding.
+// Up to kVjpFusedItems items of groups of 64 the pair kernel forms the records
+// itself, one launch less; that takes the FP32C kernel from 121 to 139 VGPRs,
+// 3 waves per SIMD, which is as many as there are then.
+constexpr int64_t kVjpWaves = 2048;
+constexpr int64_t kVjpFusedItems = 3072;
+struct VjpPlan {
+    int G, ns, nseg, ng, C, Hmax;
+    size_t tb, sb;
+    bool fused, ok;
+};
+VjpPlan vjp_sym_plan(int64_t N, int prec, int ipw, int G) {
+    VjpPlan p{};
+    p.G = G;
+    if (G == 64 && N > kSym64MaxN) return p;
+    p.ng = (int)((N + G - 1) / G);
+    p.Hmax = p.ng / 2;
+    p.C = (p.Hmax + 1 + ipw - 1) / ipw;
+    const int64_t items = (int64_t)p.ng * (p.Hmax + 1);
+    p.ns = (prec == RPYW_FP64 && G == 64 && items < kVjpWaves) ? 4 : 1;
+    p.fused = G == 64 && items <= kVjpFusedItems;
+    p.nseg = 1;
+    while (p.ns > 1 && p.nseg < 4 && items * p.ns * p.nseg < kVjpWaves) p.nseg *= 2;
+    p.tb = align_up((size_t)p.ng * p.C * p.nseg * kQ * G * sizeof(double));
+    p.sb = align_up((size_t)p.ng * (p.Hmax + 1) * p.nseg * kQ * G * real_size(prec));
+    p.ok = p.tb <= kSymPartialMaxBytes && p.sb <= kSymPartialMaxBytes;
+    return p;
 }
 
-template <typename R, int NB>
-void launch_vjp_sym(const R* rec, int ng, int C, int ipw, int Hmax, double* tpart, R* spart, hipStream_t st) {
-    hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, NB>), dim3((unsigned)(ng * C)), dim3(64 * NB), 0, st, rec, ng, C,
-                       ipw, Hmax, 1, tpart, spart, Box<R>{}, PackSrc{});
+template <typename R>
+void launch_vjp_sym(const R* rec, const PackSrc& ps, const VjpPlan& p, int ipw, double* tpart, R* spart,
+                    hipStream_t st) {
+    const dim3 grid((unsigned)(p.ng * p.C * p.nseg));
+    if constexpr (sizeof(R) == 8)
+        if (p.ns == 4) {
+            hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, 1, 4, true>), grid, dim3(256), 0, st, rec, p.ng, p.C, ipw,
+                               p.Hmax, p.nseg, tpart, spart, Box<R>{}, ps);
+            return;
+        }
+    if (p.fused)
+        hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, 1, 1, true>), grid, dim3(64), 0, st, rec, p.ng, p.C, ipw, p.Hmax,
+                           p.nseg, tpart, spart, Box<R>{}, ps);
+    else if (p.G == 64)
+        hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, 1>), grid, dim3(64), 0, st, rec, p.ng, p.C, ipw, p.Hmax, p.nseg,
+                           tpart, spart, Box<R>{}, PackSrc{});
+    else
+        hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, 4>), grid, dim3(256), 0, st, rec, p.ng, p.C, ipw, p.Hmax, p.nseg,
+                           tpart, spart, Box<R>{}, PackSrc{});
+}
+
+// One symmetric VJP: records (unless fused), pairs, epilogue.
+template <typename R>
+int vjp_sym(const double* pos, const double* f, const double* g, double* grad_pos, double* grad_f, int64_t N, double a,
+            double m0, const VjpPlan& p, int ipw, Arena& ar, hipStream_t st) {
+    const int64_t npad = (int64_t)p.ng * p.G;
+    double* tpart = (double*)ar.take(p.tb);
+    R* spart = (R*)ar.take(p.sb);
+    R* rec = nullptr;
+    if (!p.fused) rec = (R*)ar.take((size_t)npad * rec_w<R, 2>() * sizeof(R));
+    if (!tpart || !spart || (!p.fused && !rec)) return RPYW_ENOMEM;
+    if (!p.fused) {
+        hipLaunchKernelGGL(pack_kernel<R>, dim3((unsigned)((npad + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, pos, f,
+                           N, 2, rec_w<R, 2>(), 1.0 / a, rec, (double*)nullptr, g, 0.0, 0.0, npad);
+        RPYW_HIP(hipGetLastError());
+    }
+    hipEvent_t ev = nullptr;
+    profile_begin(st, &ev);
+    launch_vjp_sym<R>(rec, PackSrc{pos, f, N, 2, 1.0 / a, 0.0, 0.0, g}, p, ipw, tpart, spart, st);
+    RPYW_HIP(hipGetLastError());
+    profile_end(st, ev, (double)N * (double)N);
+    hipLaunchKernelGGL(sym_vjp_epilogue<R>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart, spart, pos, f,
+                       g, N, p.ng, p.C, p.Hmax, p.nseg, p.G, 1.0 / a, m0, grad_pos, grad_f);
+    RPYW_HIP(hipGetLastError());
+    return RPYW_OK;
 }
 
 }  // namespace
@@ -277,15 +342,11 @@ size_t vjp_ws_bytes(int64_t N, int prec) {
     size_t b = align_up((size_t)N * rec_width(prec, 2) * real_size(prec));
     b += align_up((size_t)N * sizeof(double));
     b += align_up((size_t)splits * kQ * N * sizeof(double));
-    int ng, C, Hmax;
-    size_t tb, sb;
-    for (int G : {256, 64})
-        if (vjp_sym_plan(N, prec, 1, G, &ng, &C, &Hmax, &tb, &sb)) {
-            const size_t npad = (size_t)ng * G;
-            const size_t s =
-                align_up(npad * rec_width(prec, 2) * real_size(prec)) + align_up(npad * sizeof(double)) + tb + sb;
-            b = std::max(b, s);
-        }
+    for (int G : {256, 64}) {
+        const VjpPlan p = vjp_sym_plan(N, prec, 1, G);
+        if (p.ok)
+            b = std::max(b, align_up((size_t)p.ng * G * rec_width(prec, 2) * real_size(prec)) + p.tb + p.sb);
+    }
     return b + 8 * kAlign;
 }
 
@@ -294,59 +355,17 @@ int vjp(const double* pos, const double* f, const double* g, double* grad_pos, d
     const size_t mark = ar.used;
     const int rw = rec_width(prec, 2);
     const Shape sh = tuned_shape(N, 1, prec);
-    int ng, C, Hmax;
-    size_t tb, sb;
     const int ipw = sh.ipw < 1 ? 1 : sh.ipw;
-    int G = sym_group(sh.sym);
-    bool sym = sh.sym && vjp_sym_plan(N, prec, ipw, G, &ng, &C, &Hmax, &tb, &sb);
-    if (sh.sym && !sym && G == 64) {
-        G = 256;
-        sym = vjp_sym_plan(N, prec, ipw, G, &ng, &C, &Hmax, &tb, &sb);
-    }
     const double m0 = 1.0 / (6.0 * M_PI * eta * a);
     const unsigned g1 = (unsigned)((N + kBlock - 1) / kBlock);
-    if (sym) {
-        const int64_t npad = (int64_t)ng * G;
-        void* rec = ar.take((size_t)npad * rw * real_size(prec));
-        double* B = (double*)ar.take((size_t)npad * sizeof(double));
-        double* tpart = (double*)ar.take(tb);
-        void* spart = ar.take(sb);
-        if (!rec || !B || !tpart || !spart) {
-            ar.used = mark;
-            return RPYW_ENOMEM;
-        }
-        const unsigned gpk = (unsigned)((npad + kBlock - 1) / kBlock);  // records and padding
-        hipEvent_t ev = nullptr;
-        if (prec == RPYW_FP32C) {
-            hipLaunchKernelGGL(pack_kernel<float>, dim3(gpk), dim3(kBlock), 0, st, pos, f, N, 2, rw, 1.0 / a,
-                               (float*)rec, B, g, 0.0, 0.0, npad);
-            RPYW_HIP(hipGetLastError());
-            profile_begin(st, &ev);
-            if (G == 64)
-                launch_vjp_sym<float, 1>((const float*)rec, ng, C, ipw, Hmax, tpart, (float*)spart, st);
-            else
-                launch_vjp_sym<float, 4>((const float*)rec, ng, C, ipw, Hmax, tpart, (float*)spart, st);
-            RPYW_HIP(hipGetLastError());
-            profile_end(st, ev, (double)N * (double)N);
-            hipLaunchKernelGGL(sym_vjp_epilogue<float>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart,
-                               (const float*)spart, pos, f, g, N, ng, C, Hmax, 1, G, 1.0 / a, m0, grad_pos, grad_f);
-        } else {
-            hipLaunchKernelGGL(pack_kernel<double>, dim3(gpk), dim3(kBlock), 0, st, pos, f, N, 2, rw, 1.0 / a,
-                               (double*)rec, B, g, 0.0, 0.0, npad);
-            RPYW_HIP(hipGetLastError());
-            profile_begin(st, &ev);
-            if (G == 64)
-                launch_vjp_sym<double, 1>((const double*)rec, ng, C, ipw, Hmax, tpart, (double*)spart, st);
-            else
-                launch_vjp_sym<double, 4>((const double*)rec, ng, C, ipw, Hmax, tpart, (double*)spart, st);
-            RPYW_HIP(hipGetLastError());
-            profile_end(st, ev, (double)N * (double)N);
-            hipLaunchKernelGGL(sym_vjp_epilogue<double>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart,
-                               (const double*)spart, pos, f, g, N, ng, C, Hmax, 1, G, 1.0 / a, m0, grad_pos, grad_f);
-        }
-        RPYW_HIP(hipGetLastError());
+    VjpPlan p{};
+    if (sh.sym) p = vjp_sym_plan(N, prec, ipw, sym_group(sh.sym));
+    if (sh.sym && !p.ok && p.G == 64) p = vjp_sym_plan(N, prec, ipw, 256);
+    if (p.ok) {
+        const int rc = prec == RPYW_FP32C ? vjp_sym<float>(pos, f, g, grad_pos, grad_f, N, a, m0, p, ipw, ar, st)
+                                          : vjp_sym<double>(pos, f, g, grad_pos, grad_f, N, a, m0, p, ipw, ar, st);
         ar.used = mark;
-        return RPYW_OK;
+        return rc;
     }
     void* rec = ar.take((size_t)N * rw * real_size(prec));
     double* B = (double*)ar.take((size_t)N * sizeof(double));

@@ -47,15 +47,16 @@ def test_chunk_epilogue(rp, orc, N, k, prec):
         check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"multi N={N} k={k} rhs {j} prec={prec}")
 
 
-@pytest.mark.parametrize("N", [512, 513, 1000, 1985, 33000])
+@pytest.mark.parametrize("N", [512, 513, 1500, 1985, 4033, 5000, 33000])
 @pytest.mark.parametrize("prec", [0, 1])
-def test_vjp_epilogue(rp, orc, N, prec):
-    """Odd and even numbers of groups of 64, a last wave of one blob, and
-    groups of 256."""
+def test_vjp_splits(rp, orc, N, prec):
+    """FP64 passes split 16, 8 and 4 ways and not at all, records formed by the
+    pair kernel and packed before it, groups of 64 and of 256, odd and even
+    numbers of groups, a last wave of one blob."""
     pos = 0.9 * _mixed(N, N)
     f, g = np.random.default_rng(N + 1).standard_normal((2, N, 3))
     gp, gf = rp.matvec_vjp(_t(pos), _t(f), _t(g), 0.9, 1.3, precision=prec)
-    rows = None if N < 5000 else np.r_[0:8, N - 8:N]
+    rows = None if N < 4000 else np.r_[0:8, N - 8:N]
     gp_ref, gf_ref = orc.vjp(pos, f, g, 0.9, 1.3, rows=rows)
     at = slice(None) if rows is None else rows
     check(gp.cpu().numpy()[at], gp_ref, TOL[prec], f"vjp N={N} prec={prec} grad_pos")
