@@ -365,7 +365,10 @@ int rpy_wall_set_shape(int precision, int64_t N, int32_t k, int32_t tpl, int32_t
 
 /* The launch shape later products of this precision and size class will
  * use: out6 = {tpl, tile, kblk, sym, ipw, mat} (HOST int32[6]), as for
- * rpy_wall_set_shape.  Host-only. */
+ * rpy_wall_set_shape.  Host-only.  Without a fixed shape, FP64 products of
+ * small problems (up to 2048 blobs for k <= 4, 1536 for k <= 8, else 1280) run
+ * in one launch instead, which has no shape; the Lanczos, rigid and VJP calls
+ * of these sizes use the shape. */
 int rpy_wall_get_shape(int precision, int64_t N, int32_t k, int32_t* out6);
 
 /* Host-only: coefficients c = beta0 T^{1/2} e1 = beta0 Q Lambda^{1/2} Q^T e1

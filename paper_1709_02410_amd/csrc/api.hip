@@ -121,6 +121,17 @@ Shape default_shape(int64_t N, int k, int prec) {
     return s;
 }
 
+// FP64 products of this size run in one launch (direct_pairs.h) unless a
+// shape is fixed.  The lines lie where the other kernels catch up (us a
+// call): one right-hand side 14.8 against 17.3 at 2000 blobs, 21.3 against
+// 21 at 2500; two 18.1 against 23, 27 against 27; four 28.6 against 31, 39.8
+// against 39; eight 35.4 against 44.7 at 1500, 52.2 against 47.6 at 2000 (plain);
+// sixteen, in two blocks of 8, 33 against 73 at 1000, 70.7 against 67.7 at 1500
+// (matrix cores).
+static bool direct_rule(int64_t N, int k, int prec) {
+    return prec == RPYW_FP64 && N <= (k <= 4 ? 2048 : k <= 8 ? 1536 : 1280);
+}
+
 namespace {
 // Persisted shapes: loaded once (under g_shape_mu) from RPYW_AUTOTUNE_CACHE;
 // entries of other GPU architectures are kept for the rewrite.
@@ -178,7 +189,9 @@ Shape tuned_shape(int64_t N, int k, int prec) {
     auto ov = g_overrides.find(key);
     if (ov != g_overrides.end()) return apply_env_overrides(ov->second);
     auto it = g_shapes.find(key);
-    return apply_env_overrides(it != g_shapes.end() ? it->second : default_shape(N, k, prec));
+    Shape s = apply_env_overrides(it != g_shapes.end() ? it->second : default_shape(N, k, prec));
+    s.direct = direct_rule(N, k, prec);
+    return s;
 }
 
 void set_tuned_shape(int64_t N, int k, int prec, Shape s) {

@@ -22,10 +22,11 @@
 #include <mutex>
 #include <vector>
 
+#include "direct_pairs.h"
+#include "mat_pairs.h"
 #include "pair_math.h"
 #include "records.h"
 #include "rpyw_internal.h"
-#include "mat_pairs.h"
 #include "sym_pairs.h"
 
 namespace rpyw {
@@ -792,6 +793,40 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     return RPYW_OK;
 }
 
+namespace {
+
+// FP64 products of small problems, in blocks of up to 8 right-hand sides.
+template <int K>
+void launch_direct(const double* pos, const double* F, double* U, int64_t N, int kb, double a, double eta,
+                   hipStream_t st) {
+    hipLaunchKernelGGL((direct_kernel<K>), dim3((unsigned)((N + kDirectTargets - 1) / kDirectTargets)),
+                       dim3(kDirectThreads), 0, st, pos, F, N, kb, 1.0 / a, mu0_of(a, eta), U);
+}
+
+int direct_products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta,
+                    hipStream_t st) {
+    for (int k0 = 0; k0 < k; k0 += 8) {
+        const int kb = std::min(8, k - k0);
+        const double* Fk = F + (size_t)k0 * N * 3;
+        double* Uk = U + (size_t)k0 * N * 3;
+        hipEvent_t ev = nullptr;
+        profile_begin(st, &ev);
+        if (kb == 1)
+            launch_direct<1>(pos, Fk, Uk, N, kb, a, eta, st);
+        else if (kb == 2)
+            launch_direct<2>(pos, Fk, Uk, N, kb, a, eta, st);
+        else if (kb <= 4)
+            launch_direct<4>(pos, Fk, Uk, N, kb, a, eta, st);
+        else
+            launch_direct<8>(pos, Fk, Uk, N, kb, a, eta, st);
+        RPYW_HIP(hipGetLastError());
+        profile_end(st, ev, (double)kb * (double)N * (double)N);
+    }
+    return RPYW_OK;
+}
+
+}  // namespace
+
 int products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
              Arena& ar, hipStream_t st, const Domain& dom) {
     if (dom.periodic()) {
@@ -809,6 +844,7 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
         return RPYW_OK;
     }
     Shape sh = tuned_shape(N, k, prec);
+    if (sh.direct) return direct_products(pos, F, U, N, k, a, eta, st);
     if (prec != RPYW_FP32C && !sh.mat) sh.kblk = std::min(sh.kblk, 8);  // e.g. RPYW_RHS_WIDTH=16 on the vector units
     for (int k0 = 0; k0 < k; k0 += sh.kblk) {
         const int kb = std::min(sh.kblk, k - k0);

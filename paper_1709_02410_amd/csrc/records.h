@@ -68,6 +68,27 @@ __device__ __forceinline__ void make_record(const double* __restrict__ pos, cons
     *B = b;
 }
 
+// The FP64 record of blob i for K right-hand sides of which kb are given (the
+// others are zero), in registers: make_record's loops over a count known only
+// at run time put its record in scratch memory.  Blobs i >= N as there.
+template <int K>
+struct BlobRecord {
+    double x, y, z, f[3 * K];
+    __device__ __forceinline__ void load(const double* __restrict__ pos, const double* __restrict__ F, int64_t N,
+                                         int kb, double inv_a, int64_t i) {
+        const bool pad = i >= N;
+        const int64_t j = pad ? N - 1 : i;
+        const double h = pos[3 * j + 2] * inv_a;
+        const double b = h < 1.0 ? h : 1.0;
+        x = pad ? 1e6 : pos[3 * j] * inv_a;
+        y = pad ? 1e6 : pos[3 * j + 1] * inv_a;
+        z = (pad || h < 1.0) ? 1.0 : h;
+#pragma unroll
+        for (int q = 0; q < 3 * K; ++q)
+            f[q] = (pad || q / 3 >= kb) ? 0.0 : b * F[((q / 3) * N + j) * 3 + q % 3];
+    }
+};
+
 // Records for blobs [0, Npad) (make_record; Npad >= N), and B when Bout is
 // given.
 template <typename R>

@@ -30,6 +30,7 @@ struct Shape {
     int sym;   // symmetric pair evaluation (kblk <= 4): 0 off, 1 groups of 256 blobs, 2 groups of 64
     int ipw;   // symmetric path: source groups per workgroup
     int mat = 0;  // FP32C blocks of 8 or 16 right-hand sides: contraction on the matrix cores
+    bool direct = false;  // small FP64 products in one launch (direct_pairs.h); never of a fixed shape
 };
 
 // Domain along the wall: open (lx = ly = 0) or the pseudo-periodic cell

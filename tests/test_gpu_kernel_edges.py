@@ -61,3 +61,17 @@ def test_vjp_splits(rp, orc, N, prec):
     at = slice(None) if rows is None else rows
     check(gp.cpu().numpy()[at], gp_ref, TOL[prec], f"vjp N={N} prec={prec} grad_pos")
     check(gf.cpu().numpy()[at], gf_ref, TOL[prec], f"vjp N={N} prec={prec} grad_f")
+
+
+@pytest.mark.parametrize("N", [1, 2, 255, 256, 257, 513, 1281, 2047])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 8, 9])
+def test_one_launch_products(rp, orc, N, k):
+    """FP64 products in one launch: a workgroup with one target of its two,
+    fewer sources than threads, every block width and its remainder, two
+    blocks.  (Above 1280 and 1536 blobs the wider ones take other kernels.)"""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + k).standard_normal((k, N, 3))
+    U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=0).cpu().numpy()
+    for j in {0, k // 2, k - 1}:
+        check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"one launch N={N} k={k} rhs {j}")
+
