@@ -350,7 +350,10 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
  * the symmetric kernel, which evaluates each unordered pair once and applies
  * it in both directions (kblk <= 4), over groups of 256 blobs (1) or of 64
  * blobs (2, more workgroups for small problems; taken for N <= 32768, else
- * groups of 256); ipw: source groups per workgroup of the symmetric kernel;
+ * groups of 256); in FP64 and the open domain both select the kernel with two
+ * targets per lane over groups of 128 (one right-hand side: 3584 <= N <= 32768;
+ * more: N <= 131072, else the plain kernel); ipw: source groups per workgroup
+ * of the symmetric kernel;
  * mat: 1 contracts the 3 x 3 pair blocks with the RHS block on the matrix
  * cores (kblk 8 or 16, in FP64 the only way to a block of 16; tpl, tile,
  * sym and ipw then do not apply), 0 on the vector units.  The batched

@@ -105,7 +105,11 @@ int64_t g_prof_n = 0;
 // below ten thousand blobs (which leave the GPU underfilled) and still 5% at
 // 30000; wider RHS blocks are faster on the plain kernel, and FP32C blocks
 // of 8 or more are contracted on the matrix cores.  For groups of 256
-// ipw keeps the grid at roughly 16k workgroups or more.
+// ipw keeps the grid at roughly 16k workgroups or more.  In FP64 two targets
+// per lane (sym_multi.h) make the symmetric kernel the faster one for up to
+// four right-hand sides as well; 5 or 6 right-hand sides go in a block of 4
+// and the rest (at 3840 blobs 85 and 92 against 102 us for one block of 8 on
+// the plain kernel, at 20000 1.67 and 1.85 against 2.01 ms; 7 take longer).
 Shape default_shape(int64_t N, int k, int prec) {
     Shape s;
     s.tpl = N >= 65536 ? 2 : 1;
@@ -118,6 +122,16 @@ Shape default_shape(int64_t N, int k, int prec) {
     const int64_t ng = (N + 255) / 256, hm = ng / 2 + 1;
     s.ipw = s.sym == 2 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(4, hm * ng / 16384));
     s.mat = (s.kblk >= (prec == RPYW_FP32C ? 8 : 16)) ? 1 : 0;
+    if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : 512) && k <= 6 && N <= (k == 1 ? kSym2MaxN1 : kSym2MaxN)) {
+        s.kblk = std::min(s.kblk, 4);
+        if (!s.sym) s.sym = 1;
+        // source groups per workgroup: the target side is loaded and written
+        // less often while the grid still has rounds to spare (one and two:
+        // 30.9 and 34.7 us at 3840 blobs, 100.6 and 100.5 at 8000, 575 and
+        // 574 at 20000; four right-hand sides 1123 and 1093 there)
+        const int64_t g = (N + 127) / 128, items = g * (g / 2 + 1);
+        s.ipw = items < 2048 ? 1 : items < 32768 ? 2 : 4;
+    }
     return s;
 }
 
@@ -635,7 +649,8 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             if (cand >= 6) sh = Shape{1 + ((cand - 6) & 1), ((cand - 6) & 2) ? 256 : 64, kb, 0, 4};
             if (cand >= 6 && kb >= 8 && sh.tpl == 2) continue;
             if (cand < 6 && kb > 4) continue;
-            if (sh.sym == 2 && N > kSym64MaxN) continue;
+            // FP64: one symmetric kernel from here on
+            if (sh.sym == 2 && (N > kSym64MaxN || (precision == RPYW_FP64 && (kb > 1 || N >= kSym2MinN1)))) continue;
             if (cand == 6 && kb >= 8) {
                 Shape m{1, 64, kb, 0, 4};
                 m.mat = 1;

@@ -305,8 +305,7 @@ namespace {
 // as the unfused driver below up to rounding (different summation orders).
 int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, double a, double eta,
                   const int64_t* body_offsets, int n_bodies, double tol, int max_iter, int prec, Arena& ar, int* iters,
-                  double* err, hipStream_t st, const Domain& dom, const BodyFactors* pre, const SymPlan& sp,
-                  int ipw) {
+                  double* err, hipStream_t st, const Domain& dom, const BodyFactors* pre, const SymPlan& sp) {
     const int64_t n3 = 3 * N;
     *iters = 0;
     *err = 0.0;
@@ -432,7 +431,7 @@ int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, do
         int r;
         hipEvent_t ev = nullptr;
         profile_begin(st, &ev);
-        if ((r = sym_launch(rec, sp, ipw, 1, prec, a, dom, tpart, spart, st))) return r;
+        if ((r = sym_launch(rec, sp, 1, prec, a, dom, tpart, spart, st))) return r;
         profile_end(st, ev, (dom.periodic() ? 9.0 : 1.0) * (double)N * (double)N);
         if (ypre && (r = sym_finish(tpart, spart, B, N, 1, 1, prec, sp, m0, ypre, st, nullptr, 1.0 / a))) return r;
         if ((r = lz_launch_out(prec, pc, d_units, d_groups, ngroups, tpart, spart, sp, B, m0, n3, k, V, d_ab, w,
@@ -559,10 +558,9 @@ int lanczos_sqrt(const double* pos, const double* W, double* out, int64_t N, dou
                  double* err, hipStream_t st, const Domain& dom, const BodyFactors* pre) {
     {
         SymPlan sp;
-        int ipw;
-        if (lanczos_fused_applies(N, prec, max_iter, dom, &sp, &ipw))
+        if (lanczos_fused_applies(N, prec, max_iter, dom, &sp))
             return lanczos_fused(pos, W, out, N, a, eta, body_offsets, n_bodies, tol, max_iter, prec, ar, iters, err,
-                                 st, dom, pre, sp, ipw);
+                                 st, dom, pre, sp);
     }
     const int64_t n3 = 3 * N;
     *iters = 0;

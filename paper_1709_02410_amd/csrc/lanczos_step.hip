@@ -504,18 +504,13 @@ __global__ __launch_bounds__(kVinThreads) void lz_fin_kernel(int diag, const int
 
 }  // namespace
 
-bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom, SymPlan* sp, int* ipw) {
+bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom, SymPlan* sp) {
     if (max_iter > kLanczosFusedMaxIter) return false;
-    // the plan products() would use for one right-hand side
+    // the symmetric plan of products of one right-hand side
     const Shape sh = tuned_shape(N, 1, prec);
     if (!dom.periodic() && !(sh.sym && sh.kblk <= 4)) return false;
-    const int w = sh.ipw < 1 ? 4 : sh.ipw;
-    SymPlan p = sym_plan(N, prec, 1, w, dom.periodic() ? (sh.sym == 1 ? 256 : 64) : sym_group(sh.sym));
-    if (!p.ok && p.G == 64) p = sym_plan(N, prec, 1, w, 256);
-    if (!p.ok) return false;
-    *sp = p;
-    *ipw = w;
-    return true;
+    *sp = sym_choose(N, prec, 1, sh.ipw < 1 ? 4 : sh.ipw, sh.sym, dom);
+    return sp->ok;
 }
 
 int64_t lanczos_gs2_blocks(int64_t n3, int* m) {

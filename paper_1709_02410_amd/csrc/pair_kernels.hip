@@ -27,6 +27,7 @@
 #include "pair_math.h"
 #include "records.h"
 #include "rpyw_internal.h"
+#include "sym_multi.h"
 #include "sym_pairs.h"
 
 namespace rpyw {
@@ -389,12 +390,13 @@ __global__ __launch_bounds__(64 * kEpiParts) void sym_epilogue(const double* __r
     U[((int64_t)(q / 3) * N + i) * 3 + q % 3] = mu0 * b * s;
 }
 
-// ps: the kernel forms its records from ps (groups of 64 only); otherwise
-// they are read from rec.
+// ps: the kernel forms its records from ps (groups of 64 and 128 only);
+// otherwise they are read from rec.
 template <typename R, int K, int PER>
-hipError_t launch_sym_t(const R* rec, const SymPlan& sp, int ipw, double* tpart, R* spart, const Box<R>& box,
-                        hipStream_t st, const PackSrc* ps = nullptr) {
+hipError_t launch_sym_t(const R* rec, const SymPlan& sp, double* tpart, R* spart, const Box<R>& box, hipStream_t st,
+                        const PackSrc* ps = nullptr) {
     const dim3 grid((unsigned)((int64_t)sp.ng * sp.C * sp.nseg));
+    const int ipw = sp.ipw;
     const PackSrc p0 = ps ? *ps : PackSrc{};
     if (ps && sp.G != 64) return hipErrorInvalidValue;
     if (sp.G == 64 && sp.ns == 4) {
@@ -415,6 +417,22 @@ hipError_t launch_sym_t(const R* rec, const SymPlan& sp, int ipw, double* tpart,
         hipLaunchKernelGGL((sym_kernel<R, ProductBody<R, K, PER>, 4>), grid, dim3(256), 0, st, rec, sp.ng, sp.C, ipw,
                            sp.Hmax, sp.nseg, tpart, spart, box, p0);
     }
+    return hipGetLastError();
+}
+
+// Groups of 128 (FP64, open domain).
+template <int K>
+hipError_t launch_sym2_t(const double* rec, const SymPlan& sp, double* tpart, double* spart, hipStream_t st,
+                         const PackSrc* ps) {
+    const dim3 grid((unsigned)((int64_t)sp.ng * sp.C * sp.nseg));
+    if (ps)
+        hipLaunchKernelGGL((sym2_kernel<K, true>), grid, dim3(256), 0, st, rec, *ps, sp.ng, sp.C, sp.ipw, sp.Hmax,
+                           sp.nseg, tpart, spart);
+    else if constexpr (K == 1)  // only the Krylov steps keep records, of one right-hand side
+        hipLaunchKernelGGL((sym2_kernel<K, false>), grid, dim3(256), 0, st, rec, PackSrc{}, sp.ng, sp.C, sp.ipw,
+                           sp.Hmax, sp.nseg, tpart, spart);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -558,30 +576,58 @@ double mu0_of(double a, double eta) { return 1.0 / (6.0 * M_PI * eta * a); }
 
 SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G) {
     SymPlan s{};
-    s.G = G == 64 ? 64 : 256;
+    s.G = G == 64 || G == 128 ? G : 256;
     s.ng = (int)((N + s.G - 1) / s.G);
     s.Hmax = s.ng / 2;
     if (ipw < 1) ipw = 1;
+    // The target partials of groups of 128 are kept to a quarter of the
+    // source partials on large problems.
+    if (s.G == 128 && N > kSym2MaxN1) ipw = std::max(ipw, 4);
+    s.ipw = ipw;
     s.C = (s.Hmax + 1 + ipw - 1) / ipw;
     // Segments: enough work items to give every SIMD several (independent
     // of ipw, so that the workspace bound taken at ipw 1 holds).
     const int64_t items = (int64_t)s.ng * (s.Hmax + 1);
-    // Groups of 64 split the passes of few items over 4 waves of one
-    // workgroup first (their sums meet in LDS), and over workgroups (each
-    // with partials of its own) only when there are fewer than half as many
-    // waves as wanted.
-    s.ns = (s.G == 64 && items < kSymItemsMin) ? 4 : 1;
-    const int64_t want = s.ns > 1 ? kSymItemsMin / 2 : kSymItemsMin;
-    s.nseg = 1;
-    while (s.nseg < 4 && items * s.ns * s.nseg < want) s.nseg *= 2;
-    if (s.G == 64) sym_split_override(&s.ns, &s.nseg);
+    s.ns = s.nseg = 1;
+    if (s.G == 128) {
+        // An item is four waves of 32 double steps.  Segments until more than
+        // half of the CUs have one: 1500 blobs (84 items, one and two
+        // right-hand sides) 20.7 -> 14.2 and 24 -> 16.6 us, 2000 (144) 20.9 -> 19.4
+        // and 24.5 -> 23.1; 3840 (480) 30.9 -> 32.4 and 38.5 -> 42.5.
+        while (s.nseg < 4 && items * s.nseg < 160) s.nseg *= 2;
+    } else {
+        // Groups of 64 split the passes of few items over 4 waves of one
+        // workgroup first (their sums meet in LDS), and over workgroups (each
+        // with partials of its own) only when there are fewer than half as
+        // many waves as wanted.
+        s.ns = (s.G == 64 && items < kSymItemsMin) ? 4 : 1;
+        const int64_t want = s.ns > 1 ? kSymItemsMin / 2 : kSymItemsMin;
+        while (s.nseg < 4 && items * s.ns * s.nseg < want) s.nseg *= 2;
+        if (s.G == 64) sym_split_override(&s.ns, &s.nseg);
+    }
     const size_t npad = (size_t)s.ng * s.G;
     s.rec_bytes = align_up(npad * rec_width(prec, K) * real_size(prec)) + align_up(npad * sizeof(double));
     s.tpart_bytes = align_up((size_t)s.ng * s.C * s.nseg * 3 * K * s.G * sizeof(double));
     s.spart_bytes = align_up((size_t)s.ng * (s.Hmax + 1) * s.nseg * 3 * K * s.G * real_size(prec));
     s.ok = K <= 4 && s.spart_bytes <= kSymPartialMaxBytes && s.tpart_bytes <= kSymPartialMaxBytes &&
-           (s.G == 256 || N <= kSym64MaxN);
+           (s.G != 64 || N <= kSym64MaxN) &&
+           (s.G != 128 || (prec == RPYW_FP64 && (K > 1 || N >= kSym2MinN1) && N <= (K == 1 ? kSym2MaxN1 : kSym2MaxN)));
     return s;
+}
+
+SymPlan sym_choose(int64_t N, int prec, int K, int ipw, int sym, const Domain& dom) {
+    if (prec == RPYW_FP64 && !dom.periodic()) {
+        const SymPlan s = sym_plan(N, prec, K, ipw, 128);
+        if (s.ok || K > 1) return s;
+    }
+    // Periodic products are always symmetric: groups of 64 unless the shape
+    // asks for groups of 256.
+    const bool g64 = dom.periodic() ? sym != 1 : sym == 2;
+    if (g64) {
+        const SymPlan s = sym_plan(N, prec, K, ipw, 64);
+        if (s.ok) return s;
+    }
+    return sym_plan(N, prec, K, ipw, 256);
 }
 
 void split_plan(int64_t N, int tpl, int* splits, int64_t* chunk) {
@@ -627,7 +673,7 @@ size_t product_ws_bytes(int64_t N, int prec, int kblk) {
     b += align_up((size_t)smax * kblk * 3 * N * sizeof(double));
     size_t sb = 0;
     for (int K = 1; K <= std::min(kblk, 4); K <<= 1)
-        for (int G : {256, 64}) {
+        for (int G : {256, 128, 64}) {
             const SymPlan sp = sym_plan(N, prec, K, 1, G);
             if (sp.ok) sb = std::max(sb, sp.rec_bytes + sp.tpart_bytes + sp.spart_bytes);
         }
@@ -637,7 +683,7 @@ size_t product_ws_bytes(int64_t N, int prec, int kblk) {
 namespace {
 
 int sym_pass(const double* pos, const double* F, double* U, int64_t N, int kb, int K, double a, double eta, int prec,
-             const SymPlan& sp, int ipw, Arena& ar, hipStream_t st, const Domain& dom = Domain{}) {
+             const SymPlan& sp, Arena& ar, hipStream_t st, const Domain& dom = Domain{}) {
     const size_t mark = ar.used;
     double* tpart = (double*)ar.take(sp.tpart_bytes);
     void* spart = ar.take(sp.spart_bytes);
@@ -645,10 +691,10 @@ int sym_pass(const double* pos, const double* F, double* U, int64_t N, int kb, i
         ar.used = mark;
         return RPYW_ENOMEM;
     }
-    // Groups of 64 (small problems): the pair kernel forms the records
-    // itself, two launches per product; otherwise the records are packed
-    // once by their own kernel.
-    const bool fused = sp.G == 64;
+    // Groups of 64 and of 128: the pair kernel forms the records itself, two
+    // launches per product; otherwise the records are packed once by their
+    // own kernel.
+    const bool fused = sp.G != 256;
     const PackSrc ps{pos, F, N, kb, 1.0 / a, dom.lx / a, dom.ly / a};
     void* rec = nullptr;
     double* B = nullptr;
@@ -667,7 +713,7 @@ int sym_pass(const double* pos, const double* F, double* U, int64_t N, int kb, i
     if (rc == RPYW_OK) {
         hipEvent_t ev = nullptr;
         profile_begin(st, &ev);
-        rc = sym_launch(rec, sp, ipw, K, prec, a, dom, tpart, spart, st, fused ? &ps : nullptr);
+        rc = sym_launch(rec, sp, K, prec, a, dom, tpart, spart, st, fused ? &ps : nullptr);
         if (rc == RPYW_OK) {
             profile_end(st, ev, (dom.periodic() ? 9.0 : 1.0) * (double)kb * (double)N * (double)N);
             rc = sym_finish(tpart, spart, B, N, kb, K, prec, sp, mu0_of(a, eta), U, st, pos, 1.0 / a);
@@ -694,8 +740,8 @@ int sym_pack(const double* pos, const double* F, int64_t N, int kb, int K, int p
     return RPYW_OK;
 }
 
-int sym_launch(const void* rec, const SymPlan& sp, int ipw, int K, int prec, double a, const Domain& dom,
-               double* tpart, void* spart, hipStream_t st, const PackSrc* ps) {
+int sym_launch(const void* rec, const SymPlan& sp, int K, int prec, double a, const Domain& dom, double* tpart,
+               void* spart, hipStream_t st, const PackSrc* ps) {
     auto go = [&](auto Rt, auto Kc) -> hipError_t {
         using R = decltype(Rt);
         constexpr int KK = decltype(Kc)::value;
@@ -705,13 +751,16 @@ int sym_launch(const void* rec, const SymPlan& sp, int ipw, int K, int prec, dou
                 // 4-7% slower, in FP64 up to 10% faster
                 if constexpr (sizeof(R) == 8)
                     if (std::min(dom.lx, dom.ly) > 4.5 * a)
-                        return launch_sym_t<R, 1, 2>((const R*)rec, sp, ipw, tpart, (R*)spart, make_box<R>(dom, a),
-                                                     st, ps);
-                return launch_sym_t<R, 1, 1>((const R*)rec, sp, ipw, tpart, (R*)spart, make_box<R>(dom, a), st, ps);
+                        return launch_sym_t<R, 1, 2>((const R*)rec, sp, tpart, (R*)spart, make_box<R>(dom, a), st, ps);
+                return launch_sym_t<R, 1, 1>((const R*)rec, sp, tpart, (R*)spart, make_box<R>(dom, a), st, ps);
             }
             return hipErrorInvalidValue;
         }
-        return launch_sym_t<R, KK, 0>((const R*)rec, sp, ipw, tpart, (R*)spart, Box<R>{}, st, ps);
+        if constexpr (sizeof(R) == 8)
+            if (sp.G == 128) return launch_sym2_t<KK>((const R*)rec, sp, tpart, (R*)spart, st, ps);
+        if constexpr (sizeof(R) == 4 || KK == 1)  // FP64 has the other groups for one right-hand side
+            return launch_sym_t<R, KK, 0>((const R*)rec, sp, tpart, (R*)spart, Box<R>{}, st, ps);
+        return hipErrorInvalidValue;
     };
     hipError_t e;
     if (prec == RPYW_FP32C)
@@ -744,9 +793,8 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     if (kb < 1 || kb > K) return RPYW_EINVAL;
     sh = normalized(sh, K, prec);
     if (sh.sym && K <= 4) {
-        SymPlan sp = sym_plan(N, prec, K, sh.ipw, sym_group(sh.sym));
-        if (!sp.ok && sp.G == 64) sp = sym_plan(N, prec, K, sh.ipw, 256);
-        if (sp.ok) return sym_pass(pos, F, U, N, kb, K, a, eta, prec, sp, sh.ipw, ar, st);
+        const SymPlan sp = sym_choose(N, prec, K, sh.ipw, sh.sym, Domain{});
+        if (sp.ok) return sym_pass(pos, F, U, N, kb, K, a, eta, prec, sp, ar, st);
     }
     const int rw = rec_width(prec, K);
     void* rec = ar.take((size_t)N * rw * real_size(prec));
@@ -830,15 +878,13 @@ int direct_products(const double* pos, const double* F, double* U, int64_t N, in
 int products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
              Arena& ar, hipStream_t st, const Domain& dom) {
     if (dom.periodic()) {
-        // Always symmetric (one right-hand side per pass): groups of 64
-        // unless the shape asks for groups of 256.
+        // Always symmetric, one right-hand side per pass.
         const Shape sh = tuned_shape(N, 1, prec);
-        SymPlan sp = sym_plan(N, prec, 1, sh.ipw, sh.sym == 1 ? 256 : 64);
-        if (!sp.ok) sp = sym_plan(N, prec, 1, sh.ipw, 256);
+        const SymPlan sp = sym_choose(N, prec, 1, sh.ipw, sh.sym, dom);
         if (!sp.ok) return RPYW_ENOMEM;
         for (int k0 = 0; k0 < k; ++k0) {
             const int rc = sym_pass(pos, F + (size_t)k0 * N * 3, U + (size_t)k0 * N * 3, N, 1, 1, a, eta, prec, sp,
-                                    sh.ipw, ar, st, dom);
+                                    ar, st, dom);
             if (rc != RPYW_OK) return rc;
         }
         return RPYW_OK;

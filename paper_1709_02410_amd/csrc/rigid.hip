@@ -374,7 +374,7 @@ namespace {
 int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets, int n_bodies, const double* slip,
                 const double* FT, double* lam_out, double* U_out, int64_t N, double a, double eta, double tol,
                 int max_iter, int prec, Arena& ar, int* iters, double* res_out, hipStream_t st, const Domain& dom,
-                const BodyFactors* pre, const SymPlan& sp, int ipw) {
+                const BodyFactors* pre, const SymPlan& sp) {
     const int64_t n3 = 3 * N, n6 = 6 * (int64_t)n_bodies, n = n3 + n6;
     *iters = 0;
     *res_out = 0.0;
@@ -469,7 +469,7 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
     };
     auto launch_step = [&](int k) -> int {
         int r;
-        if ((r = sym_launch(rec, sp, ipw, 1, prec, a, dom, tpart, spart, st))) return r;
+        if ((r = sym_launch(rec, sp, 1, prec, a, dom, tpart, spart, st))) return r;
         if (ypre && (r = sym_finish(tpart, spart, B, N, 1, 1, prec, sp, m0, ypre, st, nullptr, 1.0 / a))) return r;
         if ((r = rg_launch_out(prec, pos, q, pc.bofs, n_bodies, tpart, spart, sp, B, m0, zb, zb + n3, n3, n, V, k, wb,
                                part1, ypre, st)))
@@ -567,10 +567,9 @@ int rigid_solve(const double* pos, const double* q, const int64_t* body_offsets,
                 const BodyFactors* pre) {
     {
         SymPlan sp;
-        int ipw;
-        if (n_bodies > 0 && lanczos_fused_applies(N, prec, max_iter, dom, &sp, &ipw))
+        if (n_bodies > 0 && lanczos_fused_applies(N, prec, max_iter, dom, &sp))
             return rigid_fused(pos, q, body_offsets, n_bodies, slip, FT, lam_out, U_out, N, a, eta, tol, max_iter,
-                               prec, ar, iters, res_out, st, dom, pre, sp, ipw);
+                               prec, ar, iters, res_out, st, dom, pre, sp);
     }
     const int64_t n3 = 3 * N, n6 = 6 * (int64_t)n_bodies, n = n3 + n6;
     *iters = 0;

@@ -43,7 +43,8 @@ struct Domain {
 
 // Symmetric path geometry for N blobs, K right-hand sides.
 struct SymPlan {
-    int G;     // blobs per group: 256 or 64
+    int G;     // blobs per group: 256 or 64, or 128 (FP64, open domain: sym_multi.h)
+    int ipw;   // source groups per workgroup
     int ns;    // waves per item that split its passes (1, or 4 for groups of 64 when items are few)
     int nseg;  // workgroups per item that split its passes (1, 2 or 4: more workgroups for tiny problems)
     int ng, Hmax, C;
@@ -65,23 +66,36 @@ constexpr int64_t kSymItemsMin = 8192;
 // competitive); beyond it products use the plain kernel, whose workspace
 // grows as N.
 constexpr size_t kSymPartialMaxBytes = (size_t)16 << 30;
-SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G = 256);
+// Problems of the FP64 kernel with groups of 128 and one right-hand side: below
+// them groups of 64 spread better (24.7 against 31.8 us at 3000 blobs, 34.9
+// against 31.0 at 3840), beyond them groups of 256 run at the same speed with
+// half the partials.  With more right-hand sides: up to kSym2MaxN (beyond it
+// the plain kernel).
+constexpr int64_t kSym2MinN1 = 3584;
+constexpr int64_t kSym2MaxN1 = 32768;
+constexpr int64_t kSym2MaxN = 131072;
+// Plan for groups of G blobs; ok is false when N or K is out of its range.
+SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G);
 inline int sym_group(int sym) { return sym == 2 ? 64 : 256; }
+// The plan a symmetric product uses: `sym` as in Shape; FP64 products in the
+// open domain take groups of 128 within their range, whichever sym asks for.
+// not ok: no symmetric kernel for this size.
+SymPlan sym_choose(int64_t N, int prec, int K, int ipw, int sym, const Domain& dom);
 // The three stages of a symmetric product pass, for callers that keep the
 // records between passes (the Krylov solvers):
 //   sym_pack   records (positions, wrapped into the cell when periodic, and
 //              B f for kb right-hand sides; padded records are force-free
 //              blobs far away) and B, for ng G blobs;
 //   sym_launch the pair kernel over the records into the partial sums (with
-//              ps, groups of 64 only: the kernel forms the records from
-//              positions and right-hand sides itself; rec is unused);
+//              ps, groups of 64 and 128 only: the kernel forms the records
+//              from positions and right-hand sides itself; rec is unused);
 //   sym_finish U = mu0 B (sum of the partials), fixed order (B null: B from
 //              the positions, pos and 1 / a given).
 int sym_pack(const double* pos, const double* F, int64_t N, int kb, int K, int prec, const SymPlan& sp, double a,
              const Domain& dom, void* rec, double* B, hipStream_t st);
 struct PackSrc;
-int sym_launch(const void* rec, const SymPlan& sp, int ipw, int K, int prec, double a, const Domain& dom,
-               double* tpart, void* spart, hipStream_t st, const PackSrc* ps = nullptr);
+int sym_launch(const void* rec, const SymPlan& sp, int K, int prec, double a, const Domain& dom, double* tpart,
+               void* spart, hipStream_t st, const PackSrc* ps = nullptr);
 int sym_finish(const double* tpart, const void* spart, const double* B, int64_t N, int kb, int K, int prec,
                const SymPlan& sp, double mu0, double* U, hipStream_t st, const double* pos = nullptr,
                double inv_a = 1.0);
@@ -194,7 +208,7 @@ struct LanczosGroup {
 };
 constexpr int kLanczosGroupUnits = kLanczosOutEntries / 3 + 1;  // units of a group, at most
 struct BodyFactors;
-bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom, SymPlan* sp, int* ipw);
+bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom, SymPlan* sp);
 int64_t lanczos_gs2_blocks(int64_t n3, int* m);
 void lanczos_units(int64_t N, const int64_t* body_offsets, int n_bodies, std::vector<int>& units,
                    std::vector<int>& groups);

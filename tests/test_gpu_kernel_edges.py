@@ -75,3 +75,23 @@ def test_one_launch_products(rp, orc, N, k):
     for j in {0, k // 2, k - 1}:
         check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"one launch N={N} k={k} rhs {j}")
 
+
+@pytest.mark.parametrize("N,k,ipw", [(N, k, ipw) for N in (1, 64, 65, 128, 129, 257, 1500, 2049, 2305)
+                                     for k, ipw in ((2, 1), (3, 4), (4, 2))]
+                         + [(3584, 1, 1), (3649, 1, 3), (3713, 1, 2), (5000, 1, 1)])
+def test_two_targets_per_lane(rp, orc, N, k, ipw):
+    """The FP64 symmetric kernel over groups of 128: one group (diagonal items
+    alone), half-filled and nearly empty last groups, odd and even numbers of
+    groups, passes split 4 and 2 ways and not at all, chunks of several items
+    and a last chunk of fewer."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + k).standard_normal((k, N, 3))
+    rp.set_shape(0, N, k, kblk=1 if k == 1 else 2 if k == 2 else 4, sym=1, ipw=ipw)
+    try:
+        U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=0)
+        again = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=0)
+    finally:
+        rp.reset_shape(0, N, k)
+    assert torch.equal(U, again)
+    for j in range(k):
+        check(U[j].cpu().numpy(), orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"two targets N={N} k={k} rhs {j}")
