@@ -6,6 +6,8 @@
 // kernels (update, dot products with a fixed-order finish, combination).
 // All reductions use a fixed order, so results are bitwise reproducible.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -651,6 +653,35 @@ int stage_upload(const void* src, size_t bytes, void* dst, hipStream_t st) {
     RPYW_HIP(hipEventRecord(ev, st));
     g_ring.busy.push_back({off, len, ev});
     g_ring.head = off + len;
+    return RPYW_OK;
+}
+
+int wait_published(const double* p, size_t n, hipStream_t st) {
+    using Clock = std::chrono::steady_clock;
+    const volatile uint64_t* v = reinterpret_cast<const volatile uint64_t*>(p);
+    bool drained = false;
+    Clock::time_point end{};
+    size_t i = 0;
+    for (unsigned spin = 1;; ++spin) {
+        while (i < n && v[i] != kPending) ++i;
+        if (i == n) break;
+        if ((spin & 4095) == 0) {
+            if (!drained) {
+                const hipError_t q = hipStreamQuery(st);
+                if (q == hipSuccess) {
+                    // what the kernels wrote may still be on its way
+                    drained = true;
+                    end = Clock::now() + std::chrono::milliseconds(100);
+                } else if (q != hipErrorNotReady) {
+                    return RPYW_EHIP;
+                }
+            } else if (Clock::now() > end) {
+                return RPYW_EHIP;
+            }
+        }
+        __builtin_ia32_pause();
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
     return RPYW_OK;
 }
 

@@ -14,6 +14,20 @@ namespace kstep {
 
 constexpr int kPre = 16;  // values loaded ahead of use per thread
 
+// A value for the polling host, straight to its pinned memory (wait_published;
+// no order between values is assumed, so no fence goes with it).
+__device__ __forceinline__ void publish(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// The call's header: a norm, and the definiteness flags of the factors as two
+// ints in one value.
+__device__ __forceinline__ void publish_header(double* h, double norm, const int* bad0, const int* bad1) {
+    const uint64_t b0 = (uint32_t)bad0[0], b1 = bad1 ? (uint32_t)bad1[0] : 0u;
+    publish(h, norm);
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(h + 1), b0 | b1 << 32, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sum over groups of G consecutive lanes (fixed butterfly order).
 template <int G>
 __device__ __forceinline__ double lane_group_sum(double s) {

@@ -18,7 +18,6 @@
 //   evaluated on c.  At the end out = L (V c).
 // All reductions are two-stage with a fixed order (bitwise reproducible).
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -390,7 +389,7 @@ int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, do
         !tpart || !spart || (krylov_presum(sp) && !ypre))
         return RPYW_ENOMEM;
     std::lock_guard<std::mutex> lk(g_ab.mu);
-    const size_t hdr_bytes = align_up((size_t)(3 * (max_iter + 2) + 2) * sizeof(double));
+    const size_t hdr_bytes = align_up((size_t)(2 * (max_iter + 2) + 2) * sizeof(double));
     int rc = g_ab.reserve(hdr_bytes + tbytes);
     if (rc) return rc;
     double* h_ab = g_ab.p;
@@ -401,11 +400,9 @@ int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, do
     double* h_b0 = h_ab + 2 * (max_iter + 2);
     int* h_bad = (int*)(h_b0 + 1);
     double* dh_hdr = dh_ab + (h_b0 - h_ab);
-    // step flags: set by the step's last kernel after alpha_k and beta_{k-1}
-    // (no event per step: an event between the steps' kernels delays the next)
-    double* h_flag = h_b0 + 2;
-    double* dh_flag = dh_ab + (h_flag - h_ab);
-    std::memset(h_flag, 0, (size_t)(max_iter + 2) * sizeof(double));
+    // the coefficients and the header are polled (no event per step: an event
+    // between the steps' kernels delays the next)
+    pending_fill(h_ab, 2 * (size_t)(max_iter + 2) + 2);
     // the tables after them
     std::memcpy((char*)h_ab + hdr_bytes, tb.host.data(), tbytes);
     const int* dh_tab = (const int*)((const char*)dh_ab + hdr_bytes);
@@ -421,10 +418,10 @@ int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, do
     // Step k: the product (its records written by vin of step k), w = L^-1
     // M x - beta_{k-1} v_{k-1} with the first projection, y' = w - V c1
     // with the second projection, then vin of step k + 1: beta_k, v_{k+1}
-    // and the next records; it publishes step k (alpha_k, beta_k, flag).
+    // and the next records; it publishes step k (alpha_k, beta_k).
     auto vin = [&](int k) {
         return lz_launch_vin(prec, pc, d_units, nunits, n3, k, k == 0 ? W : y, k == 0 ? sqp : part2,
-                             k == 0 ? (int)npack : (int)nblk4, V, d_ab, dh_ab, dh_flag, rec, rw, B, dh_hdr, notspd,
+                             k == 0 ? (int)npack : (int)nblk4, V, d_ab, dh_ab, rec, rw, B, dh_hdr, notspd,
                              pre ? pre->flag : nullptr, st);
     };
     auto launch_step = [&](int k) -> int {
@@ -462,25 +459,10 @@ int lanczos_fused(const double* pos, const double* W, double* out, int64_t N, do
     const auto t_call = Clock::now();
     if ((rc = vin(0))) return rc;
     if ((rc = fill(1 + depth))) return rc;
-    // Waits for step k: its flag in host memory, polled; the stream is
-    // queried now and then so that a stream that drains without setting it
-    // (a failed launch) ends the wait with an error instead of spinning.
+    // Waits for alpha_k and beta_k; step 0 also brings the header.
     auto wait_step = [&](int k) -> int {
-        const volatile double* f = h_flag + k;
-        for (unsigned spin = 1;; ++spin) {
-            if (*f != 0.0) break;
-            if ((spin & 4095) == 0) {
-                const hipError_t q = hipStreamQuery(st);
-                if (q == hipSuccess) {
-                    if (*f != 0.0) break;
-                    return RPYW_EHIP;
-                }
-                if (q != hipErrorNotReady) return RPYW_EHIP;
-            }
-            __builtin_ia32_pause();
-        }
-        std::atomic_thread_fence(std::memory_order_acquire);
-        return RPYW_OK;
+        if (int r = wait_published(h_ab + 2 * k, 2, st)) return r;
+        return k == 0 ? wait_published(h_b0, 2, st) : RPYW_OK;
     };
     for (; k < max_iter; ++k) {
         if (logging) {

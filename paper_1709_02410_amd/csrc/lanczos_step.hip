@@ -22,9 +22,8 @@
 // Gram-Schmidt passes of the full reorthogonalisation; beta_k =
 // (|y'|^2 - |c2|^2)^{1/2} as in the unfused driver.  vin of step k + 1 is
 // launched with step k: its first workgroup publishes step k (alpha_k, kept
-// in device memory by gs2, and beta_k into pinned memory, then, after a
-// system-scope fence, the step's flag), so that the host sees both
-// coefficients of a step when its flag is set.
+// in device memory by gs2, and beta_k) into pinned memory, where the host
+// polls them.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -53,7 +52,7 @@ __global__ __launch_bounds__(kVinThreads) void lz_vin_kernel(int diag, const int
                                                              const double* __restrict__ src,
                                                              const double* __restrict__ part2, int ncol2,
                                                              double* __restrict__ V, double* __restrict__ d_ab,
-                                                             double* __restrict__ h_ab, double* __restrict__ h_flag,
+                                                             double* __restrict__ h_ab,
                                                              R* __restrict__ rec, int recw,
                                                              const double* __restrict__ B,
                                                              double* __restrict__ h_hdr,
@@ -118,22 +117,12 @@ __global__ __launch_bounds__(kVinThreads) void lz_vin_kernel(int diag, const int
             const double beta = s2 > 0.0 ? sqrt(s2) : 0.0;
             sinv = 1.0 / beta;  // beta = 0: breakdown, this step's values are discarded
             if (p == 0 && k > 0) {
-                // publish step k - 1: alpha (kept by its gs2) and beta, then,
-                // after a system-scope fence, its flag
+                // publish step k - 1: alpha (kept by its gs2) and beta
                 d_ab[2 * (k - 1) + 1] = beta;
-                h_ab[2 * (k - 1)] = d_ab[2 * (k - 1)];
-                h_ab[2 * (k - 1) + 1] = beta;
-                __threadfence_system();
-                h_flag[k - 1] = 1.0;
+                publish(h_ab + 2 * (k - 1), d_ab[2 * (k - 1)]);
+                publish(h_ab + 2 * (k - 1) + 1, beta);
             } else if (p == 0) {
-                // the call's header: beta_0 = |W| and the definiteness flags
-                // of the factors; the host reads it with step 0, whose flag a
-                // later kernel sets
-                h_hdr[0] = beta;
-                int* hb = reinterpret_cast<int*>(h_hdr + 1);
-                hb[0] = bad0[0];
-                hb[1] = bad1 ? bad1[0] : 0;
-                __threadfence_system();
+                publish_header(h_hdr, beta, bad0, bad1);  // beta_0 = |W|
             }
         }
     }
@@ -548,15 +537,15 @@ void lanczos_units(int64_t N, const int64_t* body_offsets, int n_bodies, std::ve
 
 int lz_launch_vin(int prec, const BodyFactors& pc, const int* units, int nunits, int64_t n3, int k,
                   const double* src, const double* part2, int ncol2, double* V, double* d_ab, double* h_ab,
-                  double* h_flag, void* rec, int recw, const double* B, double* h_hdr, const int* bad0,
+                  void* rec, int recw, const double* B, double* h_hdr, const int* bad0,
                   const int* bad1, hipStream_t st) {
     if (prec == RPYW_FP32C)
         hipLaunchKernelGGL(lz_vin_kernel<float>, dim3((unsigned)nunits), dim3(kVinThreads), 0, st, pc.diag ? 1 : 0,
-                           units, pc.lofs, pc.L, n3, k, src, part2, ncol2, V, d_ab, h_ab, h_flag, (float*)rec, recw,
+                           units, pc.lofs, pc.L, n3, k, src, part2, ncol2, V, d_ab, h_ab, (float*)rec, recw,
                            B, h_hdr, bad0, bad1);
     else
         hipLaunchKernelGGL(lz_vin_kernel<double>, dim3((unsigned)nunits), dim3(kVinThreads), 0, st, pc.diag ? 1 : 0,
-                           units, pc.lofs, pc.L, n3, k, src, part2, ncol2, V, d_ab, h_ab, h_flag, (double*)rec, recw,
+                           units, pc.lofs, pc.L, n3, k, src, part2, ncol2, V, d_ab, h_ab, (double*)rec, recw,
                            B, h_hdr, bad0, bad1);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;

@@ -24,7 +24,6 @@
 #include <algorithm>
 #include <mutex>
 #include <cstring>
-#include <atomic>
 #include <cmath>
 #include <vector>
 
@@ -369,7 +368,7 @@ namespace {
 // the same recurrence, preconditioner and host-side Givens rotations as the
 // driver below, with the product's records written by the preconditioner
 // kernel, the product gathered by the operator kernel, and the Hessenberg
-// column of step k published by its last kernel (a flag in pinned memory
+// column of step k published by its last kernel (polled pinned memory
 // instead of an event between steps).
 int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets, int n_bodies, const double* slip,
                 const double* FT, double* lam_out, double* U_out, int64_t N, double a, double eta, double tol,
@@ -430,8 +429,8 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
         !rec || !B || !tpart || !spart || (krylov_presum(sp) && !ypre))
         return RPYW_ENOMEM;
     std::lock_guard<std::mutex> lk(g_h.mu);
-    const int slot = 2 * (max_iter + 2);  // c1[0..k], c2[0..k], h_{k+1,k}
-    const size_t hdr_bytes = align_up(((size_t)PinnedSlots::kSlots * slot + 2 + (max_iter + 2)) * sizeof(double));
+    const int slot = max_iter + 2;  // h_{0..k,k}, h_{k+1,k}
+    const size_t hdr_bytes = align_up(((size_t)PinnedSlots::kSlots * slot + 2) * sizeof(double));
     int rc = g_h.reserve(hdr_bytes + tbytes);
     if (rc) return rc;
     SlotRelease slots_done{g_h, st};
@@ -441,9 +440,7 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
     double* h_b = h_slot + (size_t)PinnedSlots::kSlots * slot;
     int* h_bad = (int*)(h_b + 1);
     double* dh_hdr = g_h.dp + (h_b - h_slot);
-    double* h_flag = h_b + 2;
-    double* dh_flag = g_h.dp + (h_flag - h_slot);
-    std::memset(h_flag, 0, (size_t)(max_iter + 2) * sizeof(double));
+    pending_fill(h_slot, (size_t)PinnedSlots::kSlots * slot + 2);
     if (tbytes) std::memcpy((char*)h_slot + hdr_bytes, tb.host.data(), tbytes);
     const int* dh_tab = (const int*)((const char*)g_h.dp + hdr_bytes);
 
@@ -464,7 +461,7 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
     // then pre of step k + 1, which publishes the column of step k.
     auto pre_k = [&](int k) {
         return rg_launch_pre(prec, pc, Wall, Nall, n_bodies, n3, n, k ? yb : bv, k ? part2 : sqp,
-                             k ? (int)nblk4 : (int)nrhs, gc1, g_h.dp, slot, dh_flag, k, V, zb, zb + n3, rec, rw, B,
+                             k ? (int)nblk4 : (int)nrhs, gc1, g_h.dp, slot, k, V, zb, zb + n3, rec, rw, B,
                              dh_hdr, notspd, pre ? pre->flag : nullptr, st);
     };
     auto launch_step = [&](int k) -> int {
@@ -485,26 +482,6 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
             if (int r = launch_step(queued)) return r;
         return RPYW_OK;
     };
-    // Waits for step k: its flag, polled; the stream is queried now and then
-    // so that a stream that drains without setting it ends the wait.
-    auto wait_step = [&](int k) -> int {
-        const volatile double* f = h_flag + k;
-        for (unsigned spin = 1;; ++spin) {
-            if (*f != 0.0) break;
-            if ((spin & 4095) == 0) {
-                const hipError_t qs = hipStreamQuery(st);
-                if (qs == hipSuccess) {
-                    if (*f != 0.0) break;
-                    return RPYW_EHIP;
-                }
-                if (qs != hipErrorNotReady) return RPYW_EHIP;
-            }
-            __builtin_ia32_pause();
-        }
-        std::atomic_thread_fence(std::memory_order_acquire);
-        return RPYW_OK;
-    };
-
     std::vector<std::vector<double>> R;
     std::vector<double> cs, sn, g;
     bool converged = false;
@@ -513,8 +490,11 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
     if ((rc = pre_k(0))) return rc;
     if ((rc = fill(1 + depth))) return rc;
     for (; k < max_iter; ++k) {
-        if ((rc = wait_step(k))) return rc;
+        // column k (step 0 also brings the header)
+        double* hs = h_slot + (size_t)(k % PinnedSlots::kSlots) * slot;
+        if ((rc = wait_published(hs, (size_t)k + 2, st))) return rc;
         if (k == 0) {
+            if ((rc = wait_published(h_b, 2, st))) return rc;
             beta = *h_b;
             const bool bad = h_bad[0] || h_bad[1];
             if (bad || !std::isfinite(beta) || beta == 0.0) {
@@ -527,10 +507,9 @@ int rigid_fused(const double* pos, const double* q, const int64_t* body_offsets,
             }
             g.assign(1, beta);
         }
-        const double* hs = h_slot + (size_t)(k % PinnedSlots::kSlots) * slot;
-        std::vector<double> h(k + 2);
-        for (int j = 0; j <= k; ++j) h[j] = hs[j] + hs[k + 1 + j];
-        h[k + 1] = hs[2 * (k + 1)];
+        std::vector<double> h(hs, hs + k + 2);
+        // for column k + kSlots, whose step is not queued yet
+        pending_fill(hs, std::min((size_t)slot, (size_t)(k + PinnedSlots::kSlots) + 2));
         if (depth && (rc = fill(speculate_to(k, depth, res1, res2, tol) + 1))) return rc;
         double hk1;
         if (!givens_column(h, k, R, cs, sn, g, beta, &res, &hk1)) return RPYW_EHIP;

@@ -19,8 +19,8 @@
 //   gs2   the Lanczos gs2 kernel: c1 = V^T w (kept for the next pre),
 //         y' = w - V c1, and the block partials of V^T y' and |y'|^2.
 // The pre kernel of step k + 1 is launched with step k: its first
-// workgroup publishes the Hessenberg column of step k ([c1, c2, h] into a
-// pinned slot, then, after a system-scope fence, the step's flag).
+// workgroup publishes the Hessenberg column of step k (c1 + c2, then h)
+// into a pinned slot, where the host polls it.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
     const double* __restrict__ Lall, const int* __restrict__ bofs, const int64_t* __restrict__ lofs,
     const double* __restrict__ Wall, const double* __restrict__ Nall, int64_t n3, int64_t ld,
     const double* __restrict__ src, const double* __restrict__ part2, int ncol2, const double* __restrict__ gc1,
-    double* __restrict__ hslots, int slot, double* __restrict__ h_flag, int k, double* __restrict__ V,
+    double* __restrict__ hslots, int slot, int k, double* __restrict__ V,
     double* __restrict__ zl, double* __restrict__ zu, R* __restrict__ rec, int recw, const double* __restrict__ B,
     double* __restrict__ h_hdr, const int* __restrict__ bad0, const int* __restrict__ bad1) {
     constexpr int PW = pos_slots<R>();
@@ -90,31 +90,15 @@ __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
         for (int j = 0; j < k; ++j) s2 -= cs[j] * cs[j];
         const double h = s2 > 0.0 ? sqrt(s2) : 0.0;
         sc = h;  // h = 0: breakdown, this step's values are discarded
-        if (p == 0 && k > 0) {
-            hslots[(size_t)((k - 1) % PinnedSlots::kSlots) * slot + 2 * k] = h;
-        } else if (p == 0) {
-            // the call's header: |b| and the definiteness flags of the
-            // factors; the host reads it with step 0, whose flag a later
-            // kernel sets
-            h_hdr[0] = h;
-            int* hb = reinterpret_cast<int*>(h_hdr + 1);
-            hb[0] = bad0[0];
-            hb[1] = bad1 ? bad1[0] : 0;
-            __threadfence_system();
-        }
+        if (p == 0 && k > 0)
+            publish(hslots + (size_t)((k - 1) % PinnedSlots::kSlots) * slot + k, h);
+        else if (p == 0)
+            publish_header(h_hdr, h, bad0, bad1);  // |b|
     }
-    if (k > 0) {
-        if (p == 0) {
-            // publish column k - 1: c1 (kept by its gs2), c2, h; then its flag
-            double* hc = hslots + (size_t)((k - 1) % PinnedSlots::kSlots) * slot;
-            for (int j = t; j < k; j += kPreThreads) {
-                hc[j] = gc1[j];
-                hc[k + j] = cs[j];
-            }
-            __threadfence_system();
-            __syncthreads();
-            if (t == 0) h_flag[k - 1] = 1.0;
-        }
+    if (k > 0 && p == 0) {
+        // publish column k - 1: c1 (kept by its gs2) + c2
+        double* hc = hslots + (size_t)((k - 1) % PinnedSlots::kSlots) * slot;
+        for (int j = t; j < k; j += kPreThreads) publish(hc + j, gc1[j] + cs[j]);
     }
     if (lds_factor) sl.store(Ls, n * n);
     sw.store(Ws, 6 * n);
@@ -408,15 +392,15 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
 
 int rg_launch_pre(int prec, const BodyFactors& pc, const double* Wall, const double* Nall, int n_bodies, int64_t n3,
                   int64_t ld, const double* src, const double* part2, int ncol2, const double* gc1, double* hslots,
-                  int slot, double* h_flag, int k, double* V, double* zl, double* zu, void* rec, int recw,
+                  int slot, int k, double* V, double* zl, double* zu, void* rec, int recw,
                   const double* B, double* h_hdr, const int* bad0, const int* bad1, hipStream_t st) {
     if (prec == RPYW_FP32C)
         hipLaunchKernelGGL(rg_pre_kernel<float>, dim3((unsigned)n_bodies), dim3(kPreThreads), 0, st, pc.L, pc.bofs,
-                           pc.lofs, Wall, Nall, n3, ld, src, part2, ncol2, gc1, hslots, slot, h_flag, k, V, zl, zu,
+                           pc.lofs, Wall, Nall, n3, ld, src, part2, ncol2, gc1, hslots, slot, k, V, zl, zu,
                            (float*)rec, recw, B, h_hdr, bad0, bad1);
     else
         hipLaunchKernelGGL(rg_pre_kernel<double>, dim3((unsigned)n_bodies), dim3(kPreThreads), 0, st, pc.L, pc.bofs,
-                           pc.lofs, Wall, Nall, n3, ld, src, part2, ncol2, gc1, hslots, slot, h_flag, k, V, zl, zu,
+                           pc.lofs, Wall, Nall, n3, ld, src, part2, ncol2, gc1, hslots, slot, k, V, zl, zu,
                            (double*)rec, recw, B, h_hdr, bad0, bad1);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;

@@ -213,12 +213,13 @@ int64_t lanczos_gs2_blocks(int64_t n3, int* m);
 void lanczos_units(int64_t N, const int64_t* body_offsets, int n_bodies, std::vector<int>& units,
                    std::vector<int>& groups);
 // vin of step k; at k = 0, part2 holds the packing kernel's partials of
-// |W|^2 and vin writes the header (beta_0, then the two definiteness flags
-// *bad0 and *bad1 (0 when null) as ints) to the pinned h_hdr.
+// |W|^2 and vin publishes the header (beta_0, then the two definiteness flags
+// *bad0 and *bad1 (0 when null) as ints) to the pinned h_hdr[0..2); later
+// steps publish alpha_{k-1} and beta_{k-1} to h_ab[2 (k - 1) ..].
 int lz_launch_vin(int prec, const BodyFactors& pc, const int* units, int nunits, int64_t n3, int k,
                   const double* src, const double* part2, int ncol2, double* V, double* d_ab, double* h_ab,
-                  double* h_flag, void* rec, int recw, const double* B, double* h_hdr, const int* bad0,
-                  const int* bad1, hipStream_t st);
+                  void* rec, int recw, const double* B, double* h_hdr, const int* bad0, const int* bad1,
+                  hipStream_t st);
 // Records, B and the |W|^2 partials (lz_pack_blocks of them) for npad
 // blobs; clears *bad.
 // Also copies the call's tables (nwords ints) from pinned host memory htab
@@ -244,14 +245,14 @@ int lz_launch_gs2(const double* w, double* yo, int64_t n3, const double* V, int 
 
 // Fused GMRES steps of the rigid solve (rigid_step.hip), with the Lanczos
 // gs2 kernel (gc1: where its block 0 keeps c1 for the next pre).
-// pre publishes column k - 1 of the Hessenberg matrix into the pinned
-// slot hslots + ((k - 1) mod PinnedSlots::kSlots) slot and sets h_flag[k - 1].
+// pre publishes column k - 1 of the Hessenberg matrix (k + 1 values) into the
+// pinned slot hslots + ((k - 1) mod PinnedSlots::kSlots) slot.
 // At k = 0, part2 holds the right-hand side kernel's partials of |b|^2 and
-// pre writes the header (|b|, then the flags *bad0 and *bad1 (0 when null)
-// as ints) to the pinned h_hdr.
+// pre publishes the header (|b|, then the flags *bad0 and *bad1 (0 when null)
+// as ints) to the pinned h_hdr[0..2).
 int rg_launch_pre(int prec, const BodyFactors& pc, const double* Wall, const double* Nall, int n_bodies, int64_t n3,
                   int64_t ld, const double* src, const double* part2, int ncol2, const double* gc1, double* hslots,
-                  int slot, double* h_flag, int k, double* V, double* zl, double* zu, void* rec, int recw,
+                  int slot, int k, double* V, double* zl, double* zu, void* rec, int recw,
                   const double* B, double* h_hdr, const int* bad0, const int* bad1, hipStream_t st);
 // b = [-slip | -F, -T] (n3 + n6 entries), the partials of |b|^2
 // (rg_rhs_blocks of them), the records' positions (zero force slots) and B
@@ -366,6 +367,22 @@ inline int speculate_to(int k, int depth, double m1, double m2, double tol) {
         need = std::max(1, (int)std::ceil(std::log(tol / m1) / std::log(m1 / m2)));
     return std::max(k, std::min(k + depth, k - 1 + need));
 }
+
+// Values that kernels hand to the polling host through pinned memory
+// (kstep::publish).  A flag stored after them does not say that they have
+// arrived: writes to host memory may be seen out of order there, also with a
+// system-scope fence between them (about one step in 1e5 was read with some of
+// its values from an earlier call).  So each value stands for itself: the host
+// fills its places with kPending first and takes a value once it is something
+// else.  kPending is a signalling NaN, which no arithmetic gives.
+constexpr uint64_t kPending = 0x7ff4b10bb10bb10bull;
+inline void pending_fill(double* p, size_t n) {
+    for (size_t i = 0; i < n; ++i) std::memcpy(p + i, &kPending, sizeof(double));
+}
+// Waits until the kernels queued on st have published p[0..n).  The stream is
+// queried now and then, so that one that drains without publishing them (a
+// failed launch) ends the wait with an error.
+int wait_published(const double* p, size_t n, hipStream_t st);
 
 // Library-owned pinned host buffer plus two events for per-iteration
 // device->host copies of a solver; the caller holds mu while using it.

@@ -95,3 +95,23 @@ def test_two_targets_per_lane(rp, orc, N, k, ipw):
     assert torch.equal(U, again)
     for j in range(k):
         check(U[j].cpu().numpy(), orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"two targets N={N} k={k} rhs {j}")
+
+
+def test_repeated_solves_are_bitwise_equal(rp):
+    """Roots and rigid solves repeat bit for bit when calls of different sizes
+    alternate: no coefficient that the host reads may be one that an earlier
+    call left in its pinned memory."""
+    from paper_1709_02410_amd import workloads as wl
+    cfg, runs = wl.config1(seed=0), []
+    for bodies in (40, 60):
+        offs = cfg.body_offsets[:bodies + 1]
+        pos = cfg.pos[:offs[-1]]
+        runs.append((_t(pos), _t(pos[offs[:-1]]), offs, _t(wl.gaussian(pos.shape, bodies))))
+    first = [None, None]
+    for _ in range(100):
+        for i, (pos, q, offs, w) in enumerate(runs):
+            root, it, _, _ = rp.lanczos_sqrt(pos, w, body_offsets=offs, tol=1e-9)
+            _, U, its, _, _ = rp.rigid_solve(pos, q, offs, w, None, tol=1e-9)
+            first[i] = first[i] or (root, U, it, its)
+            assert (it, its) == first[i][2:]
+            assert torch.equal(root, first[i][0]) and torch.equal(U, first[i][1])
