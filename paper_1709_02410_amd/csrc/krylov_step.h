@@ -8,11 +8,22 @@
 #include <cstdint>
 
 #include "sym_pairs.h"
+#include "wave_sums.h"
 
 namespace rpyw {
 namespace kstep {
 
 constexpr int kPre = 16;  // values loaded ahead of use per thread
+
+// A value that is the same in the wave's lanes, kept in a scalar register: the
+// row addresses formed from it need no vector registers.
+__device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// p[i] with the offset in one 32-bit register and p in scalar ones (i below
+// 2^29; a 64-bit address per load costs two registers each).
+__device__ __forceinline__ double at32(const double* p, unsigned i) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(p) + i * 8u);
+}
 
 // A value for the polling host, straight to its pinned memory (wait_published;
 // no order between values is assumed, so no fence goes with it).
@@ -65,6 +76,57 @@ __device__ void reduce_rows(const double* __restrict__ partial, int nrows, int n
     }
     __syncthreads();
 }
+
+// reduce_rows in two halves, with as many lanes per row as the rows leave: load
+// issues the loads when one batch per lane covers the sums, to go out before
+// the loads that the sums do not need; finish adds them up (or takes several
+// batches) and ends with a barrier.  nrows ncol below 2^29.
+template <int T, int PRE = kPre>
+struct RowSums {
+    int lpr, row, lane;
+    bool one;
+    double v[PRE];
+    __device__ __forceinline__ void batch(const double* __restrict__ partial, unsigned r0, int c, int ncol) {
+        // every load in bounds (the last column for the tail, which is not added)
+#pragma unroll
+        for (int i = 0; i < PRE; ++i)
+            v[i] = at32(partial, r0 + (c + lpr * i < ncol ? c + lpr * i : ncol - 1));
+    }
+    __device__ __forceinline__ double sum(int c, int ncol) const {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i)
+            if (c + lpr * i < ncol) s += v[i];
+        return s;
+    }
+    __device__ __forceinline__ void load(const double* __restrict__ partial, int nrows, int ncol) {
+        lpr = nrows <= T / 64 ? 64 : nrows <= T / 16 ? 16 : nrows <= T / 8 ? 8 : 4;
+        row = threadIdx.x / lpr;
+        lane = threadIdx.x % lpr;
+        one = nrows <= T / lpr && ncol <= lpr * PRE;
+        if (one && row < nrows) batch(partial, row * ncol, lane, ncol);
+    }
+    __device__ __forceinline__ void put(double s, int r, int nrows, double* out) const {
+        for (int o = lpr / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0 && r < nrows) out[r] = s;
+    }
+    __device__ __forceinline__ void finish(const double* __restrict__ partial, int nrows, int ncol, double* out) {
+        if (one) {
+            put(row < nrows ? sum(lane, ncol) : 0.0, row, nrows, out);
+        } else {
+            for (int r = row; r - row < nrows; r += T / lpr) {
+                double s = 0.0;
+                if (r < nrows)
+                    for (int c = lane; c < ncol; c += lpr * PRE) {
+                        batch(partial, r * ncol, c, ncol);
+                        s += sum(c, ncol);
+                    }
+                put(s, r, nrows, out);
+            }
+        }
+        __syncthreads();
+    }
+};
 
 // Entry slots of a group of n entries (3 per blob, n <= 128) whose partial
 // sums a workgroup gathers: thread t takes slot t % S (S = 64, or 128 when

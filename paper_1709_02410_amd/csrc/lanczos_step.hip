@@ -42,9 +42,15 @@ using namespace kstep;
 constexpr int kVinThreads = 256;
 constexpr int kOutThreads = 512;
 constexpr int kGs2Threads = 256;
-constexpr int kVinReg = 64;  // basis values vin keeps in registers
+constexpr int kVinReg = 16;  // basis values a thread of vin keeps in registers
 constexpr int kPackThreads = 256;
 
+// vin and out are chains of dependent round trips (loads, the sums over them,
+// the factor) on one workgroup per body, and are bound by the length of the
+// chain: the loads go out first, with the partials that start the chain ahead
+// of the others; several threads share an entry's sums over the basis and the
+// rows of the factor; the norm is a wave's sum.  One thread per entry took 7.6
+// us (vin) and 8.9 us (out) a step on 256 boomerangs, now 5.9 and 6.9.
 template <typename R>
 __global__ __launch_bounds__(kVinThreads) void lz_vin_kernel(int diag, const int* __restrict__ units,
                                                              const int64_t* __restrict__ lofs,
@@ -62,100 +68,91 @@ __global__ __launch_bounds__(kVinThreads) void lz_vin_kernel(int diag, const int
     __shared__ double c[kLanczosFusedMaxIter + 2];
     __shared__ double x[3 * kMaxBodyBlobs];
     __shared__ double Li[kLdsFactor];
+    __shared__ double upd[kVinThreads];
     __shared__ double sinv;
     const int p = blockIdx.x, t = threadIdx.x;
-    // The partials of gs2 first (they depend on nothing this kernel loads;
-    // at k = 0 the packing kernel's partials of |W|^2): with up to 64 rows
-    // of up to 64 columns, one batch of loads per lane (4 lanes per row),
-    // added up after the other loads are issued.
-    constexpr int kRl = 4;
-    const bool one_batch = k + 1 <= kVinThreads / kRl && ncol2 <= kRl * kPre;
-    const int rr = t / kRl, rq = t % kRl;
-    double pv[kPre];
-    if (one_batch && rr <= k) {
-        const double* pr = part2 + (int64_t)rr * ncol2;
-#pragma unroll
-        for (int i = 0; i < kPre; ++i) pv[i] = pr[rq + kRl * i < ncol2 ? rq + kRl * i : ncol2 - 1];
-    }
+    // the partials of gs2 first (they depend on nothing this kernel loads; at
+    // k = 0 the packing kernel's partials of |W|^2)
+    RowSums<kVinThreads> rows;
+    rows.load(part2, k + 1, ncol2);
     const int64_t e0 = 3 * (int64_t)units[p];
     const int n = (int)(3 * (int64_t)units[p + 1] - e0);
     const bool lds_factor = !diag && n * n <= kLdsFactor;
-    // loads that do not depend on the reductions go next: this entry's
-    // source value, B of its blob, its basis values (the first kVinReg), and
-    // the inverse factor
+    // Units of up to 64 entries: four threads per entry (quarter t / 64), which
+    // take the vectors j = quarter (mod 4); larger ones (up to 126): two.
+    const int ways = n <= 64 ? 4 : 2, el = n <= 64 ? t & 63 : t & 127, qr = wave_uniform(n <= 64 ? t >> 6 : t >> 7);
+    // loads that do not depend on the reductions go next: the inverse factor,
+    // this entry's source value, B of its blob and its basis values
     Staged<kVinThreads, kLdsFactor / kVinThreads> sf;
     if (lds_factor) sf.load(Lall + 2 * lofs[p] + (int64_t)n * n, n * n);
-    const int64_t e = e0 + t, ec = t < n ? e : e0;  // ec: an in-bounds address for idle lanes
-    double vr = 0.0, bb = 0.0, a[kVinReg];
-    if (t < n) {
-        vr = src[e];
-        bb = B[e / 3];
-    }
+    const bool has = el < n;
+    const int64_t ec = e0 + (has ? el : 0);  // an in-bounds address for idle lanes
+    // entry of the record that this thread writes: four lanes apply the factor
+    // of each entry when the entries allow it
+    const bool spread = lds_factor && n <= 64;
+    const int ei = spread ? t >> 2 : t;
+    double vr = t < n ? src[e0 + t] : 0.0;
+    const double bb = ei < n ? B[(e0 + ei) / 3] : 0.0;
+    const double alpha = p == 0 && t == 0 && k > 0 ? d_ab[2 * (k - 1)] : 0.0;
+    double a[kVinReg];
 #pragma unroll
-    for (int j0 = 0; j0 < kVinReg; j0 += 16) {
-        if (j0 >= k) break;  // uniform
+    for (int i0 = 0; i0 < kVinReg; i0 += 4) {
+        if (ways * i0 >= k) break;  // uniform
 #pragma unroll
-        for (int j = j0; j < j0 + 16; ++j) a[j] = V[(j < k ? j : 0) * n3 + ec];
-    }
-    {
-        // c[0..k) = c2, c[k] = |y'|^2 (k = 0: |W|^2); one pass over up to 64
-        // rows
-        if (one_batch) {
-            double sr = 0.0;
-#pragma unroll
-            for (int i = 0; i < kPre; ++i)
-                if (rq + kRl * i < ncol2) sr += pv[i];
-            sr = lane_group_sum<kRl>(sr);
-            if (rq == 0 && rr <= k) c[rr] = sr;
-            __syncthreads();
-        } else {
-            reduce_rows<kVinThreads, 4, kPre>(part2, k + 1, ncol2, c);
+        for (int i = i0; i < i0 + 4; ++i) {
+            const int j = qr + ways * i;
+            a[i] = V[(j < k ? j : 0) * n3 + ec];
         }
+    }
+    rows.finish(part2, k + 1, ncol2, c);  // c[0..k) = c2, c[k] = |y'|^2 (k = 0: |W|^2)
+    // the second correction, and by the first wave the norm
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kVinReg; ++i)
+        if (qr + ways * i < k) s = fma(c[qr + ways * i], a[i], s);
+    for (int j = qr + ways * kVinReg; j < k; j += ways) s = fma(c[j], V[j * n3 + ec], s);
+    upd[t] = s;
+    if (t < 64) {
+        double q = 0.0;
+        for (int j = t; j < k; j += 64) q = fma(c[j], c[j], q);
+        const double s2 = c[k] - lane_group_sum<64>(q);
+        const double b = s2 > 0.0 ? sqrt(s2) : 0.0;
         if (t == 0) {
-            double s2 = c[k];
-            for (int j = 0; j < k; ++j) s2 -= c[j] * c[j];
-            const double beta = s2 > 0.0 ? sqrt(s2) : 0.0;
-            sinv = 1.0 / beta;  // beta = 0: breakdown, this step's values are discarded
+            sinv = 1.0 / b;  // b = 0: breakdown, this step's values are discarded
             if (p == 0 && k > 0) {
                 // publish step k - 1: alpha (kept by its gs2) and beta
-                d_ab[2 * (k - 1) + 1] = beta;
-                publish(h_ab + 2 * (k - 1), d_ab[2 * (k - 1)]);
-                publish(h_ab + 2 * (k - 1) + 1, beta);
+                d_ab[2 * (k - 1) + 1] = b;
+                publish(h_ab + 2 * (k - 1), alpha);
+                publish(h_ab + 2 * (k - 1) + 1, b);
             } else if (p == 0) {
-                publish_header(h_hdr, beta, bad0, bad1);  // beta_0 = |W|
+                publish_header(h_hdr, b, bad0, bad1);  // beta_0 = |W|
             }
         }
     }
     if (lds_factor) sf.store(Li, n * n);  // read after the next barrier
     __syncthreads();
     if (t < n) {
-#pragma unroll
-        for (int j = 0; j < kVinReg; ++j)
-            if (j < k) vr -= c[j] * a[j];  // a[j] is V_j only for j < k
-        for (int j0 = kVinReg; j0 < k; j0 += kPre) {
-            double b[kPre];
-#pragma unroll
-            for (int j = 0; j < kPre; ++j) b[j] = j0 + j < k ? V[(j0 + j) * n3 + e] : 0.0;
-#pragma unroll
-            for (int j = 0; j < kPre; ++j)
-                if (j0 + j < k) vr -= c[j0 + j] * b[j];
-        }
-        const double v = vr * sinv;
-        V[k * n3 + e] = v;
+        const double v = (vr - (ways == 4 ? (upd[t] + upd[t + 64]) + (upd[t + 128] + upd[t + 192])
+                                          : upd[t] + upd[t + 128])) *
+                         sinv;
+        V[k * n3 + e0 + t] = v;
         x[t] = v;
     }
     __syncthreads();
-    if (t < n) {
-        double s;
-        if (diag) {
-            s = x[t] / Lall[e];
+    // x <- (L_p^-1)^T x, row e: column e of L_p^-1 from its diagonal down
+    if (ei < n) {
+        double z;
+        if (spread) {
+            z = 0.0;
+            for (int m = ei + (t & 3); m < n; m += 4) z = fma(Li[m * n + ei], x[m], z);
+            z = lane_group_sum<4>(z);
         } else {
-            // (L_p^-1)^T row t: column t of L_p^-1 from its diagonal down
-            s = lds_factor ? dot4(Li + t * n + t, n, x + t, n - t)
-                           : dot4(Lall + 2 * lofs[p] + (int64_t)n * n + t * n + t, n, x + t, n - t);
+            z = diag         ? x[t] / Lall[e0 + t]
+                : lds_factor ? dot4(Li + t * n + t, n, x + t, n - t)
+                             : dot4(Lall + 2 * lofs[p] + (int64_t)n * n + t * n + t, n, x + t, n - t);
         }
-        const int64_t blob = e / 3;
-        rec[blob * recw + PW + (int)(e - 3 * blob)] = (R)(bb * s);
+        const int64_t blob = (e0 + ei) / 3;
+        if (!spread || (t & 3) == 0) rec[blob * recw + PW + (int)(e0 + ei - 3 * blob)] = (R)(bb * z);
     }
 }
 
@@ -185,16 +182,21 @@ __global__ __launch_bounds__(kOutThreads) void lz_out_kernel(
     const int uv = t <= nu ? units[g0 + t] : 0;
     Staged<kOutThreads, 2 * kLdsFactor / kOutThreads> sf;
     if (lds_factor) sf.load(Lall + 2 * gi.loff, 2 * gi.sq);
+    // the factor of a group of up to 64 entries is applied by eight lanes per
+    // entry (entry t / 8), otherwise by thread t for entry t
+    const bool spread = lds_factor && n <= 64;
+    const int et = spread ? t >> 3 : t;
+    const bool has = et < n && (!spread || (t & 7) == 0);
     double vprev = 0.0, bb = 0.0, dg = 0.0;
+    if (has && k > 0) vprev = V[(k - 1) * n3 + e0 + et];
     if (t < n) {
-        if (k > 0) vprev = V[(k - 1) * n3 + e0 + t];
         bb = B[(e0 + t) / 3];
         if (diag) dg = Lall[e0 + t];
     }
     const double bk = k > 0 ? d_ab[2 * (k - 1) + 1] : 0.0;
     // the lane's basis values for the dot products (waves take the vectors
     // j = wave (mod 8), lanes the entries l and l + 64), loaded ahead
-    const int wv = t >> 6, l = t & 63;
+    const int wv = wave_uniform(t >> 6), l = t & 63;
     constexpr int kWaves = kOutThreads / 64;
     double av[kWaves][2];
 #pragma unroll
@@ -231,8 +233,7 @@ __global__ __launch_bounds__(kOutThreads) void lz_out_kernel(
         y[t] = mu0 * bb * s;
     }
     __syncthreads();
-    if (t < n) {
-        const int64_t e = e0 + t;
+    if (et < n) {
         double v;
         if (diag) {
             v = y[t] / dg;
@@ -240,37 +241,38 @@ __global__ __launch_bounds__(kOutThreads) void lz_out_kernel(
             // the entry's body (unit offsets in LDS) and where its factors
             // start relative to the group's
             int q = 0, off = 0;
-            while (3 * (ub[q + 1] - ub[0]) <= t) {
+            while (3 * (ub[q + 1] - ub[0]) <= et) {
                 const int nq = 3 * (ub[q + 1] - ub[q]);
                 off += 2 * nq * nq;
                 ++q;
             }
             const int bs = 3 * (ub[q] - ub[0]), bn = 3 * (ub[q + 1] - ub[q]);
-            const int i = t - bs;
+            const int i = et - bs;
             const int64_t fi = off + (int64_t)bn * bn + (int64_t)i * bn;  // row i of L_p^-1
-            v = lds_factor ? dot4(Lf + fi, 1, y + bs, i + 1) : dot4(Lall + 2 * gi.loff + fi, 1, y + bs, i + 1);
+            if (spread) {
+                v = 0.0;
+                for (int m = t & 7; m <= i; m += 8) v = fma(Lf[fi + m], y[bs + m], v);
+                v = lane_group_sum<8>(v);
+            } else {
+                v = lds_factor ? dot4(Lf + fi, 1, y + bs, i + 1) : dot4(Lall + 2 * gi.loff + fi, 1, y + bs, i + 1);
+            }
         }
-        if (k > 0) v -= bk * vprev;
-        w[e] = v;
-        wl[t] = v;
+        if (has) {
+            if (k > 0) v -= bk * vprev;
+            w[e0 + et] = v;
+            wl[et] = v;
+        }
     }
     __syncthreads();
     const double w0 = l < n ? wl[l] : 0.0, w1 = l + 64 < n ? wl[l + 64] : 0.0;
     {
-        // the wave's kWaves dot products reduced together, one butterfly
-        // level at a time (independent shuffles overlap)
+        // the wave's kWaves dot products folded together
         double pr[kWaves];
 #pragma unroll
         for (int i = 0; i < kWaves; ++i) pr[i] = fma(av[i][1], w1, fma(av[i][0], w0, 0.0));
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-            for (int i = 0; i < kWaves; ++i) pr[i] += __shfl_xor(pr[i], o, 64);
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
-            const int j = wv + kWaves * i;
-            if (l == 0 && j <= k) part1[(int64_t)j * ngroups + g] = pr[i];
-        }
+        wave_fold<kWaves, 32>(pr);
+        const int j = wv + kWaves * wave_value<kWaves>(l);
+        if (l % (64 / kWaves) == 0 && j <= k) part1[(int64_t)j * ngroups + g] = pr[0];
     }
     for (int j = wv + kWaves * kWaves; j <= k; j += kWaves) {
         const double* Vj = V + j * n3 + e0;
@@ -281,12 +283,19 @@ __global__ __launch_bounds__(kOutThreads) void lz_out_kernel(
     }
 }
 
-// gs2: c1 from the partials of out; y' = w - sum_{j <= k} c1[j] V_j (terms
-// subtracted in order); block partials of V_j . y' (j <= k) and |y'|^2.
-// Block b takes kGs2Threads m consecutive entries, m per thread.  With one entry per
-// thread and k < kGs2Reg, the entry's basis values are loaded once, before
-// the reduction of c1, and serve both the update and the dot products.
-constexpr int kGs2Reg = 64;
+// gs2: c1 from the partials of out; y' = w - sum_{j <= k} c1[j] V_j, and block
+// partials of V_j . y' (j <= k) and |y'|^2.  Block b takes kGs2Threads m
+// consecutive entries.
+//
+// With m = 1 and k < 128 (lz_gs2_wide_kernel) a block has four threads per
+// entry, which take the vectors j = quarter (mod 4) and keep their KR values
+// in registers for the update and the dot products, so that the basis is read
+// once.  The kernel is a chain of dependent round trips on few blocks (45 at
+// 11520 entries): all loads go out first, the partials of out in one batch,
+// and a wave's dot products are folded together (wave_fold).  With one thread
+// per entry it took 10.5 us a step of the Lanczos iteration on 256 boomerangs,
+// now 8.0 (k < 64) and 12.4 (k = 64 .. 127, where it had read the basis twice).
+constexpr int kGs2WideThreads = 4 * kGs2Threads;
 // Block 0 keeps the step's first projection for the next step's first
 // kernel, which publishes the step: alpha_k = c1[k] into d_ab (Lanczos), or
 // all of c1 into gc1 (GMRES).
@@ -300,6 +309,70 @@ __device__ __forceinline__ void keep_c1(int k, const double* c1, double* __restr
     }
 }
 
+template <int KR>
+__global__ __launch_bounds__(kGs2WideThreads) void lz_gs2_wide_kernel(
+    const double* __restrict__ w, double* __restrict__ yo, int64_t n3, const double* __restrict__ V, int k,
+    const double* __restrict__ part1, int ngroups, double* __restrict__ part2, double* __restrict__ d_ab,
+    double* __restrict__ gc1) {
+    constexpr int kWaves = kGs2Threads / 64;  // waves of one quarter
+    __shared__ double c1[4 * KR];
+    __shared__ double upd[4][kGs2Threads];
+    __shared__ double red[kWaves][4 * KR + 1];
+    const int t = threadIdx.x, el = t % kGs2Threads, qr = wave_uniform(t / kGs2Threads);
+    const int64_t base = (int64_t)blockIdx.x * kGs2Threads + el;
+    const bool has = base < n3;
+    const unsigned bc = has ? base : 0;  // an in-bounds address for idle lanes
+    // the partials of out first: the chain starts there
+    RowSums<kGs2WideThreads, 8> rows;  // (16 spill)
+    rows.load(part1, k + 1, ngroups);
+    const double wv = w[bc];
+    double a[KR];
+#pragma unroll
+    for (int i0 = 0; i0 < KR; i0 += 4) {
+        if (4 * i0 > k) break;  // uniform
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) {
+            const int j = qr + 4 * i;
+            a[i] = at32(V + (j <= k ? j : 0) * n3, bc);
+        }
+    }
+    rows.finish(part1, k + 1, ngroups, c1);
+    keep_c1(k, c1, d_ab, gc1);
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < KR; ++i)
+        if (qr + 4 * i <= k) s = fma(c1[qr + 4 * i], a[i], s);
+    upd[qr][el] = s;
+    __syncthreads();
+    const double v = has ? wv - ((upd[0][el] + upd[1][el]) + (upd[2][el] + upd[3][el])) : 0.0;
+    if (has && qr == 0) yo[base] = v;
+    // the wave's share of the dot products of its quarter's vectors, 16 at a
+    // time, and of |y'|^2
+    const int wave = wave_uniform(el >> 6), lane = t & 63;
+#pragma unroll
+    for (int i0 = 0; i0 < KR; i0 += 16) {
+        if (4 * i0 > k) break;
+        double p[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) p[i] = qr + 4 * (i0 + i) <= k ? a[i0 + i] * v : 0.0;
+        wave_fold<16, 32>(p);
+        const int j = qr + 4 * (i0 + wave_value<16>(lane));
+        if (j <= k) red[wave][j] = p[0];  // lanes with one vector write the same sum
+    }
+    if (qr == 0) {
+        const double p = lane_group_sum<64>(v * v);
+        if (lane == 0) red[wave][k + 1] = p;
+    }
+    __syncthreads();
+    if (t < k + 2) {
+        double p = red[0][t];
+#pragma unroll
+        for (int u = 1; u < kWaves; ++u) p += red[u][t];
+        part2[(int64_t)t * gridDim.x + blockIdx.x] = p;
+    }
+}
+
+// The general case: several entries per thread or many basis vectors.
 __global__ __launch_bounds__(kGs2Threads) void lz_gs2_kernel(const double* __restrict__ w, double* __restrict__ yo,
                                                              int64_t n3, int m, const double* __restrict__ V, int k,
                                                              const double* __restrict__ part1, int ngroups,
@@ -315,54 +388,6 @@ __global__ __launch_bounds__(kGs2Threads) void lz_gs2_kernel(const double* __res
     // the tile's kBatch rows are added by kLpr lanes each
     constexpr int kLpr = kGs2Threads / kBatch;
     const int jr = t / kLpr, c0 = t % kLpr;
-    if (m == 1 && k < kGs2Reg) {
-        const bool has = base < n3;
-        double a[kGs2Reg];
-        double v = has ? w[base] : 0.0;
-        const int64_t bc = has ? base : 0;  // an in-bounds address for idle lanes
-#pragma unroll
-        for (int j0 = 0; j0 < kGs2Reg; j0 += 16) {
-            if (j0 > k) break;  // uniform
-#pragma unroll
-            for (int j = j0; j < j0 + 16; ++j) a[j] = V[(j <= k ? j : 0) * n3 + bc];
-        }
-        reduce_rows<kGs2Threads, 4, kPre>(part1, k + 1, ngroups, c1);  // one pass over up to 64 rows
-        keep_c1(k, c1, d_ab, gc1);
-#pragma unroll
-        for (int j = 0; j < kGs2Reg; ++j)
-            if (j <= k) v -= c1[j] * a[j];
-        v = has ? v : 0.0;  // idle lanes: a[] holds values of entry 0, and they add nothing to the dots
-        if (has) yo[base] = v;
-        // batches of 16 results with compile-time indices into a[] (the
-        // loops are fully unrolled; the last result is |y'|^2)
-#pragma unroll
-        for (int j0 = 0; j0 < kGs2Reg + kBatch; j0 += kBatch) {
-            if (j0 >= nd) break;
-            const int jn = nd - j0 < kBatch ? nd - j0 : kBatch;
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int j = j0 + u;
-                double p = 0.0;
-                if (u < jn) {
-                    if (j <= k) {
-                        p = a[j < kGs2Reg ? j : 0] * v;
-                    } else {
-                        p = v * v;
-                    }
-                }
-                tile[u][t] = p;
-            }
-            __syncthreads();
-            double s = 0.0;
-#pragma unroll
-            for (int i = 0; i < kGs2Threads / kLpr; ++i) s += tile[jr][c0 + kLpr * i];
-            s = lane_group_sum<kLpr>(s);
-            if (c0 == 0 && jr < jn) part2[(int64_t)(j0 + jr) * nblk + blockIdx.x] = s;
-            __syncthreads();
-        }
-        return;
-    }
-    // general path: several entries per thread or many basis vectors
     reduce_rows<kGs2Threads>(part1, k + 1, ngroups, c1);
     keep_c1(k, c1, d_ab, gc1);
     double x[kLanczosGs2PerThread];
@@ -598,8 +623,15 @@ int lz_launch_gs2(const double* w, double* yo, int64_t n3, const double* V, int 
                   double* part2, double* d_ab, double* gc1, hipStream_t st) {
     int m;
     const int64_t nb = lanczos_gs2_blocks(n3, &m);
-    hipLaunchKernelGGL(lz_gs2_kernel, dim3((unsigned)nb), dim3(kGs2Threads), 0, st, w, yo, n3, m, V, k, part1, ngroups,
-                       part2, d_ab, gc1);
+    if (m == 1 && k < 64)
+        hipLaunchKernelGGL(lz_gs2_wide_kernel<16>, dim3((unsigned)nb), dim3(kGs2WideThreads), 0, st, w, yo, n3, V, k,
+                           part1, ngroups, part2, d_ab, gc1);
+    else if (m == 1 && k < 128)
+        hipLaunchKernelGGL(lz_gs2_wide_kernel<32>, dim3((unsigned)nb), dim3(kGs2WideThreads), 0, st, w, yo, n3, V, k,
+                           part1, ngroups, part2, d_ab, gc1);
+    else
+        hipLaunchKernelGGL(lz_gs2_kernel, dim3((unsigned)nb), dim3(kGs2Threads), 0, st, w, yo, n3, m, V, k, part1,
+                           ngroups, part2, d_ab, gc1);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;
 }

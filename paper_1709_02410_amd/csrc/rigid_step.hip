@@ -38,9 +38,13 @@ using namespace kstep;
 constexpr int kPreThreads = 256;  // at least 3 kMaxBodyBlobs + 6 (one thread per entry)
 constexpr int kOutThreads = 256;
 constexpr int kMaxN3 = 3 * kMaxBodyBlobs;
-constexpr int kPreReg = 64;  // basis values pre keeps in registers
+constexpr int kPreReg = 16;  // basis values a thread of pre keeps in registers
 constexpr int kRhsThreads = 256;
 
+// pre, like the Lanczos vin, is bound by its chain of dependent round trips:
+// the partials' loads go out first, up to four threads share an entry's sums
+// over the basis and the rows of the factors.  One thread per entry took 17.0
+// us a step on 1024 bodies of 12 blobs (k <= 3), now 13.5.
 template <typename R>
 __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
     const double* __restrict__ Lall, const int* __restrict__ bofs, const int64_t* __restrict__ lofs,
@@ -54,76 +58,103 @@ __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
     __shared__ double r[kMaxN3 + 6], t1[kMaxN3], tt[kMaxN3];
     __shared__ double Ls[kLdsFactor];
     __shared__ double Ws[6 * kMaxN3];
+    __shared__ double upd[kPreThreads];
     __shared__ double s6[6], z6[6], sc;
     const int p = blockIdx.x, t = threadIdx.x;
+    // the partials of gs2 first: the chain starts there
+    RowSums<kPreThreads> rows;
+    rows.load(part2, k + 1, ncol2);
     const int b0 = bofs[p], n = 3 * (bofs[p + 1] - b0);
     const int64_t e0 = 3 * (int64_t)b0;
     const bool lds_factor = n * n <= kLdsFactor;
     const double* Li = Lall + 2 * lofs[p] + (int64_t)n * n;
     const double* W = Wall + 18 * (int64_t)b0;
-    // everything the step does not compute goes first: the factors, the
-    // input entry and its basis values, N_p, c2 and the scale
+    // everything the step does not compute goes next: the factors, the input
+    // entry and its basis values, N_p
     Staged<kPreThreads, kLdsFactor / kPreThreads> sl;
     if (lds_factor) sl.load(Li, n * n);
     Staged<kPreThreads, (6 * kMaxN3 + kPreThreads - 1) / kPreThreads> sw;
     sw.load(W, 6 * n);
-    // thread t < n: lambda entry t; n <= t < n + 6: U entry t - n
-    const bool has = t < n + 6;
-    const int64_t e = t < n ? e0 + t : n3 + 6 * (int64_t)p + (t - n);
-    const int64_t ec = has ? e : e0;  // an in-bounds address for idle lanes
-    double x = has ? src[e] : 0.0, a[kPreReg];
+    // Entries: lambda entry i < n, U entry i - n for n <= i < n + 6.  Four
+    // threads per entry for up to 64 of them (two up to 128, one beyond) take
+    // the vectors j = way (mod ways).
+    const int ne = n + 6;
+    auto gidx = [&](int i) -> int64_t { return i < n ? e0 + i : n3 + 6 * (int64_t)p + (i - n); };
+    const int ways = ne <= 64 ? 4 : ne <= 128 ? 2 : 1, span = kPreThreads / ways, el = t % span,
+              way = wave_uniform(t / span);
+    const int64_t ec = el < ne ? gidx(el) : e0;  // an in-bounds address for idle lanes
+    const double x = t < ne ? src[gidx(t)] : 0.0, bb = t < n ? B[(e0 + t) / 3] : 0.0;
+    double a[kPreReg];
 #pragma unroll
-    for (int j0 = 0; j0 < kPreReg; j0 += 16) {
-        if (j0 >= k) break;  // uniform
+    for (int i0 = 0; i0 < kPreReg; i0 += 4) {
+        if (ways * i0 >= k) break;  // uniform
 #pragma unroll
-        for (int j = j0; j < j0 + 16; ++j) a[j] = V[(j < k ? j : 0) * ld + ec];
+        for (int i = i0; i < i0 + 4; ++i) {
+            const int j = way + ways * i;
+            a[i] = V[(int64_t)(j < k ? j : 0) * ld + ec];
+        }
     }
+    // c1 of step k - 1, for the column that the first workgroup's last wave publishes
+    const int pl = t - (kPreThreads - 64);
+    const double g1 = p == 0 && pl >= 0 && pl < k ? gc1[pl] : 0.0;
     double np[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (t < 6)
 #pragma unroll
         for (int c = 0; c < 6; ++c) np[c] = Nall[36 * (int64_t)p + 6 * t + c];
     // c2 of step k - 1 into cs[0..k), |y'|^2 into cs[k] (k = 0: |b|^2 from
     // the right-hand side kernel's partials)
-    reduce_rows<kPreThreads, 4, kPre>(part2, k + 1, ncol2, cs);
-    if (t == 0) {
-        double s2 = cs[k];
-        for (int j = 0; j < k; ++j) s2 -= cs[j] * cs[j];
+    rows.finish(part2, k + 1, ncol2, cs);
+    // the second correction, and by the first wave the norm
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPreReg; ++i)
+        if (way + ways * i < k) s = fma(cs[way + ways * i], a[i], s);
+    for (int j = way + ways * kPreReg; j < k; j += ways) s = fma(cs[j], V[(int64_t)j * ld + ec], s);
+    upd[t] = s;
+    double* hc = hslots + (size_t)((k + PinnedSlots::kSlots - 1) % PinnedSlots::kSlots) * slot;
+    if (t < 64) {
+        double q = 0.0;
+        for (int j = t; j < k; j += 64) q = fma(cs[j], cs[j], q);
+        const double s2 = cs[k] - lane_group_sum<64>(q);
         const double h = s2 > 0.0 ? sqrt(s2) : 0.0;
-        sc = h;  // h = 0: breakdown, this step's values are discarded
-        if (p == 0 && k > 0)
-            publish(hslots + (size_t)((k - 1) % PinnedSlots::kSlots) * slot + k, h);
-        else if (p == 0)
-            publish_header(h_hdr, h, bad0, bad1);  // |b|
-    }
-    if (k > 0 && p == 0) {
+        if (t == 0) {
+            sc = h;  // h = 0: breakdown, this step's values are discarded
+            if (p == 0 && k > 0)
+                publish(hc + k, h);
+            else if (p == 0)
+                publish_header(h_hdr, h, bad0, bad1);  // |b|
+        }
+    } else if (p == 0 && pl >= 0) {
         // publish column k - 1: c1 (kept by its gs2) + c2
-        double* hc = hslots + (size_t)((k - 1) % PinnedSlots::kSlots) * slot;
-        for (int j = t; j < k; j += kPreThreads) publish(hc + j, gc1[j] + cs[j]);
+        for (int j = pl; j < k; j += 64) publish(hc + j, (j == pl ? g1 : gc1[j]) + cs[j]);
     }
     if (lds_factor) sl.store(Ls, n * n);
     sw.store(Ws, 6 * n);
     __syncthreads();
-    if (has) {
-#pragma unroll
-        for (int j = 0; j < kPreReg; ++j)
-            if (j < k) x -= cs[j] * a[j];  // a[j] is V_j only for j < k
-        for (int j0 = kPreReg; j0 < k; j0 += kPre) {
-            double b[kPre];
-#pragma unroll
-            for (int j = 0; j < kPre; ++j) b[j] = j0 + j < k ? V[(j0 + j) * ld + e] : 0.0;
-#pragma unroll
-            for (int j = 0; j < kPre; ++j)
-                if (j0 + j < k) x -= cs[j0 + j] * b[j];
-        }
-        const double v = x / sc;
-        V[(int64_t)k * ld + e] = v;
+    if (t < ne) {
+        double c = upd[t];
+        for (int u = 1; u < ways; ++u) c += upd[t + u * span];
+        const double v = (x - c) / sc;
+        V[(int64_t)k * ld + gidx(t)] = v;
         r[t] = v;  // lambda entries, then the six U entries at r[n ..]
     }
     __syncthreads();
     // t1 = L^-1 r_lambda; s = W^T r_lambda (six sums of 16 lanes each)
-    if (t < n) t1[t] = lds_factor ? dot4(Ls + t * n, 1, r, t + 1) : dot4(Li + (int64_t)t * n, 1, r, t + 1);
-    if (t < 96) {
-        const int c = t >> 4, l16 = t & 15;
+    // (up to 64 entries: four lanes per entry apply the factors)
+    const bool spread = lds_factor && n <= 64;
+    const int ei = t >> 2;
+    if (spread) {
+        if (ei < n) {
+            double z = 0.0;
+            for (int m = t & 3; m <= ei; m += 4) z = fma(Ls[ei * n + m], r[m], z);
+            z = lane_group_sum<4>(z);
+            if ((t & 3) == 0) t1[ei] = z;
+        }
+    } else if (t < n) {
+        t1[t] = lds_factor ? dot4(Ls + t * n, 1, r, t + 1) : dot4(Li + (int64_t)t * n, 1, r, t + 1);
+    }
+    if (t >= kPreThreads - 96) {
+        const int q = t - (kPreThreads - 96), c = q >> 4, l16 = q & 15;
         double s = 0.0;
         for (int i = l16; i < n; i += 16) s = fma(Ws[6 * i + c], r[i], s);
         s = lane_group_sum<16>(s);
@@ -131,9 +162,17 @@ __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
     }
     __syncthreads();
     // tt = L^-T t1 = M_pp^-1 r_lambda; z_U = -N_p (r_U + s)
-    if (t < n)
+    if (spread) {
+        if (ei < n) {
+            double z = 0.0;
+            for (int m = ei + (t & 3); m < n; m += 4) z = fma(Ls[m * n + ei], t1[m], z);
+            z = lane_group_sum<4>(z);
+            if ((t & 3) == 0) tt[ei] = z;
+        }
+    } else if (t < n) {
         tt[t] = lds_factor ? dot4(Ls + t * n + t, n, t1 + t, n - t)
                            : dot4(Li + (int64_t)t * n + t, n, t1 + t, n - t);
+    }
     if (t < 6) {
         double s = 0.0;
 #pragma unroll
@@ -149,7 +188,7 @@ __global__ __launch_bounds__(kPreThreads) void rg_pre_kernel(
         for (int c = 0; c < 6; ++c) s = fma(Ws[6 * t + c], z6[c], s);
         zl[e0 + t] = s;
         const int64_t blob = (e0 + t) / 3;
-        rec[blob * recw + PW + (int)(e0 + t - 3 * blob)] = (R)(B[blob] * s);
+        rec[blob * recw + PW + (int)(e0 + t - 3 * blob)] = (R)(bb * s);
     }
 }
 
@@ -258,6 +297,9 @@ __global__ __launch_bounds__(kPreThreads) void rg_fin_kernel(const double* __res
     }
 }
 
+// out reads the product's partials (latency-bound); its dot products are folded
+// together four at a time (wave_fold): 31 us against 36 a step on 1024 bodies
+// of 12 blobs.
 template <typename R>
 __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     const double* __restrict__ pos, const double* __restrict__ q, const int* __restrict__ bofs,
@@ -294,7 +336,7 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     }
     // the lane's basis values for the dot products: waves take the vectors
     // j = wave (mod kWaves), lanes the entries l, l + 64, l + 128
-    const int wv = t >> 6, l = t & 63;
+    const int wv = wave_uniform(t >> 6), l = t & 63;
     auto gidx = [&](int i) -> int64_t { return i < n ? e0 + i : n3 + 6 * (int64_t)p + (i - n); };
     constexpr int kJ = 64 / kWaves;  // vectors per wave held in registers (j < 64)
     double av[kJ][kSlots];
@@ -359,22 +401,21 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     double wv3[kSlots];
 #pragma unroll
     for (int s = 0; s < kSlots; ++s) wv3[s] = l + 64 * s < ne ? wl[l + 64 * s] : 0.0;
-    double pr[kJ];
+    // the wave's dot products, four vectors folded together at a time
 #pragma unroll
-    for (int i = 0; i < kJ; ++i) {
-        double s = 0.0;
+    for (int i0 = 0; i0 < kJ; i0 += 4) {
+        if (kWaves * i0 > k) break;  // uniform
+        double pr[4];
 #pragma unroll
-        for (int c = 0; c < kSlots; ++c) s = fma(av[i][c], wv3[c], s);
-        pr[i] = s;
-    }
+        for (int i = 0; i < 4; ++i) {
+            double s = 0.0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int i = 0; i < kJ; ++i) pr[i] += __shfl_xor(pr[i], o, 64);
-#pragma unroll
-    for (int i = 0; i < kJ; ++i) {
-        const int j = wv + kWaves * i;
-        if (l == 0 && j <= k) part1[(int64_t)j * nbodies + p] = pr[i];
+            for (int c = 0; c < kSlots; ++c) s = fma(av[i0 + i][c], wv3[c], s);
+            pr[i] = s;
+        }
+        wave_fold<4, 32>(pr);
+        const int j = wv + kWaves * (i0 + wave_value<4>(l));
+        if (l % 16 == 0 && j <= k) part1[(int64_t)j * nbodies + p] = pr[0];
     }
     for (int j = wv + 64; j <= k; j += kWaves) {  // beyond the vectors held in registers
         double s = 0.0;
