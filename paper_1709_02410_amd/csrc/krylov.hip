@@ -23,12 +23,162 @@ namespace {
 constexpr int kBodyThreads = 128;
 constexpr int kBuildThreads = 256;
 
+// D = Ld d Ld^T of the 3 x 3 diagonal block at row k, and 1 / d (0 where d <= 0).
+struct Diag3 {
+    double d[3], id[3], l10, l20, l21;
+    __device__ __forceinline__ explicit Diag3(const double (*P)[4]) {
+        const double p10 = P[1][0], p20 = P[2][0];
+        d[0] = P[0][0];
+        id[0] = d[0] > 0.0 ? 1.0 / d[0] : 0.0;
+        l10 = p10 * id[0];
+        l20 = p20 * id[0];
+        d[1] = fma(-l10, p10, P[1][1]);
+        id[1] = d[1] > 0.0 ? 1.0 / d[1] : 0.0;
+        const double e21 = fma(-l20, p10, P[2][1]);
+        l21 = e21 * id[1];
+        d[2] = fma(-l21, e21, fma(-l20, p20, P[2][2]));
+        id[2] = d[2] > 0.0 ? 1.0 / d[2] : 0.0;
+    }
+    // x = Ld^-1 v, z = D^-1 v
+    __device__ __forceinline__ void solve(const double* v, double* x, double* z) const {
+        x[0] = v[0];
+        x[1] = fma(-l10, x[0], v[1]);
+        x[2] = fma(-l21, x[1], fma(-l20, x[0], v[2]));
+        z[2] = x[2] * id[2];
+        z[1] = fma(-l21, z[2], x[1] * id[1]);
+        z[0] = fma(-l20, z[2], fma(-l10, z[1], x[0] * id[0]));
+    }
+};
+
+// Factors of a body of up to NM / 3 blobs in registers, three columns (a
+// blob's) at a time.  Lane t of wave w has, of the blobs w, w + 4, ..., the
+// columns of row t of the body's block (a) and the rows of column t of the
+// identity (y), on which the same elimination leaves the inverse factor.  For
+// blob K, whose columns P and rows Q its wave has put into LDS, every lane forms
+//   a(t, j) -= P_j . D^-1 P_t,   y(j, t) -= P_j . D^-1 Q_t
+// for its later blobs, with the same broadcast P_j for both; P is three values
+// per row.  What bounds the kernel is the chain of the blobs' steps, and with
+// several bodies to a compute unit the LDS reads of P_j (shared by a and y for
+// that reason).  256 threads with the block in LDS and a barrier per column
+// took 51 us for 256 bodies of 15 blobs and 68 us for 1024 of 12; this takes 19
+// and 25.
+template <int NM>
+__global__ __launch_bounds__(256) void precond_build_regs_kernel(const double* __restrict__ pos,
+                                                                 const int* __restrict__ bofs,
+                                                                 const int64_t* __restrict__ lofs, double inv_a,
+                                                                 double mu0, double* __restrict__ Lout,
+                                                                 int* __restrict__ notspd) {
+    constexpr int ld = NM | 1, NB = NM / 3, NBW = (NB + 3) / 4;
+    // the block's lower triangle, then L below the diagonal and the transpose
+    // of L^-1 above it, both without the roots of d
+    __shared__ double A[NM * ld];
+    __shared__ double px[NB], py[NB], pz[NB], pb[NB];
+    __shared__ __align__(16) double P[2][64][4], Q[2][64][4];
+    __shared__ double dg[NM], rs[NM];
+    const int p = blockIdx.x, t = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b0 = bofs[p], nb = bofs[p + 1] - b0, n = 3 * nb;
+    if (threadIdx.x < nb) {
+        const double x = pos[3 * (b0 + t)] * inv_a, y = pos[3 * (b0 + t) + 1] * inv_a,
+                     z = pos[3 * (b0 + t) + 2] * inv_a;
+        px[t] = x;
+        py[t] = y;
+        pz[t] = z < 1.0 ? 1.0 : z;
+        pb[t] = z < 1.0 ? z : 1.0;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < nb * (nb + 1) / 2; q += 256) {  // blob pairs ib <= ia
+        int ia = (int)((sqrtf(8.0f * q + 1.0f) - 1.0f) * 0.5f);
+        ia -= ia * (ia + 1) / 2 > q;
+        ia += (ia + 1) * (ia + 2) / 2 <= q;
+        const int ib = q - ia * (ia + 1) / 2;
+        const double dx = px[ia] - px[ib], dy = py[ia] - py[ib], dz = pz[ia] - pz[ib];
+        const PairCoef<double> c = pair_coef<double>(dx, dy, dz, pz[ia], pz[ib]);
+        const double sc = mu0 * pb[ia] * pb[ib];
+#pragma unroll
+        for (int beta = 0; beta < 3; ++beta) {
+            double u[3] = {0.0, 0.0, 0.0};
+            pair_apply<double>(c, dx, dy, dz, beta == 0 ? 1.0 : 0.0, beta == 1 ? 1.0 : 0.0, beta == 2 ? 1.0 : 0.0,
+                               u[0], u[1], u[2]);
+#pragma unroll
+            for (int al = 0; al < 3; ++al) A[(3 * ia + al) * ld + 3 * ib + beta] = sc * u[al];
+        }
+    }
+    __syncthreads();
+    // (entries above the diagonal and lanes from n on hold what they will:
+    // nothing of it reaches an entry of the factors)
+    double a[3 * NBW], y[3 * NBW];
+#pragma unroll
+    for (int m = 0; m < NBW; ++m)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int j = 3 * (w + 4 * m) + c;
+            a[3 * m + c] = A[(t < n ? t : 0) * ld + (j < NM ? j : 0)];
+            y[3 * m + c] = j == t ? 1.0 : 0.0;
+        }
+    if (w == 0)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            P[0][t][c] = a[c];
+            Q[0][t][c] = y[c];
+        }
+    __syncthreads();
+    for (int K = 0; K < nb; ++K) {
+        const int k = 3 * K;
+        const double(*Pk)[4] = P[K & 1];
+        const Diag3 D(Pk + k);
+        double xa[3], za[3], xy[3], zy[3];
+        D.solve(Pk[t], xa, za);
+        D.solve(Q[K & 1][t], xy, zy);
+#pragma unroll
+        for (int m = 0; m < NBW; ++m) {
+            const int B = w + 4 * m;
+            if (B <= K || B >= nb) continue;  // uniform
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const double* r = Pk[3 * B + c];
+                const double r0 = r[0], r1 = r[1], r2 = r[2];
+                a[3 * m + c] = fma(-za[2], r2, fma(-za[1], r1, fma(-za[0], r0, a[3 * m + c])));
+                y[3 * m + c] = fma(-zy[2], r2, fma(-zy[1], r1, fma(-zy[0], r0, y[3 * m + c])));
+            }
+            if (B == K + 1)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    P[(K + 1) & 1][t][c] = a[3 * m + c];
+                    Q[(K + 1) & 1][t][c] = y[3 * m + c];
+                }
+        }
+        if (w == (K & 3) && t < n)  // this blob's wave has the least left to do
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if (t == k + c)
+                    dg[t] = D.d[c];
+                else
+                    A[t * ld + k + c] = t > k + c ? xa[c] : xy[c];
+            }
+        __syncthreads();
+    }
+    if (threadIdx.x < n) {
+        const double d = dg[t];
+        if (!(d > 0.0)) atomicOr(notspd, 1);
+        const double sd = d > 0.0 ? sqrt(d) : 1.0;
+        dg[t] = sd;
+        rs[t] = 1.0 / sd;
+    }
+    __syncthreads();
+    double* L = Lout + 2 * lofs[p];
+    double* Li = L + (int64_t)n * n;
+    if (t < n)
+        for (int i = w; i < n; i += 4) {
+            L[i * n + t] = t < i ? A[i * ld + t] * rs[t] : t == i ? dg[i] : 0.0;
+            Li[i * n + t] = t < i ? A[t * ld + i] * rs[i] : t == i ? rs[i] : 0.0;
+        }
+}
+
 // Dense M^(pp) of one body (units: physical, includes mu0 and B factors)
 // assembled in LDS, then factorised in place (right-looking Cholesky).  The
 // LDS is sized at launch for the largest body of the call (ld = 3 n_max + 1
 // doubles per row, then 4 n_max doubles of blob data), so that small bodies
 // keep many workgroups per CU.
-template <int KR>
 __global__ __launch_bounds__(kBuildThreads) void precond_build_kernel(const double* __restrict__ pos,
                                                                      const int* __restrict__ bofs,
                                                                      const int64_t* __restrict__ lofs, double inv_a,
@@ -41,18 +191,11 @@ __global__ __launch_bounds__(kBuildThreads) void precond_build_kernel(const doub
     double* py = px + nmax;
     double* pz = py + nmax;
     double* pb = pz + nmax;
-    // KR > 0: the eliminated identity Y (n x n, row stride 3 nmax), after
-    // the blob data
-    double* Ybase = pb + nmax;
-    const int ldy = 3 * nmax;
     __shared__ int bad;
     const int p = blockIdx.x;
     const int b0 = bofs[p], nb = bofs[p + 1] - b0, n = 3 * nb;
 #define A(i, j) Abase[(i) * ld + (j)]
-#define Y(i, j) Ybase[(i) * ldy + (j)]
     if (threadIdx.x == 0) bad = 0;
-    if constexpr (KR > 0)
-        for (int q = threadIdx.x; q < n * n; q += blockDim.x) Y(q / n, q % n) = q / n == q % n ? 1.0 : 0.0;
     for (int a = threadIdx.x; a < nb; a += blockDim.x) {
         const double x = pos[3 * (b0 + a)] * inv_a, y = pos[3 * (b0 + a) + 1] * inv_a,
                      z = pos[3 * (b0 + a) + 2] * inv_a;
@@ -81,64 +224,14 @@ __global__ __launch_bounds__(kBuildThreads) void precond_build_kernel(const doub
     // the scaling touches only column k, which no later step reads or
     // writes, so it needs no barrier of its own.
     // Threads form a 16 x 16 grid over (row, column) of the trailing block.
-    // For bodies of up to 16 blobs (KR = 3 rows and columns per thread) a
-    // thread loads its column-k values and its entries first, then updates
-    // and stores them, so that its LDS reads overlap; the same steps also
-    // eliminate an identity block Y, which yields L^-1 without a separate
-    // substitution (below).
     const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
     for (int k = 0; k < n; ++k) {
         const double d = A(k, k);
         const bool ok = d > 0.0;
-        if constexpr (KR > 0) {
-            // every load is issued unconditionally from an in-bounds entry
-            // (row and column clamped to n - 1) and masked afterwards, so
-            // that the loads go out together instead of one branch each
-            const int nl = n - 1;
-            double ai[KR], aj[KR], v[KR][KR];
-#pragma unroll
-            for (int r = 0; r < KR; ++r) {
-                const int i = k + 1 + tr + 16 * r, j = k + 1 + tc + 16 * r;
-                ai[r] = A(i < n ? i : nl, k);
-                aj[r] = A(j < n ? j : nl, k);
-            }
-#pragma unroll
-            for (int r = 0; r < KR; ++r)
-#pragma unroll
-                for (int c = 0; c < KR; ++c) {
-                    const int i = k + 1 + tr + 16 * r, j = k + 1 + tc + 16 * c;
-                    v[r][c] = A(i < n ? i : nl, j < n ? j : nl);
-                }
-            // the same row operations on Y (rows i > k, columns j <= k, the
-            // only nonzero ones): Y(i, j) -= (A(i, k) / A(k, k)) Y(k, j)
-            double yk[KR], yv[KR][KR];
-#pragma unroll
-            for (int c = 0; c < KR; ++c) {
-                const int j = tc + 16 * c;
-                yk[c] = Y(k, j < n ? j : nl);
-            }
-#pragma unroll
-            for (int r = 0; r < KR; ++r)
-#pragma unroll
-                for (int c = 0; c < KR; ++c) {
-                    const int i = k + 1 + tr + 16 * r, j = tc + 16 * c;
-                    yv[r][c] = Y(i < n ? i : nl, j < n ? j : nl);
-                }
-            const double id = ok ? 1.0 / d : 0.0;
-#pragma unroll
-            for (int r = 0; r < KR; ++r)
-#pragma unroll
-                for (int c = 0; c < KR; ++c) {
-                    const int i = k + 1 + tr + 16 * r, j = k + 1 + tc + 16 * c, jy = tc + 16 * c;
-                    if (j <= i && i < n) A(i, j) = v[r][c] - ai[r] * aj[c] * id;
-                    if (jy <= k && i < n) Y(i, jy) = yv[r][c] - ai[r] * id * yk[c];
-                }
-        } else {
-            const double id = ok ? 1.0 / d : 0.0;
-            for (int i = k + 1 + tr; i < n; i += 16) {
-                const double aik = A(i, k);
-                for (int j = k + 1 + tc; j <= i; j += 16) A(i, j) -= aik * A(j, k) * id;
-            }
+        const double id = ok ? 1.0 / d : 0.0;
+        for (int i = k + 1 + tr; i < n; i += 16) {
+            const double aik = A(i, k);
+            for (int j = k + 1 + tc; j <= i; j += 16) A(i, j) -= aik * A(j, k) * id;
         }
         __syncthreads();
         const double sd = ok ? sqrt(d) : 1.0, isd = 1.0 / sd;
@@ -159,17 +252,6 @@ __global__ __launch_bounds__(kBuildThreads) void precond_build_kernel(const doub
     for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
         const int i = q / n, j = q % n;
         L[q] = j <= i ? A(i, j) : 0.0;
-    }
-    if constexpr (KR > 0) {
-        // A = L1 D L1^T with L1 unit lower triangular; the elimination turned
-        // the identity into Y = L1^-1, and L = L1 D^{1/2}, so L^-1 =
-        // D^{-1/2} Y: row i of Y times 1 / L(i, i)
-        for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
-            const int i = q / n, j = q % n;
-            Li[q] = j <= i ? Y(i, j) * rd[i] : 0.0;
-        }
-        if (threadIdx.x == 0 && bad) atomicOr(notspd, 1);
-        return;
     }
     // Inverse factor L^-1 (lower triangular), four lanes per column: forward
     // substitution of L x = e_col, entry (i, col) = -(sum over col <= k < i
@@ -202,7 +284,6 @@ __global__ __launch_bounds__(kBuildThreads) void precond_build_kernel(const doub
     }
     if (threadIdx.x == 0 && bad) atomicOr(notspd, 1);
 #undef A
-#undef Y
 }
 
 // mode 0: out = L v;  1: out = L^-1 v;  2: out = L^-T v, with the factor L
@@ -537,16 +618,25 @@ int body_factors_launch(const double* pos, int64_t N, double a, double eta, cons
                         int* notspd, hipStream_t st) {
     const double inv_a = 1.0 / a, m0 = 1.0 / (6.0 * M_PI * eta * a);
     if (!pc.diag) {
-        const size_t lds = ((size_t)3 * nmax * (3 * nmax + 1) + 4 * (size_t)nmax) * sizeof(double);
-        if (3 * nmax <= 48) {
-            const size_t ldsy = lds + (size_t)9 * nmax * nmax * sizeof(double);  // and Y
-            hipLaunchKernelGGL(precond_build_kernel<3>, dim3(pc.nb), dim3(kBuildThreads), ldsy, st, pos, pc.bofs,
-                               pc.lofs, inv_a, m0, pc.L, notspd, nmax);
+        auto regs = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(pc.nb), dim3(256), 0, st, pos, pc.bofs, pc.lofs, inv_a, m0, pc.L, notspd);
+        };
+        // up to 21 blobs a body's rows fit the lanes of a wave; the size of the
+        // largest body sets the registers and the LDS of all
+        if (nmax <= 8) {
+            regs(precond_build_regs_kernel<24>);
+        } else if (nmax <= 12) {
+            regs(precond_build_regs_kernel<36>);
+        } else if (nmax <= 16) {
+            regs(precond_build_regs_kernel<48>);
+        } else if (nmax <= 21) {
+            regs(precond_build_regs_kernel<63>);
         } else {
+            const size_t lds = ((size_t)3 * nmax * (3 * nmax + 1) + 4 * (size_t)nmax) * sizeof(double);
             if (lds > 65536)  // up to 129 KB for 42-blob bodies
-                RPYW_HIP(hipFuncSetAttribute((const void*)precond_build_kernel<0>,
+                RPYW_HIP(hipFuncSetAttribute((const void*)precond_build_kernel,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(precond_build_kernel<0>, dim3(pc.nb), dim3(kBuildThreads), lds, st, pos, pc.bofs,
+            hipLaunchKernelGGL(precond_build_kernel, dim3(pc.nb), dim3(kBuildThreads), lds, st, pos, pc.bofs,
                                pc.lofs, inv_a, m0, pc.L, notspd, nmax);
         }
     } else {

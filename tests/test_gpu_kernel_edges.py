@@ -117,10 +117,10 @@ def test_repeated_solves_are_bitwise_equal(rp):
             assert torch.equal(root, first[i][0]) and torch.equal(U, first[i][1])
 
 
-@pytest.mark.parametrize("blobs,bodies", [(4, 300), (15, 9), (21, 9), (25, 6), (42, 5)])
+@pytest.mark.parametrize("blobs,bodies", [(4, 300), (8, 30), (12, 12), (15, 9), (16, 9), (21, 9), (25, 6), (42, 5)])
 def test_krylov_vector_kernels(rp, orc, blobs, bodies):
-    """More than 256 groups of partials; 12, 45, 63, 75 and 126 entries to a
-    body (four, two and one thread per entry); 110 to 200 basis vectors, in
+    """More than 256 groups of partials; 12 to 126 entries to a body (four, two
+    and one thread per entry, every size of the factor kernels); 90 to 200 basis vectors, in
     registers (16 and 32 to a thread) and read again.  Bars: the tolerance
     1e-12 times the root of the condition number (1e3), and times it (1e5)."""
     from parity_util import krylov_path
@@ -133,6 +133,6 @@ def test_krylov_vector_kernels(rp, orc, blobs, bodies):
     with krylov_path(rp, N, True):
         root, it, _, ok = rp.lanczos_sqrt(_t(pos), _t(W), body_offsets=offs, tol=1e-12, max_iter=250)
         _, U, its, _, ok2 = rp.rigid_solve(_t(pos), _t(q), offs, _t(W), None, tol=1e-12, max_iter=250)
-    assert ok and ok2 and it > 100 and its > 100
+    assert ok and ok2 and it > 80 and its > 80
     check(root.cpu().numpy(), orc.dense_sqrt(pos, W, offs), 1e-9, f"root {blobs}x{bodies}")
     check(U.cpu().numpy(), orc.rigid_solve(pos, q, offs, W, None)[1], 1e-7, f"U {blobs}x{bodies}")
