@@ -272,9 +272,12 @@ int rg_launch_out(int prec, const double* pos, const double* q, const int* bofs,
                   const double* zu, int64_t n3, int64_t ld, const double* V, int k, double* w, double* part1,
                   const double* ypre, hipStream_t st);
 
-// Whether the fused Krylov steps sum the product's partials with the
-// symmetric epilogue first (groups of 256 blobs: large problems).
-inline bool krylov_presum(const SymPlan& sp) { return sp.G == 256; }
+// Whether the fused Krylov steps sum the product's partials with the symmetric
+// epilogue first: an entry has about ng / 2 of them, which the few workgroups
+// of out gather one batch after another, while the epilogue has the whole chip.
+// (A step of a rigid solve of 12288 blobs: 31 us to gather in out, 18 with the
+// epilogue; 0.7% of a solve lost at 2500 blobs, 1% gained at 4000, 8% at 10000.)
+inline bool krylov_presum(const SymPlan& sp) { return sp.G == 256 || sp.ng > 80; }
 
 // Krylov building blocks (krylov.hip).
 // Block-diagonal preconditioner factors: per body the Cholesky factor L_p of

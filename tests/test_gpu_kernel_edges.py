@@ -136,3 +136,30 @@ def test_krylov_vector_kernels(rp, orc, blobs, bodies):
     assert ok and ok2 and it > 80 and its > 80
     check(root.cpu().numpy(), orc.dense_sqrt(pos, W, offs), 1e-9, f"root {blobs}x{bodies}")
     check(U.cpu().numpy(), orc.rigid_solve(pos, q, offs, W, None)[1], 1e-7, f"U {blobs}x{bodies}")
+
+
+@pytest.mark.parametrize("N,prec", [(5100, 1), (5160, 1), (10245, 0)])
+def test_presummed_krylov_steps(rp, N, prec):
+    """Fused steps below and above the number of groups from which the
+    product's partials are summed first, against the steps on plain products
+    (pair terms in FP32: 1e-5; FP64: 1e-11, a few steps of 1e-12 each)."""
+    rng = np.random.default_rng(N)
+    side = int(np.ceil((N / 5) ** 0.5))
+    b = np.arange(N // 5)
+    at = np.stack([4.5 * (b % side), 4.5 * (b // side), np.full(b.size, 1.4)], -1)
+    arm = np.array([[0, 0, 0], [1.9, 0, 0], [0, 1.9, 0], [0, 0, 1.9], [1.9, 1.9, 0]])
+    pos = (at[:, None] + arm + 0.05 * rng.standard_normal((b.size, 5, 3))).reshape(-1, 3)
+    offs, W, q = np.arange(0, N + 1, 5), rng.standard_normal((N, 3)), pos[::5]
+
+    def run():
+        root = rp.lanczos_sqrt(_t(pos), _t(W), body_offsets=offs, tol=1e-30, max_iter=4, precision=prec)[0]
+        U = rp.rigid_solve(_t(pos), _t(q), offs, _t(W), None, tol=1e-30, max_iter=4, precision=prec)[1]
+        return root.cpu().numpy(), U.cpu().numpy()
+    got = run()
+    rp.set_shape(prec, N, 1, tpl=1, tile=256, kblk=1, sym=0)
+    try:
+        ref = run()
+    finally:
+        rp.reset_shape(prec, N, 1)
+    for g, r, what in zip(got, ref, ("root", "U")):
+        check(g, r, 1e-11 if prec == 0 else 1e-5, f"{what} N={N} prec={prec}")
