@@ -104,8 +104,11 @@ int64_t g_prof_n = 0;
 // 64 blobs, one item per workgroup, are up to 3x faster than groups of 256
 // below ten thousand blobs (which leave the GPU underfilled) and still 5% at
 // 30000; wider RHS blocks are faster on the plain kernel, and FP32C blocks
-// of 8 or more are contracted on the matrix cores.  For groups of 256
-// ipw keeps the grid at roughly 16k workgroups or more.  In FP64 two targets
+// of 8 or more are contracted on the matrix cores.  Groups of 256
+// take 4 or 6 items to a workgroup and end with chunks of one (sym_tail): 1.956
+// ms at 50000 blobs in FP32C against 1.974 with one item to each, 7.69 at 1e5
+// against 7.74 to 7.88 with four and no tail; six below 32768 items leave too
+// few workgroups (0.908 against 0.868 ms at 33000).  In FP64 two targets
 // per lane (sym_multi.h) make the symmetric kernel the faster one for up to
 // four right-hand sides as well; 5 or 6 right-hand sides go in a block of 4
 // and the rest (at 3840 blobs 85 and 92 against 102 us for one block of 8 on
@@ -119,8 +122,10 @@ Shape default_shape(int64_t N, int k, int prec) {
     // leave half of every contraction empty).
     s.kblk = std::min(kclass(k), prec == RPYW_FP32C ? 16 : (kclass(k) > 8 ? 16 : 8));
     s.sym = (s.kblk == 1 && N >= 512) ? (N <= kSym64MaxN ? 2 : 1) : 0;
-    const int64_t ng = (N + 255) / 256, hm = ng / 2 + 1;
-    s.ipw = s.sym == 2 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(4, hm * ng / 16384));
+    const int64_t ng = (N + 255) / 256, items = (ng / 2 + 1) * ng;
+    s.ipw = s.sym == 2   ? 1
+            : s.sym == 1 ? (items < 32768 ? 4 : 6)
+                         : (int)std::max<int64_t>(1, std::min<int64_t>(4, items / 16384));
     s.mat = (s.kblk >= (prec == RPYW_FP32C ? 8 : 16)) ? 1 : 0;
     if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : 512) && k <= 6 && N <= (k == 1 ? kSym2MaxN1 : kSym2MaxN)) {
         s.kblk = std::min(s.kblk, 4);

@@ -415,7 +415,7 @@ hipError_t launch_sym_t(const R* rec, const SymPlan& sp, double* tpart, R* spart
                                ipw, sp.Hmax, sp.nseg, tpart, spart, box, p0);
     } else {
         hipLaunchKernelGGL((sym_kernel<R, ProductBody<R, K, PER>, 4>), grid, dim3(256), 0, st, rec, sp.ng, sp.C, ipw,
-                           sp.Hmax, sp.nseg, tpart, spart, box, p0);
+                           sp.Hmax, sp.nseg, tpart, spart, box, p0, sp.tail);
     }
     return hipGetLastError();
 }
@@ -584,7 +584,8 @@ SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G) {
     // source partials on large problems.
     if (s.G == 128 && N > kSym2MaxN1) ipw = std::max(ipw, 4);
     s.ipw = ipw;
-    s.C = (s.Hmax + 1 + ipw - 1) / ipw;
+    s.tail = sym_tail(s.G, ipw, s.ng, s.Hmax);
+    s.C = sym_chunks(ipw, s.Hmax, s.tail);
     // Segments: enough work items to give every SIMD several (independent
     // of ipw, so that the workspace bound taken at ipw 1 holds).
     const int64_t items = (int64_t)s.ng * (s.Hmax + 1);

@@ -48,9 +48,20 @@ struct SymPlan {
     int ns;    // waves per item that split its passes (1, or 4 for groups of 64 when items are few)
     int nseg;  // workgroups per item that split its passes (1, 2 or 4: more workgroups for tiny problems)
     int ng, Hmax, C;
+    int tail;  // last chunks of a row, of one item each (sym_tail)
     size_t rec_bytes, tpart_bytes, spart_bytes;
     bool ok;
 };
+// Groups of 256: the last sym_tail items of each row are chunks of their own,
+// and are started after all others, so that the chunks that run last are short:
+// kSymTail of them, more than run at a time (1024 to 1280).  Without them the
+// end of a launch left the GPU half empty for about one chunk, 0.1 ms an item at
+// 1e5 blobs.
+constexpr int kSymTail = 2048;
+inline int sym_tail(int G, int ipw, int ng, int Hmax) {
+    return G == 256 && ipw > 1 ? std::min((kSymTail + ng - 1) / ng, Hmax + 1) : 0;
+}
+inline int sym_chunks(int ipw, int Hmax, int tail) { return (Hmax + 1 - tail + ipw - 1) / ipw + tail; }
 // Groups of 64 are for problems up to this size: their source partials grow
 // as N^2 / 128 per quantity, four times those of groups of 256, and beyond
 // a few ten thousand blobs both group sizes run at the same speed.

@@ -278,7 +278,8 @@ struct SymLane {
 template <typename R, class Body, int NB = 4, int NS = 1, bool FP = false>
 __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__ rec, int ng, int C, int ipw,
                                                            int Hmax, int nseg, double* __restrict__ tpart,
-                                                           R* __restrict__ spart, Box<R> box, PackSrc ps) {
+                                                           R* __restrict__ spart, Box<R> box, PackSrc ps,
+                                                           int tail = 0) {
     static_assert(NS == 1 || NB == 1, "step segments within a workgroup need one target block");
     using L = SymLane<R, Body>;
     using VT = typename Vec<R>::T;
@@ -304,7 +305,10 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
     // registers there).
     constexpr bool kPhased = !kLds && NQ > 3 && NS == 1;
     __shared__ R red[kLds ? 1 : (kPhased ? 1 : NW)][kLds ? 1 : NQ][kLds ? 1 : G];
-    const int g = blockIdx.x % nseg, P = blockIdx.x / nseg / C, c = blockIdx.x / nseg % C;
+    // With a tail (NB = 4) the workgroups run over the rows first, so that the
+    // last chunks of every row, of one item each, come last.
+    const int g = blockIdx.x % nseg, b0 = blockIdx.x / nseg;
+    const int P = NB == 4 && tail ? b0 % ng : b0 / C, c = NB == 4 && tail ? b0 / ng : b0 % C;
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int w = NS > 1 ? 0 : wave;     // target block of the wave
     const int seg = NS > 1 ? wave : 0;   // step segment of the wave
@@ -321,8 +325,10 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
         me.load(rec + ((int64_t)P * G + w * 64 + l) * L::RW);
     }
     const int H = sym_rowlen(P, ng);
-    const int d0 = c * ipw;
-    const int d1 = d0 + ipw - 1 < H ? d0 + ipw - 1 : H;
+    const bool last = NB == 4 && c >= C - tail;
+    const int d0 = last ? Hmax + 1 - (C - c) : c * ipw;
+    const int dn = NB == 4 && tail ? (last ? d0 : Hmax - tail) : H;
+    const int d1 = min(min(d0 + ipw - 1, dn), H);
     for (int d = d0; d <= d1; ++d) {
         const int Q = (P + d) % ng;
         __syncthreads();
@@ -402,7 +408,7 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
             }
         }
     }
-    double* tp = tpart + (int64_t)blockIdx.x * NQ * G;  // chunk c * nseg + g of row P
+    double* tp = tpart + (((int64_t)P * C + c) * nseg + g) * NQ * G;
     if constexpr (NS > 1) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) tred[seg][q][l] = me.total(q);

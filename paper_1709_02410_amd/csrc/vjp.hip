@@ -264,7 +264,7 @@ namespace {
 constexpr int64_t kVjpWaves = 2048;
 constexpr int64_t kVjpFusedItems = 3072;
 struct VjpPlan {
-    int G, ns, nseg, ng, C, Hmax;
+    int G, ns, nseg, ng, C, Hmax, tail;
     size_t tb, sb;
     bool fused, ok;
 };
@@ -274,7 +274,8 @@ VjpPlan vjp_sym_plan(int64_t N, int prec, int ipw, int G) {
     if (G == 64 && N > kSym64MaxN) return p;
     p.ng = (int)((N + G - 1) / G);
     p.Hmax = p.ng / 2;
-    p.C = (p.Hmax + 1 + ipw - 1) / ipw;
+    p.tail = sym_tail(G, ipw, p.ng, p.Hmax);
+    p.C = sym_chunks(ipw, p.Hmax, p.tail);
     const int64_t items = (int64_t)p.ng * (p.Hmax + 1);
     p.ns = (prec == RPYW_FP64 && G == 64 && items < kVjpWaves) ? 4 : 1;
     p.fused = G == 64 && items <= kVjpFusedItems;
@@ -304,7 +305,7 @@ void launch_vjp_sym(const R* rec, const PackSrc& ps, const VjpPlan& p, int ipw, 
                            tpart, spart, Box<R>{}, PackSrc{});
     else
         hipLaunchKernelGGL((sym_kernel<R, VjpBody<R>, 4>), grid, dim3(256), 0, st, rec, p.ng, p.C, ipw, p.Hmax, p.nseg,
-                           tpart, spart, Box<R>{}, PackSrc{});
+                           tpart, spart, Box<R>{}, PackSrc{}, p.tail);
 }
 
 // One symmetric VJP: records (unless fused), pairs, epilogue.

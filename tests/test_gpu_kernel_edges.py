@@ -163,3 +163,22 @@ def test_presummed_krylov_steps(rp, N, prec):
         rp.reset_shape(prec, N, 1)
     for g, r, what in zip(got, ref, ("root", "U")):
         check(g, r, 1e-11 if prec == 0 else 1e-5, f"{what} N={N} prec={prec}")
+
+
+@pytest.mark.parametrize("N", [300, 16100, 16400, 16900, 20000])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_tail_chunks(rp, N, prec):
+    """Groups of 256: rows of tail chunks alone (up to 63 groups), and of main
+    chunks with remainders and a tail, for odd and even numbers of groups; one
+    item to a chunk gives the same sums up to the order of FP64 additions."""
+    pos = 0.9 * _mixed(N, N)
+    f, g = np.random.default_rng(N + 1).standard_normal((2, N, 3))
+    runs = []
+    for ipw in (1, 2, 3, 6):
+        rp.set_shape(prec, N, 1, tpl=1, tile=256, kblk=1, sym=1, ipw=ipw)
+        u = rp.matvec(_t(pos), _t(f), 0.9, 1.3, precision=prec)
+        runs.append([x.cpu().numpy() for x in (u, *rp.matvec_vjp(_t(pos), _t(f), _t(g), 0.9, 1.3, precision=prec))])
+    rp.reset_shape(prec, N, 1)
+    for ipw, r in zip((2, 3, 6), runs[1:]):
+        for x, ref, what in zip(r, runs[0], ("u", "grad_pos", "grad_f")):
+            check(x, ref, 1e-12, f"{what} N={N} prec={prec} ipw={ipw}")
