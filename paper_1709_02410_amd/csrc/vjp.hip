@@ -360,7 +360,10 @@ int vjp(const double* pos, const double* f, const double* g, double* grad_pos, d
     const double m0 = 1.0 / (6.0 * M_PI * eta * a);
     const unsigned g1 = (unsigned)((N + kBlock - 1) / kBlock);
     VjpPlan p{};
-    if (sh.sym) p = vjp_sym_plan(N, prec, ipw, sym_group(sh.sym));
+    if (sh.sym)
+        p = vjp_sym_plan(N, prec, ipw, sym_group(sh.sym));
+    else if (sh.direct)
+        p = vjp_sym_plan(N, prec, 1, 64);
     if (sh.sym && !p.ok && p.G == 64) p = vjp_sym_plan(N, prec, ipw, 256);
     if (p.ok) {
         const int rc = prec == RPYW_FP32C ? vjp_sym<float>(pos, f, g, grad_pos, grad_f, N, a, m0, p, ipw, ar, st)

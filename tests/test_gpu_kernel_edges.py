@@ -47,7 +47,7 @@ def test_chunk_epilogue(rp, orc, N, k, prec):
         check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"multi N={N} k={k} rhs {j} prec={prec}")
 
 
-@pytest.mark.parametrize("N", [512, 513, 1500, 1985, 4033, 5000, 33000])
+@pytest.mark.parametrize("N", [1, 2, 64, 65, 300, 511, 512, 513, 1500, 1985, 4033, 5000, 33000])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_vjp_splits(rp, orc, N, prec):
     """FP64 passes split 16, 8 and 4 ways and not at all, records formed by the
