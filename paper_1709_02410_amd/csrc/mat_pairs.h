@@ -198,16 +198,20 @@ struct MatLane {
 };
 
 // Block b -> (source chunk b % splits, targets [64 (b / splits), +64)); the
-// partial sums go to the same layout as pair_kernel's.
+// partial sums go to the same layout as pair_kernel's.  Small problems share
+// each chunk out over `sub` workgroups, at multiples of the tile (so that every
+// tile's FP32 sums are those of the undivided chunk).
 template <typename R, int K>
 __global__ __launch_bounds__(kBlock) void mat_pair_kernel(const R* __restrict__ rec, int64_t N, int splits,
-                                                          int64_t chunk, double* __restrict__ part) {
+                                                          int64_t chunk, int sub, int sublen,
+                                                          double* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) R tile[mat_tile<R>() * rec_w<R, K>()];
     const int b = blockIdx.x;
     const int split = b % splits;
     const int64_t first = (int64_t)(b / splits) * kMatTargets;
-    const int64_t s0 = (int64_t)split * chunk;
-    const int64_t s1 = s0 + chunk < N ? s0 + chunk : N;
+    const int64_t c0 = (int64_t)(split / sub) * chunk, c1 = c0 + chunk < N ? c0 + chunk : N;
+    const int64_t s0 = c0 + (int64_t)(split % sub) * sublen;  // past c1: no sources, zero sums
+    const int64_t s1 = s0 + sublen < c1 ? s0 + sublen : c1;
     MatLane<R, K> L;
     L.load(rec, first, N);
     L.run(rec, s0, s1, tile);

@@ -66,41 +66,65 @@ struct Lane {
         }
     }
 
+    // S consecutive sources from the tile, which share one overlap branch so
+    // that their arithmetic interleaves; the target's sums take them in order.
+    template <int S>
+    __device__ __forceinline__ void sources(const R* s) {
+        constexpr int RW = rec_w<R, K>(), PW = pos_slots<R>();
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) {
+            R dx[S], dy[S], dz[S];
+            PairPre<R> p[S];
+            bool near = false;
+#pragma unroll
+            for (int i = 0; i < S; ++i) {
+                const R* r = s + i * RW;
+                dx[i] = x[t] - r[0];
+                dy[i] = y[t] - r[1];
+                if constexpr (sizeof(R) == 4) {
+                    dx[i] += xl[t] - r[3];
+                    dy[i] += yl[t] - r[4];
+                }
+                dz[i] = z[t] - r[2];
+                p[i] = pair_pre<R>(dx[i], dy[i], dz[i], z[t], r[2]);
+                near |= pair_near(p[i]);
+            }
+            if (__builtin_amdgcn_ballot_w64(near)) {
+                __asm__ volatile("" ::: "memory");  // keep this a branch: do not speculate it
+#pragma unroll
+                for (int i = 0; i < S; ++i) pair_fix(p[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < S; ++i) {
+                const PairCoef<R> c = pair_fin(p[i]);
+                const R* f = s + i * RW + PW;
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    pair_apply<R>(c, dx[i], dy[i], dz[i], f[3 * k], f[3 * k + 1], f[3 * k + 2], acc[t][k][0],
+                                  acc[t][k][1], acc[t][k][2]);
+            }
+        }
+    }
+
+    // Sources taken together.  FP32C, 2 and 4 right-hand sides: 23.1 -> 21.0 and
+    // 30.2 -> 26.4 us a call at 1000 blobs, 2.52 -> 2.50 and 3.43 -> 3.38 ms at
+    // 40000; four at a time are slower from 3000 blobs on (registers).
+    static constexpr int SRC = sizeof(R) == 4 && TPL == 1 ? 2 : 1;
+
     // Sum over sources [s0, s1) staged through the LDS tile.
     template <int TILE>
     __device__ void run(const R* __restrict__ rec, int64_t s0, int64_t s1, R* tile) {
         constexpr int RW = rec_w<R, K>();
-        constexpr int PW = pos_slots<R>();
         for (int64_t t0 = s0; t0 < s1; t0 += TILE) {
             const int n = (int)((s1 - t0) < TILE ? (s1 - t0) : TILE);
             __syncthreads();
             const R* g = rec + t0 * RW;
             for (int e = threadIdx.x; e < n * RW; e += kBlock) tile[e] = g[e];
             __syncthreads();
-#pragma unroll 2
-            for (int j = 0; j < n; ++j) {
-                const R* s = tile + j * RW;
-                const R sx = s[0], sy = s[1], sz = s[2];
-                R sxl = R(0), syl = R(0);
-                if constexpr (sizeof(R) == 4) {
-                    sxl = s[3];
-                    syl = s[4];
-                }
-#pragma unroll
-                for (int t = 0; t < TPL; ++t) {
-                    R dx = x[t] - sx, dy = y[t] - sy;
-                    if constexpr (sizeof(R) == 4) {
-                        dx += xl[t] - sxl;
-                        dy += yl[t] - syl;
-                    }
-                    const R dz = z[t] - sz;
-                    const PairCoef<R> p = pair_coef<R>(dx, dy, dz, z[t], sz);
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        pair_apply<R>(p, dx, dy, dz, s[PW + 3 * k], s[PW + 3 * k + 1], s[PW + 3 * k + 2],
-                                      acc[t][k][0], acc[t][k][1], acc[t][k][2]);
-                }
-            }
+            int j = 0;
+            for (; j + SRC <= n; j += SRC) sources<SRC>(tile + j * RW);
+            if constexpr (SRC > 1)
+                for (; j < n; ++j) sources<1>(tile + j * RW);
             if constexpr (sizeof(R) == 4) {
 #pragma unroll
                 for (int t = 0; t < TPL; ++t)
@@ -478,11 +502,18 @@ hipError_t launch_batched_t(const R* rec, const int4* items, int n_items, unsign
     return hipGetLastError();
 }
 
+// Source chunks of the matrix-core kernel, each shared out over sub workgroups
+// of sublen sources; splits counts the shares.
+struct MatSplit {
+    int splits, sub, sublen;
+    int64_t chunk;
+};
+
 template <typename R, int K>
-hipError_t launch_mat_t(const void* rec, int64_t N, int splits, int64_t chunk, double* part, int64_t nblocks,
+hipError_t launch_mat_t(const void* rec, int64_t N, const MatSplit& ms, double* part, int64_t nblocks,
                         hipStream_t st) {
-    hipLaunchKernelGGL((mat_pair_kernel<R, K>), dim3((unsigned)nblocks), dim3(kBlock), 0, st, (const R*)rec, N, splits,
-                       chunk, part);
+    hipLaunchKernelGGL((mat_pair_kernel<R, K>), dim3((unsigned)nblocks), dim3(kBlock), 0, st, (const R*)rec, N,
+                       ms.splits, ms.chunk, ms.sub, ms.sublen, part);
     return hipGetLastError();
 }
 
@@ -496,13 +527,13 @@ hipError_t launch_mat_batched_t(const void* rec, const int4* items, int n_items,
 }
 
 // The matrix-core launches for a precision and a block of 8 or 16.
-hipError_t launch_mat(int prec, int K, const void* rec, int64_t N, int splits, int64_t chunk, double* part,
+hipError_t launch_mat(int prec, int K, const void* rec, int64_t N, const MatSplit& ms, double* part,
                       int64_t nblocks, hipStream_t st) {
     if (prec == RPYW_FP32C)
-        return K == 16 ? launch_mat_t<float, 16>(rec, N, splits, chunk, part, nblocks, st)
-                       : launch_mat_t<float, 8>(rec, N, splits, chunk, part, nblocks, st);
-    return K == 16 ? launch_mat_t<double, 16>(rec, N, splits, chunk, part, nblocks, st)
-                   : launch_mat_t<double, 8>(rec, N, splits, chunk, part, nblocks, st);
+        return K == 16 ? launch_mat_t<float, 16>(rec, N, ms, part, nblocks, st)
+                       : launch_mat_t<float, 8>(rec, N, ms, part, nblocks, st);
+    return K == 16 ? launch_mat_t<double, 16>(rec, N, ms, part, nblocks, st)
+                   : launch_mat_t<double, 8>(rec, N, ms, part, nblocks, st);
 }
 
 hipError_t launch_mat_batched(int prec, int K, const void* rec, const int4* items, int n_items, unsigned* counter,
@@ -648,7 +679,13 @@ void split_plan(int64_t N, int tpl, int* splits, int64_t* chunk) {
 // Source chunks of the matrix-core kernel: workgroups of 64 targets, enough
 // of them for several rounds of five per CU (the tail of the last round
 // then costs little), chunks of at least 256 sources.
-void mat_split_plan(int64_t N, int* splits, int64_t* chunk) {
+// Chunks are shared out at multiples of the LDS tile while that makes kMatWgs
+// workgroups or fewer (as many as run at a time): until then the kernel is bound
+// by the chain of a wave's steps, 0.7 us for 4 sources.  FP32C, 16 right-hand
+// sides, a call: 300 blobs 53.9 -> 29.5 us, 1000 blobs 59.1 -> 31.0; sharing
+// further lost at 3000 (68 -> 77).
+constexpr int64_t kMatWgs = 1280;
+MatSplit mat_split_plan(int64_t N, int prec) {
     const int64_t ntb = (N + kMatTargets - 1) / kMatTargets;
     const int64_t want_wg = 8192;
     int64_t s = (want_wg + ntb - 1) / ntb;
@@ -656,10 +693,16 @@ void mat_split_plan(int64_t N, int* splits, int64_t* chunk) {
     if (s > max_s) s = max_s;
     if (s > 8) s = (s + 7) / 8 * 8;
     if (s < 1) s = 1;
-    int64_t c = (N + s - 1) / s;
-    s = (N + c - 1) / c;
-    *splits = (int)s;
-    *chunk = c;
+    MatSplit m;
+    m.chunk = (N + s - 1) / s;
+    s = (N + m.chunk - 1) / m.chunk;
+    const int tile = prec == RPYW_FP32C ? mat_tile<float>() : mat_tile<double>();
+    const int64_t tiles = (m.chunk + tile - 1) / tile;
+    const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(tiles, kMatWgs / (ntb * s)));
+    m.sublen = (int)((tiles + fit - 1) / fit) * tile;
+    m.sub = (int)((m.chunk + m.sublen - 1) / m.sublen);
+    m.splits = (int)s * m.sub;
+    return m;
 }
 
 size_t product_ws_bytes(int64_t N, int prec, int kblk) {
@@ -667,7 +710,7 @@ size_t product_ws_bytes(int64_t N, int prec, int kblk) {
     int64_t c;
     split_plan(N, 1, &s1, &c);
     split_plan(N, 2, &s2, &c);
-    if (kblk >= 8) mat_split_plan(N, &s3, &c);
+    if (kblk >= 8) s3 = mat_split_plan(N, prec).splits;
     const int smax = std::max(std::max(s1, s2), s3);
     size_t b = align_up((size_t)N * rec_width(prec, kblk) * real_size(prec));
     b += align_up((size_t)N * sizeof(double));
@@ -802,10 +845,13 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     double* B = (double*)ar.take((size_t)N * sizeof(double));
     int splits;
     int64_t chunk;
-    if (sh.mat)
-        mat_split_plan(N, &splits, &chunk);
-    else
+    MatSplit ms{};
+    if (sh.mat) {
+        ms = mat_split_plan(N, prec);
+        splits = ms.splits;
+    } else {
         split_plan(N, sh.tpl, &splits, &chunk);
+    }
     double* part = (double*)ar.take((size_t)splits * K * 3 * N * sizeof(double));
     if (!rec || !B || !part) {
         ar.used = mark;
@@ -826,7 +872,7 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     profile_begin(st, &ev);
     hipError_t e;
     if (sh.mat)
-        e = launch_mat(prec, K, rec, N, splits, chunk, part, nblocks, st);
+        e = launch_mat(prec, K, rec, N, ms, part, nblocks, st);
     else if (prec == RPYW_FP32C)
         e = RPYW_DISPATCH(float, K, sh.tpl, sh.tile, launch_pair_t, (const float*)rec, N, splits, chunk, part, nblocks,
                           st);

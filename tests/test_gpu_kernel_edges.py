@@ -182,3 +182,20 @@ def test_tail_chunks(rp, N, prec):
     for ipw, r in zip((2, 3, 6), runs[1:]):
         for x, ref, what in zip(r, runs[0], ("u", "grad_pos", "grad_f")):
             check(x, ref, 1e-12, f"{what} N={N} prec={prec} ipw={ipw}")
+
+
+@pytest.mark.parametrize("N", [1, 3, 127, 129, 300, 1000, 1300])
+@pytest.mark.parametrize("prec,k", [(1, 1), (1, 3), (1, 8), (1, 13), (0, 12)])
+def test_small_plain_products(rp, orc, N, prec, k):
+    """Plain and matrix-core kernels of small problems: odd numbers of sources
+    (two are taken at a time), chunks shared out at tiles with remainders, and
+    shares without sources."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + k).standard_normal((k, N, 3))
+    rp.set_shape(prec, N, k, tpl=1, tile=64, kblk={1: 1, 3: 4, 8: 8}.get(k, 16), sym=0, mat=1 if k >= 8 else 0)
+    try:
+        U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=prec).cpu().numpy()
+    finally:
+        rp.reset_shape(prec, N, k)
+    for j in {0, k // 2, k - 1}:
+        check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"plain N={N} k={k} rhs {j} prec={prec}")
