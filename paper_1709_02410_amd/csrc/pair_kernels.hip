@@ -509,6 +509,31 @@ struct MatSplit {
     int64_t chunk;
 };
 
+// Records of the plain, matrix-core and batched kernels (open domain).
+template <typename R>
+hipError_t launch_pack_t(int K, const double* pos, const double* F, int64_t N, int kb, double a, R* rec, double* B,
+                         hipStream_t st) {
+    auto rows = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((N + kPackBlobs - 1) / kPackBlobs)), dim3(256), 0, st, pos, F, N, kb,
+                           1.0 / a, rec, B);
+    };
+    if (K == 16)
+        rows(pack_rows_kernel<R, 16>);
+    else if (K == 8)
+        rows(pack_rows_kernel<R, 8>);
+    else if (K == 4)
+        rows(pack_rows_kernel<R, 4>);
+    else
+        hipLaunchKernelGGL(pack_kernel<R>, dim3((unsigned)((N + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, pos, F, N,
+                           kb, K == 2 ? rec_w<R, 2>() : rec_w<R, 1>(), 1.0 / a, rec, B, nullptr, 0.0, 0.0, N);
+    return hipGetLastError();
+}
+hipError_t launch_pack(int prec, int K, const double* pos, const double* F, int64_t N, int kb, double a, void* rec,
+                       double* B, hipStream_t st) {
+    return prec == RPYW_FP32C ? launch_pack_t<float>(K, pos, F, N, kb, a, (float*)rec, B, st)
+                              : launch_pack_t<double>(K, pos, F, N, kb, a, (double*)rec, B, st);
+}
+
 template <typename R, int K>
 hipError_t launch_mat_t(const void* rec, int64_t N, const MatSplit& ms, double* part, int64_t nblocks,
                         hipStream_t st) {
@@ -857,14 +882,7 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
         ar.used = mark;
         return RPYW_ENOMEM;
     }
-    const unsigned g1 = (unsigned)((N + kBlock - 1) / kBlock);
-    if (prec == RPYW_FP32C)
-        hipLaunchKernelGGL(pack_kernel<float>, dim3(g1), dim3(kBlock), 0, st, pos, F, N, kb, rw, 1.0 / a, (float*)rec,
-                           B, nullptr, 0.0, 0.0, N);
-    else
-        hipLaunchKernelGGL(pack_kernel<double>, dim3(g1), dim3(kBlock), 0, st, pos, F, N, kb, rw, 1.0 / a,
-                           (double*)rec, B, nullptr, 0.0, 0.0, N);
-    RPYW_HIP(hipGetLastError());
+    RPYW_HIP(launch_pack(prec, K, pos, F, N, kb, a, rec, B, st));
     const int span = sh.mat ? kMatTargets : kBlock * sh.tpl;
     const int64_t ntb = (N + span - 1) / span;
     const int64_t nblocks = ntb * splits;
@@ -1005,7 +1023,6 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     RPYW_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     const int per_cu = sh.mat ? (prec == RPYW_FP32C ? mat_batched_waves<float>() : mat_batched_waves<double>()) : 4;
     const int grid = (int)std::min<size_t>(items.size(), (size_t)ncu * per_cu);
-    const unsigned g1 = (unsigned)((Ntot + kBlock - 1) / kBlock);
     const double m0 = mu0_of(a, eta);
     double pairs = 0.0;
     for (int s = 0; s < S; ++s) {
@@ -1016,13 +1033,7 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
         const int kb = std::min(sh.kblk, k - k0);
         const double* Fk = F + (size_t)k0 * Ntot * 3;
         double* Uk = U + (size_t)k0 * Ntot * 3;
-        if (prec == RPYW_FP32C)
-            hipLaunchKernelGGL(pack_kernel<float>, dim3(g1), dim3(kBlock), 0, st, pos, Fk, Ntot, kb, rw, 1.0 / a,
-                               (float*)rec, B, nullptr, 0.0, 0.0, Ntot);
-        else
-            hipLaunchKernelGGL(pack_kernel<double>, dim3(g1), dim3(kBlock), 0, st, pos, Fk, Ntot, kb, rw, 1.0 / a,
-                               (double*)rec, B, nullptr, 0.0, 0.0, Ntot);
-        RPYW_HIP(hipGetLastError());
+        RPYW_HIP(launch_pack(prec, K, pos, Fk, Ntot, kb, a, rec, B, st));
         hipLaunchKernelGGL(zero_u32, dim3(1), dim3(1), 0, st, counter);
         RPYW_HIP(hipGetLastError());
         hipEvent_t ev = nullptr;
