@@ -23,6 +23,7 @@
 // into a pinned slot, where the host polls it.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "krylov_step.h"
@@ -38,7 +39,8 @@ using namespace kstep;
 constexpr int kPreThreads = 256;  // at least 3 kMaxBodyBlobs + 6 (one thread per entry)
 constexpr int kOutThreads = 256;
 constexpr int kMaxN3 = 3 * kMaxBodyBlobs;
-constexpr int kPreReg = 16;  // basis values a thread of pre keeps in registers
+constexpr int kPreReg = 16;      // basis values a thread of pre keeps in registers
+constexpr int kFewVectors = 16;  // basis vectors up to which out has a lighter form
 constexpr int kRhsThreads = 256;
 
 // pre, like the Lanczos vin, is bound by its chain of dependent round trips:
@@ -298,9 +300,11 @@ __global__ __launch_bounds__(kPreThreads) void rg_fin_kernel(const double* __res
 }
 
 // out reads the product's partials (latency-bound); its dot products are folded
-// together four at a time (wave_fold): 31 us against 36 a step on 1024 bodies
-// of 12 blobs.
-template <typename R>
+// together four at a time (wave_fold).  A wave keeps KJ vectors' values in
+// registers: sixteen take 174 of them, two workgroups to a compute unit; four,
+// for up to 16 vectors, halve that: 8.6 -> 4.9 us a step on 1024 bodies of 12
+// blobs, 8.3 -> 7.5 on 256 of 15.
+template <typename R, int KJ>
 __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     const double* __restrict__ pos, const double* __restrict__ q, const int* __restrict__ bofs,
     const double* __restrict__ tpart, const R* __restrict__ spart, int ng, int C, int Hmax, int nseg, int G,
@@ -338,10 +342,9 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     // j = wave (mod kWaves), lanes the entries l, l + 64, l + 128
     const int wv = wave_uniform(t >> 6), l = t & 63;
     auto gidx = [&](int i) -> int64_t { return i < n ? e0 + i : n3 + 6 * (int64_t)p + (i - n); };
-    constexpr int kJ = 64 / kWaves;  // vectors per wave held in registers (j < 64)
-    double av[kJ][kSlots];
+    double av[KJ][kSlots];
 #pragma unroll
-    for (int i = 0; i < kJ; ++i) {
+    for (int i = 0; i < KJ; ++i) {
         const int j = wv + kWaves * i;
 #pragma unroll
         for (int s = 0; s < kSlots; ++s) {
@@ -403,7 +406,7 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
     for (int s = 0; s < kSlots; ++s) wv3[s] = l + 64 * s < ne ? wl[l + 64 * s] : 0.0;
     // the wave's dot products, four vectors folded together at a time
 #pragma unroll
-    for (int i0 = 0; i0 < kJ; i0 += 4) {
+    for (int i0 = 0; i0 < KJ; i0 += 4) {
         if (kWaves * i0 > k) break;  // uniform
         double pr[4];
 #pragma unroll
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(kOutThreads) void rg_out_kernel(
         const int j = wv + kWaves * (i0 + wave_value<4>(l));
         if (l % 16 == 0 && j <= k) part1[(int64_t)j * nbodies + p] = pr[0];
     }
-    for (int j = wv + 64; j <= k; j += kWaves) {  // beyond the vectors held in registers
+    for (int j = wv + kWaves * KJ; j <= k; j += kWaves) {  // beyond the vectors held in registers
         double s = 0.0;
 #pragma unroll
         for (int c = 0; c < kSlots; ++c) {
@@ -479,14 +482,21 @@ int rg_launch_out(int prec, const double* pos, const double* q, const int* bofs,
                   const void* spart, const SymPlan& sp, const double* B, double mu0, const double* zl,
                   const double* zu, int64_t n3, int64_t ld, const double* V, int k, double* w, double* part1,
                   const double* ypre, hipStream_t st) {
+    auto go = [&](auto kernel, auto* sp_) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n_bodies), dim3(kOutThreads), 0, st, pos, q, bofs, tpart, sp_, sp.ng,
+                           sp.C, sp.Hmax, sp.nseg, sp.G, B, mu0, zl, zu, n3, ld, V, k, w, part1, n_bodies, ypre);
+    };
+    auto pick = [&](auto* s) {
+        using R = std::remove_const_t<std::remove_pointer_t<decltype(s)>>;
+        if (k < kFewVectors)
+            go(rg_out_kernel<R, 4>, s);
+        else
+            go(rg_out_kernel<R, 16>, s);
+    };
     if (prec == RPYW_FP32C)
-        hipLaunchKernelGGL(rg_out_kernel<float>, dim3((unsigned)n_bodies), dim3(kOutThreads), 0, st, pos, q, bofs,
-                           tpart, (const float*)spart, sp.ng, sp.C, sp.Hmax, sp.nseg, sp.G, B, mu0, zl, zu, n3, ld, V,
-                           k, w, part1, n_bodies, ypre);
+        pick((const float*)spart);
     else
-        hipLaunchKernelGGL(rg_out_kernel<double>, dim3((unsigned)n_bodies), dim3(kOutThreads), 0, st, pos, q, bofs,
-                           tpart, (const double*)spart, sp.ng, sp.C, sp.Hmax, sp.nseg, sp.G, B, mu0, zl, zu, n3, ld,
-                           V, k, w, part1, n_bodies, ypre);
+        pick((const double*)spart);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;
 }
