@@ -520,10 +520,14 @@ __global__ __launch_bounds__(kVinThreads) void lz_fin_kernel(int diag, const int
 
 bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom, SymPlan* sp) {
     if (max_iter > kLanczosFusedMaxIter) return false;
-    // the symmetric plan of products of one right-hand side
+    // The symmetric plan of products of one right-hand side.  Where single
+    // products take one launch (small FP64 ones) the steps take it as well, also
+    // below the sizes of symmetric products: their vector work is fused with it
+    // (rigid solves of 60 to 500 blobs 175 -> 120 us, roots 768 -> 494 us at 60
+    // and 1593 -> 998 us at 500).
     const Shape sh = tuned_shape(N, 1, prec);
-    if (!dom.periodic() && !(sh.sym && sh.kblk <= 4)) return false;
-    *sp = sym_choose(N, prec, 1, sh.ipw < 1 ? 4 : sh.ipw, sh.sym, dom);
+    if (!dom.periodic() && !(sh.sym && sh.kblk <= 4) && !sh.direct) return false;
+    *sp = sym_choose(N, prec, 1, sh.ipw < 1 ? 4 : sh.ipw, sh.sym || !sh.direct ? sh.sym : 2, dom);
     return sp->ok;
 }
 

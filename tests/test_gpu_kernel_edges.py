@@ -199,3 +199,22 @@ def test_small_plain_products(rp, orc, N, prec, k):
         rp.reset_shape(prec, N, k)
     for j in {0, k // 2, k - 1}:
         check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"plain N={N} k={k} rhs {j} prec={prec}")
+
+
+@pytest.mark.parametrize("blobs,bodies", [(3, 1), (4, 1), (5, 12), (7, 9), (15, 34)])
+def test_small_krylov_steps(rp, orc, blobs, bodies):
+    """Fused FP64 steps of problems below 512 blobs (default shape), down to
+    one body in one group.  Bars: as for the vector kernels."""
+    from paper_1709_02410_amd import workloads as wl
+    N = blobs * bodies
+    side = (2.8 * N) ** (1 / 3)
+    pos = np.random.default_rng(N).uniform(0, side, (N, 3)) + [0, 0, 0.6]
+    offs = np.arange(0, N + 1, blobs)
+    W, q = wl.gaussian(pos.shape, blobs), pos[offs[:-1]]
+    root, _, _, ok = rp.lanczos_sqrt(_t(pos), _t(W), body_offsets=offs, tol=1e-12, max_iter=250)
+    free, _, _, ok1 = rp.lanczos_sqrt(_t(pos), _t(W), tol=1e-12, max_iter=250)
+    _, U, _, _, ok2 = rp.rigid_solve(_t(pos), _t(q), offs, _t(W), None, tol=1e-12, max_iter=250)
+    assert ok and ok1 and ok2
+    check(root.cpu().numpy(), orc.dense_sqrt(pos, W, offs), 1e-9, f"root {blobs}x{bodies}")
+    check(free.cpu().numpy(), orc.dense_sqrt(pos, W, None), 1e-9, f"root without bodies N={N}")
+    check(U.cpu().numpy(), orc.rigid_solve(pos, q, offs, W, None)[1], 1e-7, f"U {blobs}x{bodies}")
