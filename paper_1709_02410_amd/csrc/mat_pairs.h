@@ -226,6 +226,14 @@ __global__ __launch_bounds__(kBlock) void mat_pair_kernel(const R* __restrict__ 
     }
 }
 
+// Sources of a batched item {sys_begin, sys_end, target_begin, part}: part of
+// `parts` shares of whole tiles of its system (past its end: none).
+__device__ __forceinline__ int2 part_sources(const int4& it, int parts, int tile) {
+    const int tiles = (it.y - it.x + tile - 1) / tile, len = (tiles + parts - 1) / parts * tile;
+    const int s0 = it.x + it.w * len;
+    return make_int2(s0, s0 + len < it.y ? s0 + len : it.y);
+}
+
 // Batched systems on the matrix cores: as batched_kernel, with work items of
 // 64 targets; five resident workgroups per CU in FP32 (the register bound
 // keeps the item loop's extra registers within five waves per SIMD), four in
@@ -239,7 +247,8 @@ __global__ __launch_bounds__(kBlock, mat_batched_waves<R>()) void mat_batched_ke
                                                              const int4* __restrict__ items, int n_items,
                                                              unsigned* __restrict__ counter,
                                                              const double* __restrict__ B, double mu0, int64_t Ntot,
-                                                             int kb, double* __restrict__ U) {
+                                                             int kb, double* __restrict__ U, int parts,
+                                                             double* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) R tile[mat_tile<R>() * rec_w<R, K>()];
     __shared__ int s_item;
     for (;;) {
@@ -251,8 +260,20 @@ __global__ __launch_bounds__(kBlock, mat_batched_waves<R>()) void mat_batched_ke
         const int4 it = items[item];
         MatLane<R, K> L;
         L.load(rec, it.z, it.y);
-        L.run(rec, it.x, it.y, tile);
+        const int2 src = part_sources(it, parts, mat_tile<R>());
+        L.run(rec, src.x, src.y, tile);
         const int k = MatLane<R, K>::rhs();
+        if (parts > 1) {
+            if (k < K)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t i = (int64_t)it.z + MatLane<R, K>::target(v);
+                    if (i >= it.y) continue;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) part[((int64_t)(it.w * K + k) * 3 + c) * Ntot + i] = L.total(c, v);
+                }
+            continue;
+        }
         if (k >= kb) continue;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {

@@ -203,13 +203,17 @@ __global__ __launch_bounds__(64 * kEpiParts) void epilogue_kernel(const double* 
 }
 
 // Batched systems: persistent workgroups take items {sys_begin, sys_end,
-// target_begin} from an atomic counter; every item covers all sources of its
-// system and writes final velocities.
+// target_begin, part} from an atomic counter.  With one part an item covers all
+// sources of its system and writes final velocities; with more (few items, see
+// batched_parts) it covers its share of them, at multiples of the tile (the
+// FP32 sums of a tile are the same), and writes partial sums in the layout of
+// pair_kernel's, which epilogue_kernel adds up.
 template <typename R, int K, int TPL, int TILE>
 __global__ __launch_bounds__(kBlock) void batched_kernel(const R* __restrict__ rec, const int4* __restrict__ items,
                                                          int n_items, unsigned* __restrict__ counter,
                                                          const double* __restrict__ B, double mu0, int64_t Ntot,
-                                                         int kb, double* __restrict__ U) {
+                                                         int kb, double* __restrict__ U, int parts,
+                                                         double* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) R tile[TILE * rec_w<R, K>()];
     __shared__ int s_item;
     for (;;) {
@@ -221,11 +225,20 @@ __global__ __launch_bounds__(kBlock) void batched_kernel(const R* __restrict__ r
         const int4 it = items[item];
         Lane<R, K, TPL> L;
         L.load(rec, it.z, it.y, threadIdx.x);
-        L.template run<TILE>(rec, it.x, it.y, tile);
+        const int2 src = part_sources(it, parts, TILE);
+        L.template run<TILE>(rec, src.x, src.y, tile);
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
             const int64_t i = (int64_t)it.z + (int64_t)t * kBlock + threadIdx.x;
             if (i >= it.y) continue;
+            if (parts > 1) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        part[((int64_t)(it.w * K + k) * 3 + c) * Ntot + i] = L.total(t, k, c);
+                continue;
+            }
             const double sc = mu0 * B[i];
 #pragma unroll
             for (int k = 0; k < K; ++k)
@@ -496,9 +509,10 @@ hipError_t launch_pair_t(const R* rec, int64_t N, int splits, int64_t chunk, dou
 
 template <typename R, int K, int TPL, int TILE>
 hipError_t launch_batched_t(const R* rec, const int4* items, int n_items, unsigned* counter, const double* B,
-                            double mu0, int64_t Ntot, int kb, double* U, int grid, hipStream_t st) {
+                            double mu0, int64_t Ntot, int kb, double* U, int parts, double* part, int grid,
+                            hipStream_t st) {
     hipLaunchKernelGGL((batched_kernel<R, K, TPL, TILE>), dim3(grid), dim3(kBlock), 0, st, rec, items, n_items,
-                       counter, B, mu0, Ntot, kb, U);
+                       counter, B, mu0, Ntot, kb, U, parts, part);
     return hipGetLastError();
 }
 
@@ -544,10 +558,11 @@ hipError_t launch_mat_t(const void* rec, int64_t N, const MatSplit& ms, double* 
 
 template <typename R, int K>
 hipError_t launch_mat_batched_t(const void* rec, const int4* items, int n_items, unsigned* counter,
-                                const double* B, double mu0, int64_t Ntot, int kb, double* U, int grid,
+                                const double* B, double mu0, int64_t Ntot, int kb, double* U, int parts,
+                                double* part, int grid,
                                 hipStream_t st) {
     hipLaunchKernelGGL((mat_batched_kernel<R, K>), dim3(grid), dim3(kBlock), 0, st, (const R*)rec, items, n_items,
-                       counter, B, mu0, Ntot, kb, U);
+                       counter, B, mu0, Ntot, kb, U, parts, part);
     return hipGetLastError();
 }
 
@@ -562,13 +577,14 @@ hipError_t launch_mat(int prec, int K, const void* rec, int64_t N, const MatSpli
 }
 
 hipError_t launch_mat_batched(int prec, int K, const void* rec, const int4* items, int n_items, unsigned* counter,
-                              const double* B, double mu0, int64_t Ntot, int kb, double* U, int grid,
+                              const double* B, double mu0, int64_t Ntot, int kb, double* U, int parts, double* part,
+                              int grid,
                               hipStream_t st) {
     if (prec == RPYW_FP32C)
-        return K == 16 ? launch_mat_batched_t<float, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, grid, st)
-                       : launch_mat_batched_t<float, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, grid, st);
-    return K == 16 ? launch_mat_batched_t<double, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, grid, st)
-                   : launch_mat_batched_t<double, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, grid, st);
+        return K == 16 ? launch_mat_batched_t<float, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st)
+                       : launch_mat_batched_t<float, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st);
+    return K == 16 ? launch_mat_batched_t<double, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st)
+                   : launch_mat_batched_t<double, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st);
 }
 
 // Expand (K, TPL, TILE) runtime values into template instantiations.
@@ -968,12 +984,34 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
 
 // ------------------------------------------------------------ batched
 
+// Parts into which the sources of every system are split, so that there are
+// about kBatchedItems items of work: 1024 to 1280 run at a time, and the large
+// systems' items are long (few or small systems are a serial pass over all
+// sources on a few workgroups; many end unevenly).  A call, before and now: two
+// systems of up to 5000 blobs, FP32C, 80 -> 30 us; 14 of up to 11000, 8
+// right-hand sides, FP64, 4.9 -> 2.4 ms; 64 of up to 12000, 4 right-hand sides,
+// FP64, 5.7 -> 3.4 ms; 64 of up to 17000, 16 right-hand sides, FP32C, 11.1 ->
+// 10.9 ms.  Twice as many items lose up to 12%.
+constexpr int64_t kBatchedItems = 8192;
+int batched_parts(int64_t Ntot, bool mat) {
+    const int64_t items = Ntot / (mat ? kMatTargets : kBlock) + 1;
+    // (rounded down where the partial sums of a part are the larger: span 256)
+    return (int)std::max<int64_t>(1, std::min<int64_t>(64, (kBatchedItems + (mat ? items - 1 : 0)) / items));
+}
+
 size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec) {
     const int kb = kernel_k(std::max(k, 1), prec, 1);  // the widest the batched kernels take
     size_t b = align_up((size_t)Ntot * rec_width(prec, kb) * real_size(prec));
     b += align_up((size_t)Ntot * sizeof(double));
     const size_t max_items = (size_t)(Ntot / kMatTargets) + (size_t)S + 1;  // items of 64 or more targets
-    b += align_up(max_items * sizeof(int4));
+    size_t items = max_items, part = 0;
+    for (int K = 1; K <= kb; K <<= 1) {
+        const int p = std::max(batched_parts(Ntot, false), K >= 8 ? batched_parts(Ntot, true) : 1);
+        if (p > 1) part = std::max(part, (size_t)p * K * 3 * Ntot * sizeof(double));
+    }
+    items = std::max(items, ((size_t)(Ntot / kBlock) + S + 1) * batched_parts(Ntot, false));
+    items = std::max(items, max_items * batched_parts(Ntot, true));
+    b += align_up(items * sizeof(int4)) + align_up(part);
     b += kAlign;  // counter
     return b + 4 * kAlign;
 }
@@ -999,10 +1037,14 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
         return sys_offsets[x + 1] - sys_offsets[x] > sys_offsets[y + 1] - sys_offsets[y];
     });
     const int span = sh.mat ? kMatTargets : kBlock * sh.tpl;
+    const int tile = !sh.mat ? (sh.tile == 64 ? 64 : 256)
+                     : prec == RPYW_FP32C ? mat_tile<float>() : mat_tile<double>();
+    const int parts = (int)std::min<int64_t>(batched_parts(Ntot, sh.mat), (nmax + tile - 1) / tile);
     std::vector<int4> items;
     for (int s : order) {
         const int b0 = (int)sys_offsets[s], b1 = (int)sys_offsets[s + 1];
-        for (int t = b0; t < b1; t += span) items.push_back(make_int4(b0, b1, t, 0));
+        for (int p = 0; p < parts; ++p)
+            for (int t = b0; t < b1; t += span) items.push_back(make_int4(b0, b1, t, p));
     }
     const size_t mark = ar.used;
     const int K = kernel_k(sh.kblk, prec, sh.mat);
@@ -1012,7 +1054,8 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     double* B = (double*)ar.take((size_t)Ntot * sizeof(double));
     int4* ditems = (int4*)ar.take(items.size() * sizeof(int4));
     unsigned* counter = (unsigned*)ar.take(sizeof(unsigned));
-    if (!rec || !B || !ditems || !counter) {
+    double* part = parts > 1 ? (double*)ar.take((size_t)parts * K * 3 * Ntot * sizeof(double)) : nullptr;
+    if (!rec || !B || !ditems || !counter || (parts > 1 && !part)) {
         ar.used = mark;
         return RPYW_ENOMEM;
     }
@@ -1040,15 +1083,23 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
         profile_begin(st, &ev);
         hipError_t e;
         if (sh.mat)
-            e = launch_mat_batched(prec, K, rec, ditems, (int)items.size(), counter, B, m0, Ntot, kb, Uk, grid, st);
+            e = launch_mat_batched(prec, K, rec, ditems, (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+                                   grid, st);
         else if (prec == RPYW_FP32C)
             e = RPYW_DISPATCH(float, K, sh.tpl, sh.tile, launch_batched_t, (const float*)rec, ditems,
-                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, grid, st);
+                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+                                   grid, st);
         else
             e = RPYW_DISPATCH(double, K, sh.tpl, sh.tile, launch_batched_t, (const double*)rec, ditems,
-                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, grid, st);
+                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+                                   grid, st);
         if (e != hipSuccess) return RPYW_EHIP;
         profile_end(st, ev, kb * pairs);
+        if (parts > 1) {
+            hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)((Ntot + 63) / 64), (unsigned)(3 * kb)),
+                               dim3(64 * kEpiParts), 0, st, part, B, Ntot, K, parts, m0, Uk);
+            RPYW_HIP(hipGetLastError());
+        }
     }
     ar.used = mark;
     return RPYW_OK;

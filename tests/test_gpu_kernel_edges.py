@@ -218,3 +218,19 @@ def test_small_krylov_steps(rp, orc, blobs, bodies):
     check(root.cpu().numpy(), orc.dense_sqrt(pos, W, offs), 1e-9, f"root {blobs}x{bodies}")
     check(free.cpu().numpy(), orc.dense_sqrt(pos, W, None), 1e-9, f"root without bodies N={N}")
     check(U.cpu().numpy(), orc.rigid_solve(pos, q, offs, W, None)[1], 1e-7, f"U {blobs}x{bodies}")
+
+
+@pytest.mark.parametrize("sizes", [(1,), (3, 700), (513, 64, 1, 2000, 129), (1500, 1400)])
+@pytest.mark.parametrize("prec,k", [(1, 1), (1, 3), (1, 16), (0, 1), (0, 8), (0, 16)])
+def test_batched_parts(rp, orc, sizes, prec, k):
+    """Batched systems whose sources are split into parts: more parts than a
+    small system has tiles, a last tile of one blob, one part (one blob)."""
+    offs = np.r_[0, np.cumsum(sizes)]
+    pos = np.concatenate([0.9 * _mixed(n, n) for n in sizes])
+    F = np.random.default_rng(k).standard_normal((k, offs[-1], 3))
+    U = rp.matvec_batched(_t(pos), offs, _t(F), 0.9, 1.3, precision=prec)
+    assert torch.equal(U, rp.matvec_batched(_t(pos), offs, _t(F), 0.9, 1.3, precision=prec))
+    for a, b in zip(offs, offs[1:]):
+        for j in {0, k - 1}:
+            check(U[j, a:b].cpu().numpy(), orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec],
+                  f"system {b - a} of {sizes} k={k} rhs {j} prec={prec}")
