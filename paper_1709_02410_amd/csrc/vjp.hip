@@ -154,12 +154,14 @@ struct VjpBody {
     }
 };
 
-// One wave per quantity of 64 consecutive blobs (coalesced over the blobs),
-// then the chain rule of the regularisation by the first wave.  Bound by the
-// reads of the partials (0.53 GB at 5e4 blobs in FP32C).  One thread per blob
-// for all nine sums, as before, ran N / 256 workgroups of a serial chain:
-// 547 us against 133 us there, and 36 us against 4.1 us at 1000 blobs
-// (FP64).
+// One wave per quantity of kEpiBlobs consecutive blobs, four lanes to a blob that
+// share its chunks and items (128-byte reads), then the chain rule of the
+// regularisation by the first lanes.  Bound by the reads of the partials (0.53
+// GB at 5e4 blobs in FP32C), and on small problems by their chain.  One thread
+// per blob for all nine sums took 547 us at 5e4 blobs and 36 us at 1000 (FP64),
+// one lane per blob and quantity 133 and 10.4; four lanes save another 5 us of a
+// call at 1000 blobs (26.8 -> 21.6 us) and 3% at 8000.
+constexpr int kEpiBlobs = 16;
 template <typename R>
 __global__ __launch_bounds__(64 * kQ) void sym_vjp_epilogue(const double* __restrict__ tpart,
                                                             const R* __restrict__ spart,
@@ -169,12 +171,16 @@ __global__ __launch_bounds__(64 * kQ) void sym_vjp_epilogue(const double* __rest
                                                             int Hmax, int nseg, int G, double inv_a, double mu0,
                                                             double* __restrict__ grad_pos,
                                                             double* __restrict__ grad_f) {
-    __shared__ double sum[kQ][64];
-    const int x = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * 64 + x;
-    sum[q][x] = i < N ? sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G, 0, 1, nseg) : 0.0;
+    __shared__ double sum[kQ][kEpiBlobs];
+    constexpr int U = 64 / kEpiBlobs;
+    const int x = threadIdx.x % kEpiBlobs, u = (threadIdx.x & 63) / kEpiBlobs, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kEpiBlobs + x;
+    double t = i < N ? sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G, u, U, nseg) : 0.0;
+#pragma unroll
+    for (int m = kEpiBlobs; m < 64; m <<= 1) t += __shfl_xor(t, m, 64);
+    if (u == 0) sum[q][x] = t;
     __syncthreads();
-    if (q != 0 || i >= N) return;
+    if (threadIdx.x >= kEpiBlobs || i >= N) return;
     double s[kQ];
 #pragma unroll
     for (int k = 0; k < kQ; ++k) s[k] = sum[k][x];
@@ -254,7 +260,7 @@ namespace {
 // kSym64MaxN), 9 quantities per blob.  FP64 splits the passes of few items as
 // the product does, first over the four waves of a workgroup (ns), then over
 // workgroups (nseg): 136 items of 64 steps left the GPU nearly empty at 1000
-// blobs: 85 us a call before, 27 us now, with the records formed in the pair
+// blobs: 85 us a call before, 22 us now, with the records formed in the pair
 // kernel (5000 blobs 317 -> 180 us).  Its 2 waves per SIMD (registers) fill
 // the GPU with kVjpWaves; beyond that a split only adds partials.  FP32C is
 // not split: it sums a pass in FP32, so another split is another rounding.
@@ -328,7 +334,7 @@ int vjp_sym(const double* pos, const double* f, const double* g, double* grad_po
     launch_vjp_sym<R>(rec, PackSrc{pos, f, N, 2, 1.0 / a, 0.0, 0.0, g}, p, ipw, tpart, spart, st);
     RPYW_HIP(hipGetLastError());
     profile_end(st, ev, (double)N * (double)N);
-    hipLaunchKernelGGL(sym_vjp_epilogue<R>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kQ), 0, st, tpart, spart, pos, f,
+    hipLaunchKernelGGL(sym_vjp_epilogue<R>, dim3((unsigned)((N + kEpiBlobs - 1) / kEpiBlobs)), dim3(64 * kQ), 0, st, tpart, spart, pos, f,
                        g, N, p.ng, p.C, p.Hmax, p.nseg, p.G, 1.0 / a, m0, grad_pos, grad_f);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;
