@@ -321,7 +321,7 @@ int rpy_wall_matvec_periodic(const double* pos, const double* F, double* U, int6
         return RPYW_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     Scratch s;
-    int rc = acquire(ws, ws_bytes, product_ws_bytes(N, precision, 1), st, s);
+    int rc = acquire(ws, ws_bytes, product_ws_bytes(N, precision, ws ? 1 : std::min(k, 2)), st, s);
     if (rc == RPYW_OK) rc = products(pos, F, U, N, k, a, eta, precision, s.ar, st, Domain{Lx, Ly});
     if (log_enabled()) log_shape("rpy_wall_matvec_periodic", N, k, precision, rc);
     return rc;

@@ -234,3 +234,22 @@ def test_batched_parts(rp, orc, sizes, prec, k):
         for j in {0, k - 1}:
             check(U[j, a:b].cpu().numpy(), orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec],
                   f"system {b - a} of {sizes} k={k} rhs {j} prec={prec}")
+
+
+@pytest.mark.parametrize("N", [1, 64, 130, 700, 2000])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("cell", [(40.0, 37.0), (4.2, 4.3)])
+def test_periodic_pairs_of_right_hand_sides(rp, orc, N, prec, cell):
+    """Two right-hand sides to a pass (and the odd one alone), in wide cells and
+    in one below 4.5 a: the sums of single products, FP32C to the last bit,
+    FP64 up to the order of additions."""
+    rng = np.random.default_rng(N)
+    pos = np.column_stack([rng.uniform(0, cell[0], N), rng.uniform(0, cell[1], N), rng.uniform(0.4, 30.0, N)])
+    F = rng.standard_normal((3, N, 3))
+    U = rp.matvec_periodic(_t(pos), _t(F), cell, 1.0, 1.3, precision=prec).cpu().numpy()
+    for j in range(3):
+        one = rp.matvec_periodic(_t(pos), _t(F[j:j + 1]), cell, 1.0, 1.3, precision=prec).cpu().numpy()[0]
+        if prec == 1:
+            assert np.array_equal(U[j], one)
+        else:
+            check(U[j], one, 1e-13, f"periodic N={N} rhs {j}")
