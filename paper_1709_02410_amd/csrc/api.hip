@@ -365,7 +365,7 @@ int rpy_wall_matvec_batched(const double* pos, const int64_t* sys_offsets, int32
     if (Ntot >= kMaxN) return RPYW_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     Scratch s;
-    int rc = acquire(ws, ws_bytes, batched_ws_bytes(Ntot, S, k, precision), st, s);
+    int rc = acquire(ws, ws_bytes, batched_ws_bytes(Ntot, S, k, precision, !ws), st, s);
     if (rc == RPYW_OK) rc = batched_products(pos, sys_offsets, S, F, U, k, a, eta, precision, s.ar, st);
     log_line("rpy_wall_matvec_batched S=%d Ntot=%lld k=%d prec=%d status=%d", S, (long long)Ntot, k, precision, rc);
     return rc;

@@ -1012,19 +1012,21 @@ int batched_parts(int64_t Ntot, bool mat) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(64, (kBatchedItems + (mat ? items - 1 : 0)) / items));
 }
 
-size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec) {
+size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec, bool split) {
     const int kb = kernel_k(std::max(k, 1), prec, 1);  // the widest the batched kernels take
     size_t b = align_up((size_t)Ntot * rec_width(prec, kb) * real_size(prec));
     b += align_up((size_t)Ntot * sizeof(double));
     const size_t max_items = (size_t)(Ntot / kMatTargets) + (size_t)S + 1;  // items of 64 or more targets
-    size_t items = max_items, part = 0;
-    for (int K = 1; K <= kb; K <<= 1) {
-        const int p = std::max(batched_parts(Ntot, false), K >= 8 ? batched_parts(Ntot, true) : 1);
-        if (p > 1) part = std::max(part, (size_t)p * K * 3 * Ntot * sizeof(double));
+    size_t items = max_items;
+    if (split) {
+        const bool mat = default_shape(Ntot, std::max(k, 1), prec).mat;
+        const int parts = batched_parts(Ntot, mat);
+        if (parts > 1) {
+            items = (mat ? max_items : (size_t)(Ntot / kBlock) + (size_t)S + 1) * parts;
+            b += align_up((size_t)parts * kernel_k(std::max(k, 1), prec, mat) * 3 * Ntot * sizeof(double));
+        }
     }
-    items = std::max(items, ((size_t)(Ntot / kBlock) + S + 1) * batched_parts(Ntot, false));
-    items = std::max(items, max_items * batched_parts(Ntot, true));
-    b += align_up(items * sizeof(int4)) + align_up(part);
+    b += align_up(std::max(items, max_items) * sizeof(int4));
     b += kAlign;  // counter
     return b + 4 * kAlign;
 }
@@ -1052,23 +1054,31 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     const int span = sh.mat ? kMatTargets : kBlock * sh.tpl;
     const int tile = !sh.mat ? (sh.tile == 64 ? 64 : 256)
                      : prec == RPYW_FP32C ? mat_tile<float>() : mat_tile<double>();
-    const int parts = (int)std::min<int64_t>(batched_parts(Ntot, sh.mat), (nmax + tile - 1) / tile);
-    std::vector<int4> items;
-    for (int s : order) {
-        const int b0 = (int)sys_offsets[s], b1 = (int)sys_offsets[s + 1];
-        for (int p = 0; p < parts; ++p)
-            for (int t = b0; t < b1; t += span) items.push_back(make_int4(b0, b1, t, p));
-    }
     const size_t mark = ar.used;
     const int K = kernel_k(sh.kblk, prec, sh.mat);
     if (sh.kblk > K) return RPYW_EINVAL;
     const int rw = rec_width(prec, K);
     void* rec = ar.take((size_t)Ntot * rw * real_size(prec));
     double* B = (double*)ar.take((size_t)Ntot * sizeof(double));
-    int4* ditems = (int4*)ar.take(items.size() * sizeof(int4));
     unsigned* counter = (unsigned*)ar.take(sizeof(unsigned));
-    double* part = parts > 1 ? (double*)ar.take((size_t)parts * K * 3 * Ntot * sizeof(double)) : nullptr;
-    if (!rec || !B || !ditems || !counter || (parts > 1 && !part)) {
+    // the sources in one part if the workspace does not hold more
+    int parts = (int)std::min<int64_t>(batched_parts(Ntot, sh.mat), (nmax + tile - 1) / tile);
+    std::vector<int4> items;
+    int4* ditems = nullptr;
+    double* part = nullptr;
+    for (const size_t before = ar.used;; parts = 1) {
+        ar.used = before;
+        items.clear();
+        for (int s : order) {
+            const int b0 = (int)sys_offsets[s], b1 = (int)sys_offsets[s + 1];
+            for (int p = 0; p < parts; ++p)
+                for (int t = b0; t < b1; t += span) items.push_back(make_int4(b0, b1, t, p));
+        }
+        ditems = (int4*)ar.take(items.size() * sizeof(int4));
+        part = parts > 1 ? (double*)ar.take((size_t)parts * K * 3 * Ntot * sizeof(double)) : nullptr;
+        if (parts == 1 || (ditems && part)) break;
+    }
+    if (!rec || !B || !ditems || !counter) {
         ar.used = mark;
         return RPYW_ENOMEM;
     }

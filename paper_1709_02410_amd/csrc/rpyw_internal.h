@@ -149,7 +149,8 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
              Arena& ar, hipStream_t st, const Domain& dom = Domain{});
 
 // Batched independent systems (persistent kernel, LPT work list).
-size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec);
+// split: with room for the sources in parts (batched_products does without).
+size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec, bool split = true);
 int batched_products(const double* pos, const int64_t* sys_offsets, int S, const double* F, double* U, int k,
                      double a, double eta, int prec, Arena& ar, hipStream_t st);
 
