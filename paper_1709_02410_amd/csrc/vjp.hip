@@ -88,17 +88,12 @@ __global__ __launch_bounds__(kBlock) void vjp_kernel(const R* __restrict__ rec, 
     }
 }
 
-__global__ void vjp_epilogue(const double* __restrict__ part, const double* __restrict__ pos,
-                             const double* __restrict__ f, const double* __restrict__ g, int64_t N, int splits,
-                             double inv_a, double mu0, double* __restrict__ grad_pos, double* __restrict__ grad_f) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    double s[kQ];
-    for (int q = 0; q < kQ; ++q) {
-        double t = 0.0;
-        for (int p = 0; p < splits; ++p) t += part[((int64_t)p * kQ + q) * N + i];
-        s[q] = t;
-    }
+// The gradients of blob i from its nine sums (the chain rule of the
+// regularisation).
+__device__ __forceinline__ void vjp_finish(const double (&s)[kQ], const double* __restrict__ pos,
+                                           const double* __restrict__ f, const double* __restrict__ g, int64_t i,
+                                           double inv_a, double mu0, double* __restrict__ grad_pos,
+                                           double* __restrict__ grad_f) {
     const double z = pos[3 * i + 2] * inv_a;
     const double B = z < 1.0 ? z : 1.0;
     if (grad_pos) {
@@ -110,6 +105,44 @@ __global__ void vjp_epilogue(const double* __restrict__ part, const double* __re
     }
     if (grad_f)
         for (int c = 0; c < 3; ++c) grad_f[3 * i + c] = mu0 * B * s[6 + c];
+}
+
+// Epilogues: one wave per quantity of kEpiBlobs consecutive blobs, four lanes to
+// a blob that share its chunks (128-byte reads).
+constexpr int kEpiBlobs = 16;
+constexpr int kEpiShares = 64 / kEpiBlobs;
+// Adds the shares t of the lanes, finishes the blobs.
+__device__ __forceinline__ void vjp_shares(double t, const double* __restrict__ pos, const double* __restrict__ f,
+                                           const double* __restrict__ g, int64_t N, double inv_a, double mu0,
+                                           double* __restrict__ grad_pos, double* __restrict__ grad_f) {
+    __shared__ double sum[kQ][kEpiBlobs];
+    const int x = threadIdx.x % kEpiBlobs;
+#pragma unroll
+    for (int m = kEpiBlobs; m < 64; m <<= 1) t += __shfl_xor(t, m, 64);
+    if ((threadIdx.x & 63) < kEpiBlobs) sum[threadIdx.x >> 6][x] = t;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kEpiBlobs + x;
+    if (threadIdx.x >= kEpiBlobs || i >= N) return;
+    double s[kQ];
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) s[k] = sum[k][x];
+    vjp_finish(s, pos, f, g, i, inv_a, mu0, grad_pos, grad_f);
+}
+
+// Of the plain kernel (below 512 blobs in FP32C, 4 to 7 chunks).  One thread per
+// blob was a chain of nine sums on one or two workgroups: 10.2 us at 300 blobs,
+// now 3 (a call 58.5 -> 50.6).
+__global__ __launch_bounds__(64 * kQ) void vjp_epilogue(const double* __restrict__ part,
+                                                        const double* __restrict__ pos, const double* __restrict__ f,
+                                                        const double* __restrict__ g, int64_t N, int splits,
+                                                        double inv_a, double mu0, double* __restrict__ grad_pos,
+                                                        double* __restrict__ grad_f) {
+    const int u = (threadIdx.x & 63) / kEpiBlobs, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kEpiBlobs + threadIdx.x % kEpiBlobs;
+    double t = 0.0;
+    if (i < N)
+        for (int p = u; p < splits; p += kEpiShares) t += part[((int64_t)p * kQ + q) * N + i];
+    vjp_shares(t, pos, f, g, N, inv_a, mu0, grad_pos, grad_f);
 }
 
 // Symmetric VJP (sym_pairs.h).  For the pair (i, j) the scalar
@@ -154,14 +187,12 @@ struct VjpBody {
     }
 };
 
-// One wave per quantity of kEpiBlobs consecutive blobs, four lanes to a blob that
-// share its chunks and items (128-byte reads), then the chain rule of the
-// regularisation by the first lanes.  Bound by the reads of the partials (0.53
+// Of the symmetric kernel: the four lanes share chunks and items.  Bound by the
+// reads of the partials (0.53
 // GB at 5e4 blobs in FP32C), and on small problems by their chain.  One thread
 // per blob for all nine sums took 547 us at 5e4 blobs and 36 us at 1000 (FP64),
 // one lane per blob and quantity 133 and 10.4; four lanes save another 5 us of a
 // call at 1000 blobs (26.8 -> 21.6 us) and 3% at 8000.
-constexpr int kEpiBlobs = 16;
 template <typename R>
 __global__ __launch_bounds__(64 * kQ) void sym_vjp_epilogue(const double* __restrict__ tpart,
                                                             const R* __restrict__ spart,
@@ -171,30 +202,10 @@ __global__ __launch_bounds__(64 * kQ) void sym_vjp_epilogue(const double* __rest
                                                             int Hmax, int nseg, int G, double inv_a, double mu0,
                                                             double* __restrict__ grad_pos,
                                                             double* __restrict__ grad_f) {
-    __shared__ double sum[kQ][kEpiBlobs];
-    constexpr int U = 64 / kEpiBlobs;
-    const int x = threadIdx.x % kEpiBlobs, u = (threadIdx.x & 63) / kEpiBlobs, q = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * kEpiBlobs + x;
-    double t = i < N ? sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G, u, U, nseg) : 0.0;
-#pragma unroll
-    for (int m = kEpiBlobs; m < 64; m <<= 1) t += __shfl_xor(t, m, 64);
-    if (u == 0) sum[q][x] = t;
-    __syncthreads();
-    if (threadIdx.x >= kEpiBlobs || i >= N) return;
-    double s[kQ];
-#pragma unroll
-    for (int k = 0; k < kQ; ++k) s[k] = sum[k][x];
-    const double z = pos[3 * i + 2] * inv_a;
-    const double B = z < 1.0 ? z : 1.0;
-    if (grad_pos) {
-        const double dLdB = mu0 * (g[3 * i] * s[3] + g[3 * i + 1] * s[4] + g[3 * i + 2] * s[5] + f[3 * i] * s[6] +
-                                   f[3 * i + 1] * s[7] + f[3 * i + 2] * s[8]);
-        grad_pos[3 * i] = mu0 * inv_a * s[0];
-        grad_pos[3 * i + 1] = mu0 * inv_a * s[1];
-        grad_pos[3 * i + 2] = z < 1.0 ? inv_a * dLdB : mu0 * inv_a * s[2];
-    }
-    if (grad_f)
-        for (int c = 0; c < 3; ++c) grad_f[3 * i + c] = mu0 * B * s[6 + c];
+    const int u = (threadIdx.x & 63) / kEpiBlobs, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kEpiBlobs + threadIdx.x % kEpiBlobs;
+    const double t = i < N ? sym_gather<R>(tpart, spart, i, ng, C, Hmax, kQ, q, G, u, kEpiShares, nseg) : 0.0;
+    vjp_shares(t, pos, f, g, N, inv_a, mu0, grad_pos, grad_f);
 }
 
 // div_i,a = sum_j sum_b d(M_ij)_ab / d r_j,b (source derivative; for j = i
@@ -334,8 +345,8 @@ int vjp_sym(const double* pos, const double* f, const double* g, double* grad_po
     launch_vjp_sym<R>(rec, PackSrc{pos, f, N, 2, 1.0 / a, 0.0, 0.0, g}, p, ipw, tpart, spart, st);
     RPYW_HIP(hipGetLastError());
     profile_end(st, ev, (double)N * (double)N);
-    hipLaunchKernelGGL(sym_vjp_epilogue<R>, dim3((unsigned)((N + kEpiBlobs - 1) / kEpiBlobs)), dim3(64 * kQ), 0, st, tpart, spart, pos, f,
-                       g, N, p.ng, p.C, p.Hmax, p.nseg, p.G, 1.0 / a, m0, grad_pos, grad_f);
+    hipLaunchKernelGGL(sym_vjp_epilogue<R>, dim3((unsigned)((N + kEpiBlobs - 1) / kEpiBlobs)), dim3(64 * kQ), 0, st,
+                       tpart, spart, pos, f, g, N, p.ng, p.C, p.Hmax, p.nseg, p.G, 1.0 / a, m0, grad_pos, grad_f);
     RPYW_HIP(hipGetLastError());
     return RPYW_OK;
 }
@@ -406,8 +417,8 @@ int vjp(const double* pos, const double* f, const double* g, double* grad_pos, d
     }
     RPYW_HIP(hipGetLastError());
     profile_end(st, ev, (double)N * (double)N);
-    hipLaunchKernelGGL(vjp_epilogue, dim3(g1), dim3(kBlock), 0, st, part, pos, f, g, N, splits, 1.0 / a, m0, grad_pos,
-                       grad_f);
+    hipLaunchKernelGGL(vjp_epilogue, dim3((unsigned)((N + kEpiBlobs - 1) / kEpiBlobs)), dim3(64 * kQ), 0, st, part, pos,
+                       f, g, N, splits, 1.0 / a, m0, grad_pos, grad_f);
     RPYW_HIP(hipGetLastError());
     ar.used = mark;
     return RPYW_OK;
