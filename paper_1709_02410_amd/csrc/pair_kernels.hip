@@ -778,8 +778,13 @@ int sym_pass(const double* pos, const double* F, double* U, int64_t N, int kb, i
     }
     // Groups of 64 and of 128: the pair kernel forms the records itself, two
     // launches per product; otherwise the records are packed once by their
-    // own kernel.
-    const bool fused = sp.G != 256;
+    // own kernel.  So are those of FP32C products in a periodic cell whose
+    // passes are not split: forming them there is a wrap in FP64 per record,
+    // and the kernel that reads them needs 94 vector registers instead of 106
+    // (5 waves on a SIMD, not 4): 2.53 -> 2.46 ms at 20000 blobs, 5.64 -> 5.49
+    // at 29958.  In FP64 the packed form is the slower one (two right-hand
+    // sides at 20000 blobs: 5.73 ms, formed in the kernel 5.49).
+    const bool fused = sp.G != 256 && !(dom.periodic() && prec == RPYW_FP32C && sp.ns == 1);
     const PackSrc ps{pos, F, N, kb, 1.0 / a, dom.lx / a, dom.ly / a};
     void* rec = nullptr;
     double* B = nullptr;

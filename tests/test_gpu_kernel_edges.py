@@ -253,3 +253,24 @@ def test_periodic_pairs_of_right_hand_sides(rp, orc, N, prec, cell):
             assert np.array_equal(U[j], one)
         else:
             check(U[j], one, 1e-13, f"periodic N={N} rhs {j}")
+
+
+@pytest.mark.parametrize("N", [8128, 8129, 8192, 8193])
+def test_periodic_fp32c_records(rp, N):
+    """Both sides of the line between FP32C records formed in the kernel (127
+    groups of 64) and packed ones (128 and more), full and ragged last groups,
+    one and two right-hand sides: the FP32C products over groups of 256.  (FP64
+    is no reference at this size: some pairs are half a cell apart up to FP32
+    rounding, and precisions may differ in the images that they take.)"""
+    rng = np.random.default_rng(N)
+    cell = (150.0, 140.0)
+    pos = np.column_stack([rng.uniform(-200, 300, N), rng.uniform(-200, 300, N), rng.uniform(0.4, 30.0, N)])
+    F = rng.standard_normal((3, N, 3))
+    U = rp.matvec_periodic(_t(pos), _t(F), cell, 1.0, 1.3, precision=1).cpu().numpy()
+    rp.set_shape(1, N, 1, tpl=1, tile=256, kblk=1, sym=1, ipw=1)
+    try:
+        for j in range(3):
+            ref = rp.matvec(_t(pos), _t(F[j]), 1.0, 1.3, precision=1, box=cell).cpu().numpy()
+            check(U[j], ref, TOL[1], f"periodic N={N} rhs {j}")
+    finally:
+        rp.reset_shape(1, N, 1)
