@@ -959,6 +959,11 @@ int direct_products(const double* pos, const double* F, double* U, int64_t N, in
     return RPYW_OK;
 }
 
+bool overlap(const double* x, int64_t nx, const double* y, int64_t ny) {
+    const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y;
+    return a < b + (size_t)ny * sizeof(double) && b < a + (size_t)nx * sizeof(double);
+}
+
 }  // namespace
 
 int products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
@@ -989,7 +994,10 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
         return RPYW_OK;
     }
     Shape sh = tuned_shape(N, k, prec);
-    if (sh.direct) return direct_products(pos, F, U, N, k, a, eta, st);
+    // One launch writes velocities while other workgroups still read: outputs
+    // on top of the inputs take the other kernels, which read them all first.
+    if (sh.direct && !overlap(U, 3 * N * k, F, 3 * N * k) && !overlap(U, 3 * N * k, pos, 3 * N))
+        return direct_products(pos, F, U, N, k, a, eta, st);
     if (prec != RPYW_FP32C && !sh.mat) sh.kblk = std::min(sh.kblk, 8);  // e.g. RPYW_RHS_WIDTH=16 on the vector units
     for (int k0 = 0; k0 < k; k0 += sh.kblk) {
         const int kb = std::min(sh.kblk, k - k0);

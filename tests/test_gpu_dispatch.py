@@ -1,0 +1,52 @@
+"""Which kernel a call takes: rules of the dispatch at their edges, against the
+FP64 oracle or against the same call through a fixed launch shape.  Bars: those
+of the two precisions (FP64 1e-12, FP32C 1e-5, relative L2 and largest entry)."""
+import numpy as np
+import pytest
+
+from parity_util import check
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+TOL = {0: 1e-12, 1: 1e-5}
+
+
+@pytest.fixture(scope="module")
+def rp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1709_02410_amd import rpywall
+    rpywall.lib()
+    return rpywall
+
+
+def _t(x):
+    return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float64, device="cuda")
+
+
+def _mixed(n, seed):
+    """Blobs above and below z = a, overlapping pairs, one coincident pair."""
+    rng = np.random.default_rng(seed)
+    box = max(2.0, 2.0 * np.sqrt(n))
+    pos = np.column_stack([rng.uniform(0, box, n), rng.uniform(0, box, n), rng.uniform(0.3, 4.0, n)])
+    if n >= 3:
+        pos[2] = pos[1]
+    return pos
+
+
+@pytest.mark.parametrize("N,k", [(1, 1), (300, 1), (300, 9), (1000, 1), (1280, 16), (2000, 4), (2048, 1)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_velocities_on_top_of_forces(rp, orc, N, k, prec):
+    """out = F: all forces are read before the first velocity is written, also
+    at the sizes of the one-launch products."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + k).standard_normal((k, N, 3))
+    U = _t(F)
+    rp.matvec_multi(_t(pos), U, 0.9, 1.3, precision=prec, out=U)
+    for j in {0, k // 2, k - 1}:
+        check(U[j].cpu().numpy(), orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"in place N={N} k={k} rhs {j}")
+    if k == 1:
+        u = _t(F[0])
+        rp.matvec_noalloc(_t(pos), u, 0.9, 1.3, precision=prec, out=u)
+        check(u.cpu().numpy(), orc.matvec(pos, F[0], 0.9, 1.3), TOL[prec], f"in place, noalloc N={N}")
