@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "batched_plan.h"
 #include "pair_math.h"
 #include "records.h"
 #include "rpyw_internal.h"
@@ -226,11 +227,13 @@ __global__ __launch_bounds__(kBlock) void mat_pair_kernel(const R* __restrict__ 
     }
 }
 
-// Sources of a batched item {sys_begin, sys_end, target_begin, part}: part of
-// `parts` shares of whole tiles of its system (past its end: none).
-__device__ __forceinline__ int2 part_sources(const int4& it, int parts, int tile) {
-    const int tiles = (it.y - it.x + tile - 1) / tile, len = (tiles + parts - 1) / parts * tile;
-    const int s0 = it.x + it.w * len;
+// Sources of a batched item {sys_begin, sys_end, target_begin, share}
+// (BatchedItem): its share of whole tiles of its system.
+__device__ __forceinline__ int2 part_sources(const int4& it, int tile) {
+    const int used = it.w >> 8;
+    if (used == 1) return make_int2(it.x, it.y);
+    const int len = share_tiles((it.y - it.x + tile - 1) / tile, used) * tile;
+    const int s0 = it.x + (it.w & 255) * len;
     return make_int2(s0, s0 + len < it.y ? s0 + len : it.y);
 }
 
@@ -247,8 +250,8 @@ __global__ __launch_bounds__(kBlock, mat_batched_waves<R>()) void mat_batched_ke
                                                              const int4* __restrict__ items, int n_items,
                                                              unsigned* __restrict__ counter,
                                                              const double* __restrict__ B, double mu0, int64_t Ntot,
-                                                             int kb, double* __restrict__ U, int parts,
-                                                             double* __restrict__ part) {
+                                                             int kb, double* __restrict__ U,
+                                                             double* __restrict__ part, int* __restrict__ used) {
     __shared__ __attribute__((aligned(16))) R tile[mat_tile<R>() * rec_w<R, K>()];
     __shared__ int s_item;
     for (;;) {
@@ -260,17 +263,20 @@ __global__ __launch_bounds__(kBlock, mat_batched_waves<R>()) void mat_batched_ke
         const int4 it = items[item];
         MatLane<R, K> L;
         L.load(rec, it.z, it.y);
-        const int2 src = part_sources(it, parts, mat_tile<R>());
+        const int2 src = part_sources(it, mat_tile<R>());
         L.run(rec, src.x, src.y, tile);
         const int k = MatLane<R, K>::rhs();
-        if (parts > 1) {
+        if (part) {
+            const int p = it.w & 255;
+            if (p == 0 && (int)threadIdx.x < kMatTargets && it.z + (int)threadIdx.x < it.y)
+                used[it.z + threadIdx.x] = it.w >> 8;
             if (k < K)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int64_t i = (int64_t)it.z + MatLane<R, K>::target(v);
                     if (i >= it.y) continue;
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) part[((int64_t)(it.w * K + k) * 3 + c) * Ntot + i] = L.total(c, v);
+                    for (int c = 0; c < 3; ++c) part[((int64_t)(p * K + k) * 3 + c) * Ntot + i] = L.total(c, v);
                 }
             continue;
         }

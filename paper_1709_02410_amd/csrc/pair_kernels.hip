@@ -22,6 +22,7 @@
 #include <mutex>
 #include <vector>
 
+#include "batched_plan.h"
 #include "direct_pairs.h"
 #include "mat_pairs.h"
 #include "pair_math.h"
@@ -173,7 +174,8 @@ __global__ __launch_bounds__(kBlock) void pair_kernel(const R* __restrict__ rec,
     }
 }
 
-// U[k][i][c] = mu0 B_i sum_s part[s][k][c][i] for k < kb: kEpiParts threads per
+// U[k][i][c] = mu0 B_i sum_s part[s][k][c][i] for k < kb, s < splits (used[i] if
+// given: batched systems): kEpiParts threads per
 // (blob, component q = 3 k + c) add the chunks s = u (mod kEpiParts), then the
 // shares are added in order.  Bound by the reads of the partials (coalesced
 // over 64 blobs).  One thread per blob for all components and chunks, as
@@ -182,7 +184,8 @@ __global__ __launch_bounds__(kBlock) void pair_kernel(const R* __restrict__ rec,
 constexpr int kEpiParts = 8;
 __global__ __launch_bounds__(64 * kEpiParts) void epilogue_kernel(const double* __restrict__ part,
                                                                   const double* __restrict__ B, int64_t N, int kdim,
-                                                                  int splits, double mu0, double* __restrict__ U) {
+                                                                  int splits, double mu0, double* __restrict__ U,
+                                                                  const int* __restrict__ used = nullptr) {
     __shared__ double red[kEpiParts][64];
     const int x = threadIdx.x & 63, u = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + x;
@@ -191,8 +194,11 @@ __global__ __launch_bounds__(64 * kEpiParts) void epilogue_kernel(const double* 
     if (i < N) {
         const int64_t st = (int64_t)3 * kdim * N;
         const double* p = part + (int64_t)q * N + i;
+        const double first = u < splits ? p[u * st] : 0.0;  // does not wait for used[i]
+        if (used) splits = used[i];
+        if (u < splits) s = first;
 #pragma unroll 4
-        for (int c = u; c < splits; c += kEpiParts) s += p[c * st];
+        for (int c = u + kEpiParts; c < splits; c += kEpiParts) s += p[c * st];
     }
     red[u][x] = s;
     __syncthreads();
@@ -203,17 +209,17 @@ __global__ __launch_bounds__(64 * kEpiParts) void epilogue_kernel(const double* 
 }
 
 // Batched systems: persistent workgroups take items {sys_begin, sys_end,
-// target_begin, part} from an atomic counter.  With one part an item covers all
-// sources of its system and writes final velocities; with more (few items, see
-// batched_parts) it covers its share of them, at multiples of the tile (the
-// FP32 sums of a tile are the same), and writes partial sums in the layout of
-// pair_kernel's, which epilogue_kernel adds up.
+// target_begin, share} (batched_plan.h) from an atomic counter.  Without `part`
+// an item covers all sources of its system and writes final velocities; with it
+// (few items) it covers its share of them, at multiples of the tile (the FP32
+// sums of a tile are the same), and writes partial sums in the layout of
+// pair_kernel's, which epilogue_kernel adds up, and in used[] the number of them.
 template <typename R, int K, int TPL, int TILE>
 __global__ __launch_bounds__(kBlock) void batched_kernel(const R* __restrict__ rec, const int4* __restrict__ items,
                                                          int n_items, unsigned* __restrict__ counter,
                                                          const double* __restrict__ B, double mu0, int64_t Ntot,
-                                                         int kb, double* __restrict__ U, int parts,
-                                                         double* __restrict__ part) {
+                                                         int kb, double* __restrict__ U,
+                                                         double* __restrict__ part, int* __restrict__ used) {
     __shared__ __attribute__((aligned(16))) R tile[TILE * rec_w<R, K>()];
     __shared__ int s_item;
     for (;;) {
@@ -225,18 +231,19 @@ __global__ __launch_bounds__(kBlock) void batched_kernel(const R* __restrict__ r
         const int4 it = items[item];
         Lane<R, K, TPL> L;
         L.load(rec, it.z, it.y, threadIdx.x);
-        const int2 src = part_sources(it, parts, TILE);
+        const int2 src = part_sources(it, TILE);
         L.template run<TILE>(rec, src.x, src.y, tile);
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
             const int64_t i = (int64_t)it.z + (int64_t)t * kBlock + threadIdx.x;
             if (i >= it.y) continue;
-            if (parts > 1) {
+            if (part) {
+                const int p = it.w & 255;
+                if (p == 0) used[i] = it.w >> 8;
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        part[((int64_t)(it.w * K + k) * 3 + c) * Ntot + i] = L.total(t, k, c);
+                    for (int c = 0; c < 3; ++c) part[((int64_t)(p * K + k) * 3 + c) * Ntot + i] = L.total(t, k, c);
                 continue;
             }
             const double sc = mu0 * B[i];
@@ -509,10 +516,10 @@ hipError_t launch_pair_t(const R* rec, int64_t N, int splits, int64_t chunk, dou
 
 template <typename R, int K, int TPL, int TILE>
 hipError_t launch_batched_t(const R* rec, const int4* items, int n_items, unsigned* counter, const double* B,
-                            double mu0, int64_t Ntot, int kb, double* U, int parts, double* part, int grid,
+                            double mu0, int64_t Ntot, int kb, double* U, double* part, int* used, int grid,
                             hipStream_t st) {
     hipLaunchKernelGGL((batched_kernel<R, K, TPL, TILE>), dim3(grid), dim3(kBlock), 0, st, rec, items, n_items,
-                       counter, B, mu0, Ntot, kb, U, parts, part);
+                       counter, B, mu0, Ntot, kb, U, part, used);
     return hipGetLastError();
 }
 
@@ -558,11 +565,10 @@ hipError_t launch_mat_t(const void* rec, int64_t N, const MatSplit& ms, double* 
 
 template <typename R, int K>
 hipError_t launch_mat_batched_t(const void* rec, const int4* items, int n_items, unsigned* counter,
-                                const double* B, double mu0, int64_t Ntot, int kb, double* U, int parts,
-                                double* part, int grid,
-                                hipStream_t st) {
+                                const double* B, double mu0, int64_t Ntot, int kb, double* U, double* part,
+                                int* used, int grid, hipStream_t st) {
     hipLaunchKernelGGL((mat_batched_kernel<R, K>), dim3(grid), dim3(kBlock), 0, st, (const R*)rec, items, n_items,
-                       counter, B, mu0, Ntot, kb, U, parts, part);
+                       counter, B, mu0, Ntot, kb, U, part, used);
     return hipGetLastError();
 }
 
@@ -577,14 +583,13 @@ hipError_t launch_mat(int prec, int K, const void* rec, int64_t N, const MatSpli
 }
 
 hipError_t launch_mat_batched(int prec, int K, const void* rec, const int4* items, int n_items, unsigned* counter,
-                              const double* B, double mu0, int64_t Ntot, int kb, double* U, int parts, double* part,
-                              int grid,
-                              hipStream_t st) {
+                              const double* B, double mu0, int64_t Ntot, int kb, double* U, double* part, int* used,
+                              int grid, hipStream_t st) {
     if (prec == RPYW_FP32C)
-        return K == 16 ? launch_mat_batched_t<float, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st)
-                       : launch_mat_batched_t<float, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st);
-    return K == 16 ? launch_mat_batched_t<double, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st)
-                   : launch_mat_batched_t<double, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, parts, part, grid, st);
+        return K == 16 ? launch_mat_batched_t<float, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, part, used, grid, st)
+                       : launch_mat_batched_t<float, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, part, used, grid, st);
+    return K == 16 ? launch_mat_batched_t<double, 16>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, part, used, grid, st)
+                   : launch_mat_batched_t<double, 8>(rec, items, n_items, counter, B, mu0, Ntot, kb, U, part, used, grid, st);
 }
 
 // Expand (K, TPL, TILE) runtime values into template instantiations.
@@ -1010,36 +1015,21 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
 
 // ------------------------------------------------------------ batched
 
-// Parts into which the sources of every system are split, so that there are
-// about kBatchedItems items of work: 1024 to 1280 run at a time, and the large
-// systems' items are long (few or small systems are a serial pass over all
-// sources on a few workgroups; many end unevenly).  A call, before and now: two
-// systems of up to 5000 blobs, FP32C, 80 -> 30 us; 14 of up to 11000, 8
-// right-hand sides, FP64, 4.9 -> 2.4 ms; 64 of up to 12000, 4 right-hand sides,
-// FP64, 5.7 -> 3.4 ms; 64 of up to 17000, 16 right-hand sides, FP32C, 11.1 ->
-// 10.9 ms.  Twice as many items lose up to 12%.
-constexpr int64_t kBatchedItems = 8192;
-int batched_parts(int64_t Ntot, bool mat) {
-    const int64_t items = Ntot / (mat ? kMatTargets : kBlock) + 1;
-    // (rounded down where the partial sums of a part are the larger: span 256)
-    return (int)std::max<int64_t>(1, std::min<int64_t>(64, (kBatchedItems + (mat ? items - 1 : 0)) / items));
-}
-
 size_t batched_ws_bytes(int64_t Ntot, int S, int k, int prec, bool split) {
     const int kb = kernel_k(std::max(k, 1), prec, 1);  // the widest the batched kernels take
     size_t b = align_up((size_t)Ntot * rec_width(prec, kb) * real_size(prec));
     b += align_up((size_t)Ntot * sizeof(double));
-    const size_t max_items = (size_t)(Ntot / kMatTargets) + (size_t)S + 1;  // items of 64 or more targets
-    size_t items = max_items;
+    size_t items = (size_t)(Ntot / kMatTargets) + (size_t)S + 1;  // items of 64 or more targets
     if (split) {
         const bool mat = default_shape(Ntot, std::max(k, 1), prec).mat;
-        const int parts = batched_parts(Ntot, mat);
+        const int parts = batched_parts(Ntot / (mat ? kMatTargets : kBlock) + 1, mat);
         if (parts > 1) {
-            items = (mat ? max_items : (size_t)(Ntot / kBlock) + (size_t)S + 1) * parts;
+            items += kBatchedItems;
             b += align_up((size_t)parts * kernel_k(std::max(k, 1), prec, mat) * 3 * Ntot * sizeof(double));
+            b += align_up((size_t)Ntot * sizeof(int));
         }
     }
-    b += align_up(std::max(items, max_items) * sizeof(int4));
+    b += align_up(items * sizeof(int4));
     b += kAlign;  // counter
     return b + 4 * kAlign;
 }
@@ -1058,12 +1048,6 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     sh.sym = 0;
     sh = apply_env_overrides(sh);
     sh = normalized(sh, kernel_k(sh.kblk, prec, sh.mat), prec);
-    // Work list in LPT order: systems by decreasing size, then their tiles.
-    std::vector<int> order(S);
-    for (int s = 0; s < S; ++s) order[s] = s;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        return sys_offsets[x + 1] - sys_offsets[x] > sys_offsets[y + 1] - sys_offsets[y];
-    });
     const int span = sh.mat ? kMatTargets : kBlock * sh.tpl;
     const int tile = !sh.mat ? (sh.tile == 64 ? 64 : 256)
                      : prec == RPYW_FP32C ? mat_tile<float>() : mat_tile<double>();
@@ -1074,22 +1058,30 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     void* rec = ar.take((size_t)Ntot * rw * real_size(prec));
     double* B = (double*)ar.take((size_t)Ntot * sizeof(double));
     unsigned* counter = (unsigned*)ar.take(sizeof(unsigned));
+    // items with one part (more than kBatchedItems systems are never split)
+    int64_t whole = std::max<int64_t>(Ntot / (sh.mat ? kMatTargets : kBlock) + 1, S);
+    if (S < kBatchedItems) {
+        int64_t n = 0;
+        for (int s = 0; s < S; ++s) n += (sys_offsets[s + 1] - sys_offsets[s] + span - 1) / span;
+        whole = std::max(whole, n);
+    }
     // the sources in one part if the workspace does not hold more
-    int parts = (int)std::min<int64_t>(batched_parts(Ntot, sh.mat), (nmax + tile - 1) / tile);
-    std::vector<int4> items;
+    int parts = batched_parts(whole, sh.mat);
+    const int64_t from = split_from(whole, sh.mat, nmax, span);
+    std::vector<BatchedItem> items;
+    static_assert(sizeof(BatchedItem) == sizeof(int4));
     int4* ditems = nullptr;
     double* part = nullptr;
+    int* used = nullptr;
     for (const size_t before = ar.used;; parts = 1) {
         ar.used = before;
-        items.clear();
-        for (int s : order) {
-            const int b0 = (int)sys_offsets[s], b1 = (int)sys_offsets[s + 1];
-            for (int p = 0; p < parts; ++p)
-                for (int t = b0; t < b1; t += span) items.push_back(make_int4(b0, b1, t, p));
-        }
+        parts = batched_items(sys_offsets, S, span, tile, parts, from, whole, items);
         ditems = (int4*)ar.take(items.size() * sizeof(int4));
-        part = parts > 1 ? (double*)ar.take((size_t)parts * K * 3 * Ntot * sizeof(double)) : nullptr;
-        if (parts == 1 || (ditems && part)) break;
+        if (parts == 1) break;
+        part = (double*)ar.take((size_t)parts * K * 3 * Ntot * sizeof(double));
+        used = (int*)ar.take((size_t)Ntot * sizeof(int));
+        if (ditems && part && used) break;
+        part = nullptr;
     }
     if (!rec || !B || !ditems || !counter) {
         ar.used = mark;
@@ -1119,21 +1111,21 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
         profile_begin(st, &ev);
         hipError_t e;
         if (sh.mat)
-            e = launch_mat_batched(prec, K, rec, ditems, (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+            e = launch_mat_batched(prec, K, rec, ditems, (int)items.size(), counter, B, m0, Ntot, kb, Uk, part, used,
                                    grid, st);
         else if (prec == RPYW_FP32C)
             e = RPYW_DISPATCH(float, K, sh.tpl, sh.tile, launch_batched_t, (const float*)rec, ditems,
-                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, part, used,
                                    grid, st);
         else
             e = RPYW_DISPATCH(double, K, sh.tpl, sh.tile, launch_batched_t, (const double*)rec, ditems,
-                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, parts, part,
+                              (int)items.size(), counter, B, m0, Ntot, kb, Uk, part, used,
                                    grid, st);
         if (e != hipSuccess) return RPYW_EHIP;
         profile_end(st, ev, kb * pairs);
         if (parts > 1) {
             hipLaunchKernelGGL(epilogue_kernel, dim3((unsigned)((Ntot + 63) / 64), (unsigned)(3 * kb)),
-                               dim3(64 * kEpiParts), 0, st, part, B, Ntot, K, parts, m0, Uk);
+                               dim3(64 * kEpiParts), 0, st, part, B, Ntot, K, parts, m0, Uk, used);
             RPYW_HIP(hipGetLastError());
         }
     }

@@ -50,3 +50,19 @@ def test_velocities_on_top_of_forces(rp, orc, N, k, prec):
         u = _t(F[0])
         rp.matvec_noalloc(_t(pos), u, 0.9, 1.3, precision=prec, out=u)
         check(u.cpu().numpy(), orc.matvec(pos, F[0], 0.9, 1.3), TOL[prec], f"in place, noalloc N={N}")
+
+
+@pytest.mark.parametrize("prec,k", [(0, 1), (0, 8), (0, 16), (1, 1), (1, 16)])
+def test_batched_small_systems_beside_a_large_one(rp, orc, prec, k):
+    """Systems of fewer shares than the largest one's parts: the sums of the
+    parts that they do not use are zero whatever the workspace held."""
+    sizes = [2500] + [1, 5, 64, 65, 130, 700] * 4
+    offs = np.r_[0, np.cumsum(sizes)]
+    pos = np.concatenate([0.9 * _mixed(n, n) for n in sizes])
+    F = np.random.default_rng(k).standard_normal((k, offs[-1], 3))
+    junk = torch.full((1 << 26,), float("nan"), dtype=torch.float64, device="cuda")
+    del junk  # the allocator hands this memory to the call's workspace
+    U = rp.matvec_batched(_t(pos), offs, _t(F), 0.9, 1.3, precision=prec).cpu().numpy()
+    for a, b in zip(offs, offs[1:8]):
+        for j in {0, k - 1}:
+            check(U[j, a:b], orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec], f"system of {b - a} k={k} rhs {j}")
