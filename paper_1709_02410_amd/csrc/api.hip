@@ -117,10 +117,7 @@ Shape default_shape(int64_t N, int k, int prec) {
     Shape s;
     s.tpl = N >= 65536 ? 2 : 1;
     s.tile = 64;
-    // FP64: blocks of up to 8 on the vector units; 9 to 16 right-hand sides
-    // go to the matrix cores as one block of 16 (a block of 8 there would
-    // leave half of every contraction empty).
-    s.kblk = std::min(kclass(k), prec == RPYW_FP32C ? 16 : (kclass(k) > 8 ? 16 : 8));
+    s.kblk = widest_block(k, prec);
     s.sym = (s.kblk == 1 && N >= 512) ? (N <= kSym64MaxN ? 2 : 1) : 0;
     const int64_t ng = (N + 255) / 256, items = (ng / 2 + 1) * ng;
     s.ipw = s.sym == 2   ? 1
@@ -227,6 +224,10 @@ void set_shape_override(int64_t N, int k, int prec, Shape s) {
 void clear_shape_override(int64_t N, int k, int prec) {
     std::lock_guard<std::mutex> lk(g_shape_mu);
     g_overrides.erase({prec, size_class(N), kclass(k)});
+}
+
+int widest_block(int k, int prec) {
+    return std::min(kclass(k), prec == RPYW_FP32C ? 16 : (kclass(k) > 8 ? 16 : 8));
 }
 
 bool profiling_enabled() { return g_prof; }

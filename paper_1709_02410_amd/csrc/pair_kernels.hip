@@ -1046,6 +1046,7 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
     // RPYW_TILE / RPYW_RHS_WIDTH overrides still apply.
     Shape sh = default_shape(nmax, k, prec);
     sh.sym = 0;
+    sh.kblk = widest_block(k, prec);
     sh = apply_env_overrides(sh);
     sh = normalized(sh, kernel_k(sh.kblk, prec, sh.mat), prec);
     const int span = sh.mat ? kMatTargets : kBlock * sh.tpl;

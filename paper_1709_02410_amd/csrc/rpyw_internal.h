@@ -156,6 +156,11 @@ int batched_products(const double* pos, const int64_t* sys_offsets, int S, const
 
 // Shape selection.
 Shape default_shape(int64_t N, int k, int prec);
+// The widest block that takes k right-hand sides at once.  FP64: blocks of up
+// to 8 on the vector units; 9 to 16 right-hand sides go to the matrix cores as
+// one block of 16 (a block of 8 there would leave half of every contraction
+// empty).
+int widest_block(int k, int prec);
 // The launch shape products of N blobs and k right-hand sides use: the one
 // fixed by rpy_wall_set_shape for this (precision, size class, RHS class) if
 // any, else the tuned one, else the built-in default; then the RPYW_TILE /

@@ -66,3 +66,23 @@ def test_batched_small_systems_beside_a_large_one(rp, orc, prec, k):
     for a, b in zip(offs, offs[1:8]):
         for j in {0, k - 1}:
             check(U[j, a:b], orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec], f"system of {b - a} k={k} rhs {j}")
+
+
+@pytest.mark.parametrize("sizes", [(700, 40), (3000, 1, 520)])
+@pytest.mark.parametrize("prec,k", [(0, 5), (0, 6), (0, 7), (1, 5)])
+def test_batched_five_and_six_right_hand_sides(rp, orc, sizes, prec, k):
+    """One pass over the pairs, as for 7 and 8, in a block of 8."""
+    offs = np.r_[0, np.cumsum(sizes)]
+    pos = np.concatenate([0.9 * _mixed(n, n) for n in sizes])
+    F = np.random.default_rng(k).standard_normal((k, offs[-1], 3))
+    rp.profile_enable(True)
+    try:
+        rp.profile_read(reset=True)
+        U = rp.matvec_batched(_t(pos), offs, _t(F), 0.9, 1.3, precision=prec).cpu().numpy()
+        launches = rp.profile_read(reset=True)[1]
+    finally:
+        rp.profile_enable(False)
+    assert launches == 1
+    for a, b in zip(offs, offs[1:]):
+        for j in (0, 3, k - 1):
+            check(U[j, a:b], orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec], f"system of {b - a} k={k} rhs {j}")
