@@ -110,9 +110,10 @@ int64_t g_prof_n = 0;
 // against 7.74 to 7.88 with four and no tail; six below 32768 items leave too
 // few workgroups (0.908 against 0.868 ms at 33000).  In FP64 two targets
 // per lane (sym_multi.h) make the symmetric kernel the faster one for up to
-// four right-hand sides as well; 5 or 6 right-hand sides go in a block of 4
-// and the rest (at 3840 blobs 85 and 92 against 102 us for one block of 8 on
-// the plain kernel, at 20000 1.67 and 1.85 against 2.01 ms; 7 take longer).
+// four right-hand sides as well; above kSym2MinN5 blobs 5 or 6 go in a block of 4
+// and the rest (five: 76.7 us for one block of 8 on the plain kernel against 81.0
+// at 3300 blobs, 93.3 against 81.8 at 3400, 1.96 against 1.67 ms at 20000; six:
+// 78.5 and 91.0, 95.0 and 92.0, 1.99 and 1.85; 7 take longer).
 Shape default_shape(int64_t N, int k, int prec) {
     Shape s;
     s.tpl = N >= 65536 ? 2 : 1;
@@ -124,9 +125,11 @@ Shape default_shape(int64_t N, int k, int prec) {
             : s.sym == 1 ? (items < 32768 ? 4 : 6)
                          : (int)std::max<int64_t>(1, std::min<int64_t>(4, items / 16384));
     s.mat = (s.kblk >= (prec == RPYW_FP32C ? 8 : 16)) ? 1 : 0;
-    if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : 512) && k <= 6 && N <= (k == 1 ? kSym2MaxN1 : kSym2MaxN)) {
+    if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : k <= 4 ? 512 : kSym2MinN5) && k <= 6 &&
+        N <= (k == 1 ? kSym2MaxN1 : kSym2MaxN)) {
         s.kblk = std::min(s.kblk, 4);
-        if (!s.sym) s.sym = 1;
+        // (the one right-hand side left of five goes over groups as for k = 1)
+        if (!s.sym) s.sym = N <= kSym64MaxN ? 2 : 1;
         // source groups per workgroup: the target side is loaded and written
         // less often while the grid still has rounds to spare (one and two:
         // 30.9 and 34.7 us at 3840 blobs, 100.6 and 100.5 at 8000, 575 and

@@ -83,6 +83,7 @@ constexpr size_t kSymPartialMaxBytes = (size_t)16 << 30;
 // half the partials.  With more right-hand sides: up to kSym2MaxN (beyond it
 // the plain kernel).
 constexpr int64_t kSym2MinN1 = 3584;
+constexpr int64_t kSym2MinN5 = 3329;  // five or six right-hand sides (14 blocks of 256 targets of the plain kernel)
 constexpr int64_t kSym2MaxN1 = 32768;
 constexpr int64_t kSym2MaxN = 131072;
 // Plan for groups of G blobs; ok is false when N or K is out of its range.

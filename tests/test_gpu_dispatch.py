@@ -86,3 +86,15 @@ def test_batched_five_and_six_right_hand_sides(rp, orc, sizes, prec, k):
     for a, b in zip(offs, offs[1:]):
         for j in (0, 3, k - 1):
             check(U[j, a:b], orc.matvec(pos[a:b], F[j, a:b], 0.9, 1.3), TOL[prec], f"system of {b - a} k={k} rhs {j}")
+
+
+@pytest.mark.parametrize("N", [1537, 2049, 3328, 3329, 3583, 3584])
+@pytest.mark.parametrize("k", [5, 6])
+def test_five_and_six_right_hand_sides(rp, orc, N, k):
+    """FP64, both sides of the line between one block of 8 and 4 + the rest,
+    whose single right-hand side takes groups of 64 and of 128."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + k).standard_normal((k, N, 3))
+    U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=0).cpu().numpy()
+    for j in (0, 3, k - 1):
+        check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"N={N} k={k} rhs {j}")
