@@ -658,8 +658,11 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             if (cand >= 6) sh = Shape{1 + ((cand - 6) & 1), ((cand - 6) & 2) ? 256 : 64, kb, 0, 4};
             if (cand >= 6 && kb >= 8 && sh.tpl == 2) continue;
             if (cand < 6 && kb > 4) continue;
-            // FP64: one symmetric kernel from here on
-            if (sh.sym == 2 && (N > kSym64MaxN || (precision == RPYW_FP64 && (kb > 1 || N >= kSym2MinN1)))) continue;
+            if (sh.sym == 2 && N > kSym64MaxN) continue;
+            // where both values of sym are the kernel over groups of 128 (FP64),
+            // the one that also means groups of 64 for smaller problems of the
+            // class, single right-hand sides, derivatives and periodic products
+            if (sh.sym == 1 && N <= kSym64MaxN && precision == RPYW_FP64 && (kb > 1 || N >= kSym2MinN1)) continue;
             if (cand == 6 && kb >= 8) {
                 Shape m{1, 64, kb, 0, 4};
                 m.mat = 1;

@@ -98,3 +98,44 @@ def test_five_and_six_right_hand_sides(rp, orc, N, k):
     U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=0).cpu().numpy()
     for j in (0, 3, k - 1):
         check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[0], f"N={N} k={k} rhs {j}")
+
+
+TUNED_PROBE = """
+import sys
+sys.path.insert(0, {root!r})
+import numpy as np, torch
+from paper_1709_02410_amd import rpywall as rp
+def t(x): return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float64, device="cuda")
+def cloud(n):
+    rng = np.random.default_rng(n)
+    b = 2.0 * np.sqrt(n)
+    return t(np.column_stack([rng.uniform(0, b, n), rng.uniform(0, b, n), rng.uniform(0.3, 4.0, n)]))
+{body}
+"""
+
+
+def _tuned_probe(body, env=None):
+    """body in a process of its own: tuned shapes last as long as the process."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    e = {k: v for k, v in os.environ.items() if not k.startswith("RPYW_")}
+    r = subprocess.run([sys.executable, "-c", TUNED_PROBE.format(root=root, body=body)], env={**e, **(env or {})},
+                       capture_output=True, text=True, timeout=100)
+    print(r.stdout[-2000:], flush=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return r
+
+
+def test_tuned_fp64_shapes_keep_the_other_calls_on_groups_of_64(rp):
+    """The tuner at a size where every symmetric FP64 product is the kernel over
+    groups of 128: what else reads the shape stays over groups of 64."""
+    _tuned_probe('''
+for n, k in ((3840, 1), (20000, 1), (3400, 5)):
+    p = cloud(n)
+    rp.autotune(p, torch.ones((k, n, 3), dtype=torch.float64, device="cuda"), precision=0)
+    s = rp.get_shape(0, n, k)
+    print(n, k, s, flush=True)
+    assert s["sym"] != 1, s
+''')
