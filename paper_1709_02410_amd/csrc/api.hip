@@ -120,10 +120,6 @@ Shape default_shape(int64_t N, int k, int prec) {
     s.tile = 64;
     s.kblk = widest_block(k, prec);
     s.sym = (s.kblk == 1 && N >= 512) ? (N <= kSym64MaxN ? 2 : 1) : 0;
-    const int64_t ng = (N + 255) / 256, items = (ng / 2 + 1) * ng;
-    s.ipw = s.sym == 2   ? 1
-            : s.sym == 1 ? (items < 32768 ? 4 : 6)
-                         : (int)std::max<int64_t>(1, std::min<int64_t>(4, items / 16384));
     s.mat = (s.kblk >= (prec == RPYW_FP32C ? 8 : 16)) ? 1 : 0;
     if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : k <= 4 ? 512 : kSym2MinN5) && k <= 6 &&
         N <= (k == 1 ? kSym2MaxN1 : kSym2MaxN)) {
@@ -135,8 +131,15 @@ Shape default_shape(int64_t N, int k, int prec) {
         // 30.9 and 34.7 us at 3840 blobs, 100.6 and 100.5 at 8000, 575 and
         // 574 at 20000; four right-hand sides 1123 and 1093 there)
         const int64_t g = (N + 127) / 128, items = g * (g / 2 + 1);
-        s.ipw = items < 2048 ? 1 : items < 32768 ? 2 : 4;
+        s.ipw2 = items < 2048 ? 1 : items < 32768 ? 2 : 4;
     }
+    const int64_t ng = (N + 255) / 256, items = (ng / 2 + 1) * ng;
+    // (groups of 64, FP64: two source groups for VJPs and periodic products of
+    // 30000 blobs 4.55 and 9.47 ms, one 4.65 and 9.54; of 10000 577 and 1180 us,
+    // one 545 and 1104)
+    s.ipw = s.sym == 2   ? (prec == RPYW_FP64 && N >= 28672 ? 2 : 1)
+            : s.sym == 1 ? (items < 32768 ? 4 : 6)
+                         : (int)std::max<int64_t>(1, std::min<int64_t>(4, items / 16384));
     return s;
 }
 
@@ -239,8 +242,8 @@ bool profiling_enabled() { return g_prof; }
 // its products use, and the status.
 void log_shape(const char* fn, int64_t N, int k, int prec, int rc) {
     const Shape sh = tuned_shape(N, k, prec);
-    log_line("%s N=%lld k=%d prec=%d shape tpl=%d tile=%d kblk=%d sym=%d ipw=%d mat=%d status=%d", fn, (long long)N, k,
-             prec, sh.tpl, sh.tile, sh.kblk, sh.sym, sh.ipw, sh.mat, rc);
+    log_line("%s N=%lld k=%d prec=%d shape tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d status=%d", fn,
+             (long long)N, k, prec, sh.tpl, sh.tile, sh.kblk, sh.sym, sh.ipw, sh.ipw2, sh.mat, rc);
 }
 
 void profile_begin(hipStream_t st, hipEvent_t* ev) {
@@ -658,6 +661,11 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             if (cand >= 6) sh = Shape{1 + ((cand - 6) & 1), ((cand - 6) & 2) ? 256 : 64, kb, 0, 4};
             if (cand >= 6 && kb >= 8 && sh.tpl == 2) continue;
             if (cand < 6 && kb > 4) continue;
+            // (of groups of 128 the ipw is tuned, that of the other calls is left)
+            if (sh.sym && precision == RPYW_FP64 && N <= kSym2MaxN && (kb > 1 || (N >= kSym2MinN1 && N <= kSym2MaxN1))) {
+                sh.ipw2 = sh.ipw;
+                sh.ipw = default_shape(N, 1, precision).ipw;
+            }
             if (sh.sym == 2 && N > kSym64MaxN) continue;
             // where both values of sym are the kernel over groups of 128 (FP64),
             // the one that also means groups of 64 for smaller problems of the
@@ -709,8 +717,9 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
         std::lock_guard<std::mutex> lk(g_shape_mu);
         save_cache_locked();
     }
-    log_line("rpy_wall_autotune N=%lld k=%d prec=%d -> tpl=%d tile=%d kblk=%d sym=%d ipw=%d mat=%d (%.4f ms)",
-             (long long)N, k, precision, best.tpl, best.tile, best.kblk, best.sym, best.ipw, best.mat, best_t / 2.0);
+    log_line("rpy_wall_autotune N=%lld k=%d prec=%d -> tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d (%.4f ms)",
+             (long long)N, k, precision, best.tpl, best.tile, best.kblk, best.sym, best.ipw, best.ipw2, best.mat,
+             best_t / 2.0);
     return RPYW_OK;
 }
 
@@ -738,6 +747,7 @@ int rpy_wall_get_shape(int precision, int64_t N, int32_t k, int32_t* out6) {
     if (K >= 8) s.tpl = 1;
     if (K > 4) s.sym = 0;
     if (K < 8) s.mat = 0;
+    if (s.sym) s.ipw = sym_choose(N, precision, K, s, Domain{}).G == 128 && s.ipw2 ? s.ipw2 : s.ipw;
     out6[0] = s.tpl;
     out6[1] = s.tile;
     out6[2] = s.kblk;

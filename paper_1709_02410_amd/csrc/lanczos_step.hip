@@ -525,9 +525,11 @@ bool lanczos_fused_applies(int64_t N, int prec, int max_iter, const Domain& dom,
     // below the sizes of symmetric products: their vector work is fused with it
     // (rigid solves of 60 to 500 blobs 175 -> 120 us, roots 768 -> 494 us at 60
     // and 1593 -> 998 us at 500).
-    const Shape sh = tuned_shape(N, 1, prec);
+    Shape sh = tuned_shape(N, 1, prec);
     if (!dom.periodic() && !(sh.sym && sh.kblk <= 4) && !sh.direct) return false;
-    *sp = sym_choose(N, prec, 1, sh.ipw < 1 ? 4 : sh.ipw, sh.sym || !sh.direct ? sh.sym : 2, dom);
+    if (sh.ipw < 1) sh.ipw = 4;
+    if (!sh.sym && sh.direct) sh.sym = 2;
+    *sp = sym_choose(N, prec, 1, sh, dom);
     return sp->ok;
 }
 

@@ -693,19 +693,19 @@ SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G) {
     return s;
 }
 
-SymPlan sym_choose(int64_t N, int prec, int K, int ipw, int sym, const Domain& dom) {
+SymPlan sym_choose(int64_t N, int prec, int K, const Shape& sh, const Domain& dom) {
     if (prec == RPYW_FP64 && !dom.periodic()) {
-        const SymPlan s = sym_plan(N, prec, K, ipw, 128);
+        const SymPlan s = sym_plan(N, prec, K, sh.ipw2 ? sh.ipw2 : sh.ipw, 128);
         if (s.ok || K > 1) return s;
     }
     // Periodic products are always symmetric: groups of 64 unless the shape
     // asks for groups of 256.
-    const bool g64 = dom.periodic() ? sym != 1 : sym == 2;
+    const bool g64 = dom.periodic() ? sh.sym != 1 : sh.sym == 2;
     if (g64) {
-        const SymPlan s = sym_plan(N, prec, K, ipw, 64);
+        const SymPlan s = sym_plan(N, prec, K, sh.ipw, 64);
         if (s.ok) return s;
     }
-    return sym_plan(N, prec, K, ipw, 256);
+    return sym_plan(N, prec, K, sh.ipw, 256);
 }
 
 void split_plan(int64_t N, int tpl, int* splits, int64_t* chunk) {
@@ -888,7 +888,7 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     if (kb < 1 || kb > K) return RPYW_EINVAL;
     sh = normalized(sh, K, prec);
     if (sh.sym && K <= 4) {
-        const SymPlan sp = sym_choose(N, prec, K, sh.ipw, sh.sym, Domain{});
+        const SymPlan sp = sym_choose(N, prec, K, sh, Domain{});
         if (sp.ok) return sym_pass(pos, F, U, N, kb, K, a, eta, prec, sp, ar, st);
     }
     const int rw = rec_width(prec, K);
@@ -980,9 +980,9 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
         // two, FP32C and FP64: 1202 blobs 39.6 -> 25.3 and 50.7 -> 33.6 us, 20000
         // blobs 5.10 -> 3.52 and 9.2 -> 5.8 ms.
         const Shape sh = tuned_shape(N, 1, prec);
-        const SymPlan sp = sym_choose(N, prec, 1, sh.ipw, sh.sym, dom);
+        const SymPlan sp = sym_choose(N, prec, 1, sh, dom);
         if (!sp.ok) return RPYW_ENOMEM;
-        const SymPlan sp2 = sym_choose(N, prec, 2, sh.ipw, sh.sym, dom);
+        const SymPlan sp2 = sym_choose(N, prec, 2, sh, dom);
         bool two = sp2.ok && sp2.G == 64 && sp.G == 64;
         for (int k0 = 0; k0 < k;) {
             const double* Fk = F + (size_t)k0 * N * 3;

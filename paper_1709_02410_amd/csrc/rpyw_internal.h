@@ -29,6 +29,7 @@ struct Shape {
     int kblk;  // right-hand sides per pass: 1, 2, 4, 8 or 16
     int sym;   // symmetric pair evaluation (kblk <= 4): 0 off, 1 groups of 256 blobs, 2 groups of 64
     int ipw;   // symmetric path: source groups per workgroup
+    int ipw2 = 0;  // the same over groups of 128 (0: ipw); the FP64 VJP and periodic products share sym and ipw
     int mat = 0;  // FP32C blocks of 8 or 16 right-hand sides: contraction on the matrix cores
     bool direct = false;  // small FP64 products in one launch (direct_pairs.h); never of a fixed shape
 };
@@ -89,10 +90,10 @@ constexpr int64_t kSym2MaxN = 131072;
 // Plan for groups of G blobs; ok is false when N or K is out of its range.
 SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G);
 inline int sym_group(int sym) { return sym == 2 ? 64 : 256; }
-// The plan a symmetric product uses: `sym` as in Shape; FP64 products in the
-// open domain take groups of 128 within their range, whichever sym asks for.
+// The plan a symmetric product uses (sym, ipw, ipw2 of the shape); FP64 products
+// in the open domain take groups of 128 within their range, whichever sym asks for.
 // not ok: no symmetric kernel for this size.
-SymPlan sym_choose(int64_t N, int prec, int K, int ipw, int sym, const Domain& dom);
+SymPlan sym_choose(int64_t N, int prec, int K, const Shape& sh, const Domain& dom);
 // The three stages of a symmetric product pass, for callers that keep the
 // records between passes (the Krylov solvers):
 //   sym_pack   records (positions, wrapped into the cell when periodic, and

@@ -175,7 +175,9 @@ int read_shape_cache(const char* path, std::vector<CachedShape>& out) {
             field_int(obj, "size_class", &c.size_class) && field_int(obj, "k", &c.kclass) &&
             field_int(obj, "tpl", &c.s.tpl) && field_int(obj, "tile", &c.s.tile) &&
             field_int(obj, "kblk", &c.s.kblk) && field_int(obj, "sym", &c.s.sym) && field_int(obj, "ipw", &c.s.ipw)) {
-            if (!field_int(obj, "mat", &c.s.mat)) c.s.mat = 0;  // entries written before the field existed
+            // entries written before the fields existed
+            if (!field_int(obj, "mat", &c.s.mat)) c.s.mat = 0;
+            if (!field_int(obj, "ipw2", &c.s.ipw2) || c.s.ipw2 < 0) c.s.ipw2 = 0;
             out.push_back(c);
         }
         p = b + 1;
@@ -192,9 +194,9 @@ int write_shape_cache(const char* path, const std::vector<CachedShape>& entries)
         const CachedShape& c = entries[i];
         std::fprintf(f,
                      "%s\n  {\"arch\": \"%s\", \"precision\": %d, \"size_class\": %d, \"k\": %d, \"tpl\": %d, "
-                     "\"tile\": %d, \"kblk\": %d, \"sym\": %d, \"ipw\": %d, \"mat\": %d}",
+                     "\"tile\": %d, \"kblk\": %d, \"sym\": %d, \"ipw\": %d, \"ipw2\": %d, \"mat\": %d}",
                      i ? "," : "", c.arch.c_str(), c.prec, c.size_class, c.kclass, c.s.tpl, c.s.tile, c.s.kblk,
-                     c.s.sym, c.s.ipw, c.s.mat);
+                     c.s.sym, c.s.ipw, c.s.ipw2, c.s.mat);
     }
     std::fprintf(f, "\n]}\n");
     const bool ok = std::fclose(f) == 0;

@@ -139,3 +139,47 @@ for n, k in ((3840, 1), (20000, 1), (3400, 5)):
     print(n, k, s, flush=True)
     assert s["sym"] != 1, s
 ''')
+
+
+def _other_calls(rp, n):
+    """What else reads the FP64 shape of one right-hand side: VJP, periodic
+    product, and the product of a smaller problem of the size class."""
+    pos, f = _t(_mixed(n, n)), _t(np.random.default_rng(n).standard_normal((n, 3)))
+    return (*rp.matvec_vjp(pos, f, f), rp.matvec_periodic(pos, f[None], (250.0, 260.0)))
+
+
+@pytest.mark.parametrize("N", [8300, 16500])
+def test_source_groups_of_the_128_kernel_are_its_own(rp, N):
+    """FP64 products over groups of 128 take two source groups to a workgroup
+    here, VJPs and periodic products over groups of 64 one: their sums are to
+    the bit those of that shape."""
+    assert rp.get_shape(0, N, 1)["ipw"] == 2
+    got = _other_calls(rp, N)
+    rp.set_shape(0, N, 1, tpl=1, tile=256, kblk=1, sym=2, ipw=1)
+    try:
+        ref = _other_calls(rp, N)
+    finally:
+        rp.reset_shape(0, N, 1)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_tuning_leaves_the_other_calls_alone(rp, tmp_path):
+    """... also after a tuning (of the groups of 128), and from its cache file."""
+    body = '''
+def other(n):
+    p, f = cloud(n), torch.ones((n, 3), dtype=torch.float64, device="cuda")
+    return (*rp.matvec_vjp(p, f, f), rp.matvec_periodic(p, f[None], (250.0, 260.0)))
+before = other(3840), other(9000), rp.matvec(cloud(3000), torch.ones((3000, 3), dtype=torch.float64, device="cuda"))
+if {tune}:
+    for n in (3840, 9000):
+        rp.autotune(cloud(n), torch.ones((1, n, 3), dtype=torch.float64, device="cuda"), precision=0)
+for n in (3840, 9000): print(n, rp.get_shape(0, n, 1), flush=True)
+after = other(3840), other(9000), rp.matvec(cloud(3000), torch.ones((3000, 3), dtype=torch.float64, device="cuda"))
+flat = lambda x: [z for y in x for z in (y if isinstance(y, tuple) else (y,))]
+if {tune}: torch.save(flat(before), {file!r})
+assert all(torch.equal(a, b) for a, b in zip(flat(after), torch.load({file!r})))
+'''
+    env = {"RPYW_AUTOTUNE_CACHE": str(tmp_path / "shapes.json")}
+    first = _tuned_probe(body.format(tune=True, file=str(tmp_path / "ref.pt")), env)
+    again = _tuned_probe(body.format(tune=False, file=str(tmp_path / "ref.pt")), env)
+    assert first.stdout == again.stdout
