@@ -337,7 +337,8 @@ const char* rpyw_strerror(int status);
  * symmetric or plain kernel) of the pair kernels for problems of this size
  * by timing the candidates on the given inputs; the result is kept for the
  * rest of the process and is used by every later call of the same precision
- * and size class.  Candidates are tried in a fixed order of preference and
+ * and size class.  FP64 products of small problems in one launch (see
+ * rpy_wall_get_shape) are a candidate.  Candidates are tried in a fixed order of preference and
  * a later one must be at least 1.5% faster to replace an earlier one, so
  * near-ties are resolved the same way from run to run.  Inputs as for
  * rpy_wall_matvec_multi (k RHS); blocks until the timing is done. */
@@ -369,10 +370,12 @@ int rpy_wall_set_shape(int precision, int64_t N, int32_t k, int32_t tpl, int32_t
 
 /* The launch shape later products of this precision and size class will
  * use: out6 = {tpl, tile, kblk, sym, ipw, mat} (HOST int32[6]), as for
- * rpy_wall_set_shape.  Host-only.  Without a fixed shape, FP64 products of
- * small problems (up to 2048 blobs for k <= 4, 1536 for k <= 8, else 1280) run
- * in one launch instead, which has no shape; the Lanczos, rigid and VJP calls
- * of these sizes use the shape. */
+ * rpy_wall_set_shape.  Host-only.  FP64 products of small problems (up to 2048
+ * blobs for k <= 4, 1536 for k <= 8, else 1280) run in one launch instead,
+ * which has no shape, unless one is fixed, tuned (the tuner keeps the faster of
+ * the two; so does its cache file) or RPYW_TILE or RPYW_RHS_WIDTH is set; the
+ * Lanczos, rigid and VJP calls of these sizes use the shape (below 512 blobs
+ * the symmetric kernel over groups of 64, where the products take one launch). */
 int rpy_wall_get_shape(int precision, int64_t N, int32_t k, int32_t* out6);
 
 /* Host-only: coefficients c = beta0 T^{1/2} e1 = beta0 Q Lambda^{1/2} Q^T e1

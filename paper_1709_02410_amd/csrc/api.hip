@@ -98,6 +98,17 @@ int64_t g_prof_n = 0;
 
 }  // namespace
 
+// FP64 products of this size run in one launch (direct_pairs.h), unless the
+// tuner found another shape faster or one is fixed.  The lines lie where the
+// other kernels catch up (us a call): one right-hand side 14.8 against 17.3 at
+// 2000 blobs, 21.3 against 21 at 2500; two 18.1 against 23, 27 against 27; four 28.6 against 31, 39.8
+// against 39; eight 35.4 against 44.7 at 1500, 52.2 against 47.6 at 2000 (plain);
+// sixteen, in two blocks of 8, 33 against 73 at 1000, 70.7 against 67.7 at 1500
+// (matrix cores).
+static bool direct_rule(int64_t N, int k, int prec) {
+    return prec == RPYW_FP64 && N <= (k <= 4 ? 2048 : k <= 8 ? 1536 : 1280);
+}
+
 // Defaults from measurements on MI355X: the symmetric kernel wins for one
 // right-hand side from a few hundred blobs up (1.7x at 1e5, 2x at 1000,
 // where its passes are also split into segments); groups of
@@ -119,6 +130,7 @@ Shape default_shape(int64_t N, int k, int prec) {
     s.tpl = N >= 65536 ? 2 : 1;
     s.tile = 64;
     s.kblk = widest_block(k, prec);
+    s.direct = direct_rule(N, k, prec);
     s.sym = (s.kblk == 1 && N >= 512) ? (N <= kSym64MaxN ? 2 : 1) : 0;
     s.mat = (s.kblk >= (prec == RPYW_FP32C ? 8 : 16)) ? 1 : 0;
     if (prec == RPYW_FP64 && N >= (k == 1 ? kSym2MinN1 : k <= 4 ? 512 : kSym2MinN5) && k <= 6 &&
@@ -141,17 +153,6 @@ Shape default_shape(int64_t N, int k, int prec) {
             : s.sym == 1 ? (items < 32768 ? 4 : 6)
                          : (int)std::max<int64_t>(1, std::min<int64_t>(4, items / 16384));
     return s;
-}
-
-// FP64 products of this size run in one launch (direct_pairs.h) unless a
-// shape is fixed.  The lines lie where the other kernels catch up (us a
-// call): one right-hand side 14.8 against 17.3 at 2000 blobs, 21.3 against
-// 21 at 2500; two 18.1 against 23, 27 against 27; four 28.6 against 31, 39.8
-// against 39; eight 35.4 against 44.7 at 1500, 52.2 against 47.6 at 2000 (plain);
-// sixteen, in two blocks of 8, 33 against 73 at 1000, 70.7 against 67.7 at 1500
-// (matrix cores).
-static bool direct_rule(int64_t N, int k, int prec) {
-    return prec == RPYW_FP64 && N <= (k <= 4 ? 2048 : k <= 8 ? 1536 : 1280);
 }
 
 namespace {
@@ -211,9 +212,9 @@ Shape tuned_shape(int64_t N, int k, int prec) {
     auto ov = g_overrides.find(key);
     if (ov != g_overrides.end()) return apply_env_overrides(ov->second);
     auto it = g_shapes.find(key);
-    Shape s = apply_env_overrides(it != g_shapes.end() ? it->second : default_shape(N, k, prec));
-    s.direct = direct_rule(N, k, prec);
-    return s;
+    Shape s = it != g_shapes.end() ? it->second : default_shape(N, k, prec);
+    s.direct = s.direct && direct_rule(N, k, prec);  // tuned at another size of the class
+    return apply_env_overrides(s);
 }
 
 void set_tuned_shape(int64_t N, int k, int prec, Shape s) {
@@ -242,8 +243,9 @@ bool profiling_enabled() { return g_prof; }
 // its products use, and the status.
 void log_shape(const char* fn, int64_t N, int k, int prec, int rc) {
     const Shape sh = tuned_shape(N, k, prec);
-    log_line("%s N=%lld k=%d prec=%d shape tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d status=%d", fn,
-             (long long)N, k, prec, sh.tpl, sh.tile, sh.kblk, sh.sym, sh.ipw, sh.ipw2, sh.mat, rc);
+    log_line("%s N=%lld k=%d prec=%d shape tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d direct=%d status=%d",
+             fn,
+             (long long)N, k, prec, sh.tpl, sh.tile, sh.kblk, sh.sym, sh.ipw, sh.ipw2, sh.mat, sh.direct, rc);
 }
 
 void profile_begin(hipStream_t st, hipEvent_t* ev) {
@@ -647,7 +649,7 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
     const bool prof = g_prof;
     g_prof = false;
     // Candidates in order of preference (least partial-sum traffic first):
-    // symmetric over groups of 256 with ipw 4, 2, 1, then (small problems)
+    // one launch for all (small FP64 problems), symmetric over groups of 256 with ipw 4, 2, 1, then (small problems)
     // over groups of 64 with ipw 4, 2, 1, then (FP32C blocks of 8 or more)
     // the matrix-core kernel, then plain (tpl, tile) in {1,2} x {64,256},
     // for every RHS block width.  Two timed rounds over all candidates (the
@@ -655,6 +657,8 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
     // round.  A later candidate must be faster by 1.5% to win, so near-ties
     // resolve the same way every time.
     std::vector<Shape> cands;
+    const bool direct = direct_rule(N, k, precision);
+    if (direct) cands.push_back(default_shape(N, k, precision));
     for (int kb = 1; kb <= std::min(kc, 16); kb <<= 1) {
         for (int cand = 0; cand < 10; ++cand) {
             Shape sh{1, 256, kb, cand < 3 ? 1 : 2, 4 >> (cand % 3)};
@@ -686,14 +690,10 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             float ms = 0.f;
             for (int rep = 0; rep < 3; ++rep) {
                 if (rep == 1) RPYW_HIP(hipEventRecord(e0, st));
-                for (int k0 = 0; k0 < k; k0 += cands[c].kblk) {
-                    const int n = std::min(cands[c].kblk, k - k0);
-                    rc = product_pass(pos, F + (size_t)k0 * N * 3, U + (size_t)k0 * N * 3, N, n, a, eta, precision,
-                                      cands[c], s.ar, st);
-                    if (rc != RPYW_OK) {
-                        g_prof = prof;
-                        return rc;
-                    }
+                rc = shaped_products(pos, F, U, N, k, a, eta, precision, cands[c], s.ar, st);
+                if (rc != RPYW_OK) {
+                    g_prof = prof;
+                    return rc;
                 }
             }
             RPYW_HIP(hipEventRecord(e1, st));
@@ -709,6 +709,8 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             best_t = tbest[c];
             best = cands[c];
         }
+    // not timed: the rule decides for smaller problems of the class
+    if (!direct && precision == RPYW_FP64) best.direct = true;
     g_prof = prof;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -717,9 +719,10 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
         std::lock_guard<std::mutex> lk(g_shape_mu);
         save_cache_locked();
     }
-    log_line("rpy_wall_autotune N=%lld k=%d prec=%d -> tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d (%.4f ms)",
+    log_line("rpy_wall_autotune N=%lld k=%d prec=%d -> tpl=%d tile=%d kblk=%d sym=%d ipw=%d ipw2=%d mat=%d direct=%d (%.4f "
+             "ms)",
              (long long)N, k, precision, best.tpl, best.tile, best.kblk, best.sym, best.ipw, best.ipw2, best.mat,
-             best_t / 2.0);
+             direct && best.direct, best_t / 2.0);
     return RPYW_OK;
 }
 

@@ -998,7 +998,11 @@ int products(const double* pos, const double* F, double* U, int64_t N, int k, do
         }
         return RPYW_OK;
     }
-    Shape sh = tuned_shape(N, k, prec);
+    return shaped_products(pos, F, U, N, k, a, eta, prec, tuned_shape(N, k, prec), ar, st);
+}
+
+int shaped_products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
+                    Shape sh, Arena& ar, hipStream_t st) {
     // One launch writes velocities while other workgroups still read: outputs
     // on top of the inputs take the other kernels, which read them all first.
     if (sh.direct && !overlap(U, 3 * N * k, F, 3 * N * k) && !overlap(U, 3 * N * k, pos, 3 * N))

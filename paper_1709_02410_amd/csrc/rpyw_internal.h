@@ -31,7 +31,7 @@ struct Shape {
     int ipw;   // symmetric path: source groups per workgroup
     int ipw2 = 0;  // the same over groups of 128 (0: ipw); the FP64 VJP and periodic products share sym and ipw
     int mat = 0;  // FP32C blocks of 8 or 16 right-hand sides: contraction on the matrix cores
-    bool direct = false;  // small FP64 products in one launch (direct_pairs.h); never of a fixed shape
+    bool direct = false;  // small FP64 products in one launch (direct_pairs.h), within its sizes
 };
 
 // Domain along the wall: open (lx = ly = 0) or the pseudo-periodic cell
@@ -149,6 +149,9 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
 // domain one right-hand side at a time through the symmetric kernel.
 int products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
              Arena& ar, hipStream_t st, const Domain& dom = Domain{});
+// The open-domain products with a given shape.
+int shaped_products(const double* pos, const double* F, double* U, int64_t N, int k, double a, double eta, int prec,
+                    Shape sh, Arena& ar, hipStream_t st);
 
 // Batched independent systems (persistent kernel, LPT work list).
 // split: with room for the sources in parts (batched_products does without).

@@ -131,6 +131,7 @@ Shape apply_env_overrides(Shape s) {
     const Env& e = env();
     if (e.tile) s.tile = e.tile;
     if (e.rhs_width) s.kblk = e.rhs_width;
+    if (e.tile || e.rhs_width) s.direct = false;  // which has neither
     return s;
 }
 
@@ -178,6 +179,8 @@ int read_shape_cache(const char* path, std::vector<CachedShape>& out) {
             // entries written before the fields existed
             if (!field_int(obj, "mat", &c.s.mat)) c.s.mat = 0;
             if (!field_int(obj, "ipw2", &c.s.ipw2) || c.s.ipw2 < 0) c.s.ipw2 = 0;
+            int direct = 0;
+            c.s.direct = field_int(obj, "direct", &direct) && direct == 1;
             out.push_back(c);
         }
         p = b + 1;
@@ -194,9 +197,10 @@ int write_shape_cache(const char* path, const std::vector<CachedShape>& entries)
         const CachedShape& c = entries[i];
         std::fprintf(f,
                      "%s\n  {\"arch\": \"%s\", \"precision\": %d, \"size_class\": %d, \"k\": %d, \"tpl\": %d, "
-                     "\"tile\": %d, \"kblk\": %d, \"sym\": %d, \"ipw\": %d, \"ipw2\": %d, \"mat\": %d}",
+                     "\"tile\": %d, \"kblk\": %d, \"sym\": %d, \"ipw\": %d, \"ipw2\": %d, \"mat\": %d, "
+                     "\"direct\": %d}",
                      i ? "," : "", c.arch.c_str(), c.prec, c.size_class, c.kclass, c.s.tpl, c.s.tile, c.s.kblk,
-                     c.s.sym, c.s.ipw, c.s.ipw2, c.s.mat);
+                     c.s.sym, c.s.ipw, c.s.ipw2, c.s.mat, c.s.direct ? 1 : 0);
     }
     std::fprintf(f, "\n]}\n");
     const bool ok = std::fclose(f) == 0;

@@ -141,6 +141,48 @@ for n, k in ((3840, 1), (20000, 1), (3400, 5)):
 ''')
 
 
+def test_small_fp64_products_obey_tuned_and_environment_shapes(rp, tmp_path):
+    """The one-launch products are the built-in choice and a candidate of the
+    tuner; a tuned shape without them, and RPYW_TILE or RPYW_RHS_WIDTH, are the
+    shape that runs: to the bit the product with that shape fixed."""
+    import json
+    path = tmp_path / "shapes.json"
+    body = '''
+import json, os
+out = {{}}
+for n, k in ((300, 1), (1000, 1), (1000, 2)):
+    f = torch.ones((k, n, 3), dtype=torch.float64, device="cuda")
+    out[n, k] = rp.matvec_multi(cloud(n), f)
+    s = rp.get_shape(0, n, k)
+    rp.set_shape(0, n, k, **s)
+    fixed = rp.matvec_multi(cloud(n), f)
+    rp.reset_shape(0, n, k)
+    assert torch.equal(out[n, k], fixed) == {obeys}, (n, k, s)
+vjp = rp.matvec_vjp(cloud(300), out[300, 1][0], out[300, 1][0])
+rp.set_shape(0, 300, 1, tpl=1, tile=64, kblk=1, sym=0, ipw=4)
+assert torch.equal(vjp[0], rp.matvec_vjp(cloud(300), out[300, 1][0], out[300, 1][0])[0]) == {obeys}
+rp.reset_shape(0, 300, 1)
+if {tune}:
+    for n, k in out: rp.autotune(cloud(n), torch.ones((k, n, 3), dtype=torch.float64, device="cuda"), precision=0)
+    for n, k in out:  # far faster than the other kernels here
+        assert torch.equal(out[n, k], rp.matvec_multi(cloud(n), torch.ones((k, n, 3), dtype=torch.float64, device="cuda")))
+'''
+    cache = {"RPYW_AUTOTUNE_CACHE": str(path)}
+    _tuned_probe(body.format(obeys=False, tune=True), cache)  # the default, then tuned
+    entries = json.loads(path.read_text())["entries"]
+    assert len(entries) == 3 and all(e["direct"] == 1 for e in entries)
+    _tuned_probe(body.format(obeys=False, tune=False), cache)  # from the file
+    for e in entries:
+        e.update(direct=0, sym=0, tpl=1, tile=64, ipw=4, kblk=1)
+    path.write_text(json.dumps({"version": 1, "entries": entries}))
+    _tuned_probe(body.format(obeys=True, tune=False), cache)
+    for e in entries:
+        del e["direct"], e["ipw2"]  # a file of an earlier version
+    path.write_text(json.dumps({"version": 1, "entries": entries}))
+    _tuned_probe(body.format(obeys=True, tune=False), cache)
+    _tuned_probe(body.format(obeys=True, tune=False), {"RPYW_TILE": "256"})
+
+
 def _other_calls(rp, n):
     """What else reads the FP64 shape of one right-hand side: VJP, periodic
     product, and the product of a smaller problem of the size class."""
