@@ -764,6 +764,9 @@ size_t product_ws_bytes(int64_t N, int prec, int kblk) {
     size_t sb = 0;
     for (int K = 1; K <= std::min(kblk, 4); K <<= 1)
         for (int G : {256, 128, 64}) {
+            // FP64 blocks of two and four have only groups of 128, and two
+            // right-hand sides of a periodic product groups of 64
+            if (prec == RPYW_FP64 && ((K > 1 && G == 256) || (K > 2 && G == 64))) continue;
             const SymPlan sp = sym_plan(N, prec, K, 1, G);
             if (sp.ok) sb = std::max(sb, sp.rec_bytes + sp.tpart_bytes + sp.spart_bytes);
         }

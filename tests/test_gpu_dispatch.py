@@ -225,3 +225,21 @@ assert all(torch.equal(a, b) for a, b in zip(flat(after), torch.load({file!r})))
     first = _tuned_probe(body.format(tune=True, file=str(tmp_path / "ref.pt")), env)
     again = _tuned_probe(body.format(tune=False, file=str(tmp_path / "ref.pt")), env)
     assert first.stdout == again.stdout
+
+
+@pytest.mark.parametrize("N", [500, 3000, 3400, 9000, 33000])
+@pytest.mark.parametrize("k", [2, 4, 5, 9])
+def test_calls_fit_the_workspace_that_they_ask_for(rp, N, k):
+    """FP64, every symmetric shape (the binding passes exactly the bytes of the
+    query; too few would raise), with the sums of single products."""
+    pos, F = _t(_mixed(N, N)), _t(np.random.default_rng(N).standard_normal((k, N, 3)))
+    ref = rp.matvec(pos, F[k - 1].contiguous(), precision=0).cpu().numpy()
+    check(rp.matvec_multi(pos, F, precision=0)[k - 1].cpu().numpy(), ref, 1e-12, f"N={N} k={k}")
+    for kblk in (1, 2, 4):
+        for sym in (1, 2):
+            rp.set_shape(0, N, k, tpl=1, tile=256, kblk=kblk, sym=sym, ipw=1)
+            try:
+                U = rp.matvec_multi(pos, F, precision=0)
+            finally:
+                rp.reset_shape(0, N, k)
+            check(U[k - 1].cpu().numpy(), ref, 1e-12, f"N={N} k={k} kblk={kblk} sym={sym}")
