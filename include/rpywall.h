@@ -112,10 +112,14 @@ int rpy_wall_matvec_multi(const double* pos, const double* F, double* U, int64_t
  * pair includes the blob's own 8 images.  The minimum image is the shift
  * by the nearest integer multiple of the cell (ties to even).  Positions
  * may lie outside the cell: they are wrapped into it first.  Evaluated by
- * the symmetric kernel (9 image blocks per unordered pair), up to 30000
- * blobs two right-hand sides at a time when ws holds the bytes of a product
- * with k = 2 (ws of k = 1 is enough).  F, U: device [k][N][3]; Lx, Ly > 0 in the units of
- * pos; other arguments as for rpy_wall_matvec_multi. */
+ * the symmetric kernel (9 image blocks per unordered pair), two right-hand
+ * sides at a time over groups of 64 blobs, that is up to 32768 blobs unless the
+ * launch shape has sym = 1, and when ws holds the bytes of a product with k = 2
+ * or is NULL; ws of k = 1 is always enough.  Sums of pairs and of single
+ * right-hand sides are the same to the bit in FP32C; in FP64 the order of the
+ * additions may differ, and with it the last digits between the two workspace
+ * sizes.  F, U: device [k][N][3]; Lx, Ly > 0 in the units of pos; other
+ * arguments as for rpy_wall_matvec_multi. */
 int rpy_wall_matvec_periodic(const double* pos, const double* F, double* U, int64_t N, int32_t k, double a,
                              double eta, double Lx, double Ly, int precision, void* ws, size_t ws_bytes,
                              void* stream);

@@ -330,7 +330,9 @@ int rpy_wall_matvec_periodic(const double* pos, const double* F, double* U, int6
         return RPYW_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     Scratch s;
-    int rc = acquire(ws, ws_bytes, product_ws_bytes(N, precision, ws ? 1 : std::min(k, 2)), st, s);
+    // room for two right-hand sides to a pass only where there are such passes
+    const int kpass = ws || N > kSym64MaxN ? 1 : std::min(k, 2);
+    int rc = acquire(ws, ws_bytes, product_ws_bytes(N, precision, kpass), st, s);
     if (rc == RPYW_OK) rc = products(pos, F, U, N, k, a, eta, precision, s.ar, st, Domain{Lx, Ly});
     if (log_enabled()) log_shape("rpy_wall_matvec_periodic", N, k, precision, rc);
     return rc;

@@ -208,7 +208,8 @@ def matvec_periodic(pos: torch.Tensor, F: torch.Tensor, box, a: float = 1.0, eta
     _dev(pos, "pos", (N, 3))
     _dev(F, "F", (k, N, 3))
     out = torch.empty_like(F) if out is None else _dev(out, "out", (k, N, 3))
-    ws = _workspace(workspace_bytes(OP_MATVEC, N, min(k, 2), precision=precision), pos.device)
+    # two right-hand sides share a pass up to 32768 blobs
+    ws = _workspace(workspace_bytes(OP_MATVEC, N, min(k, 2) if N <= 32768 else 1, precision=precision), pos.device)
     _check(lib().rpy_wall_matvec_periodic(pos.data_ptr(), F.data_ptr(), out.data_ptr(), N, k, a, eta,
                                           float(box[0]), float(box[1]), precision, ws.data_ptr(), ws.numel(),
                                           _stream(pos.device)), "rpy_wall_matvec_periodic")

@@ -243,3 +243,49 @@ def test_calls_fit_the_workspace_that_they_ask_for(rp, N, k):
             finally:
                 rp.reset_shape(0, N, k)
             check(U[k - 1].cpu().numpy(), ref, 1e-12, f"N={N} k={k} kblk={kblk} sym={sym}")
+
+
+@pytest.mark.parametrize("N,pairs", [(30001, True), (32768, True), (32769, False)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_periodic_pairs_of_right_hand_sides_at_their_largest(rp, N, pairs, prec):
+    """Two right-hand sides to a pass up to 32768 blobs, with the workspace of
+    two and without one, and single passes beyond or with the workspace of one;
+    the same sums, to the last bit in FP32C.  Beyond, the memory that the call
+    takes is that of one."""
+    import ctypes
+    rng = np.random.default_rng(N)
+    cell = (300.0, 310.0)
+    pos = _t(np.column_stack([rng.uniform(0, cell[0], N), rng.uniform(0, cell[1], N), rng.uniform(0.4, 30.0, N)]))
+    F = _t(rng.standard_normal((2, N, 3)))
+    torch.cuda.reset_peak_memory_stats()
+    held = torch.cuda.memory_allocated()
+
+    def passes(fn):
+        rp.profile_enable(True)
+        rp.profile_read(reset=True)
+        try:
+            U = fn()
+            return U, rp.profile_read(reset=True)[1]
+        finally:
+            rp.profile_enable(False)
+
+    def raw(ws):
+        U = torch.empty_like(F)
+        rp._check(rp.lib().rpy_wall_matvec_periodic(
+            pos.data_ptr(), F.data_ptr(), U.data_ptr(), N, 2, 1.0, 1.0, *cell, prec,
+            ws.data_ptr() if ws is not None else None, ctypes.c_size_t(ws.numel() if ws is not None else 0),
+            rp._stream(pos.device)), "periodic")
+        return U
+    got, n = passes(lambda: rp.matvec_periodic(pos, F, cell, precision=prec))
+    assert n == (1 if pairs else 2)
+    one = rp.workspace_bytes(rp.OP_MATVEC, N, 1, precision=prec)
+    if not pairs:
+        assert torch.cuda.max_memory_allocated() - held < 1.2 * one + (64 << 20)
+    own, n = passes(lambda: raw(None))
+    assert n == (1 if pairs else 2) and torch.equal(own, got)
+    single, n = passes(lambda: raw(torch.empty(one, dtype=torch.uint8, device="cuda")))
+    assert n == 2
+    if prec == 1:
+        assert torch.equal(single, got)
+    else:
+        check(single.cpu().numpy(), got.cpu().numpy(), 1e-13, f"N={N} single passes")
