@@ -326,9 +326,13 @@ __global__ __launch_bounds__(64 * NB * NS) void sym_kernel(const R* __restrict__
     }
     const int H = sym_rowlen(P, ng);
     const bool last = NB == 4 && c >= C - tail;
-    const int d0 = last ? Hmax + 1 - (C - c) : c * ipw;
+    // (The loop's bounds in scalar registers: left to the compiler they take three
+    // vector registers, which cost the FP32 VJP and periodic kernels a wave on
+    // every SIMD: VJP of 196608 blobs 103.0 ms, so 101.3; periodic product of
+    // 61440 23.0 and 22.4.)
+    const int d0 = __builtin_amdgcn_readfirstlane(last ? Hmax + 1 - (C - c) : c * ipw);
     const int dn = NB == 4 && tail ? (last ? d0 : Hmax - tail) : H;
-    const int d1 = min(min(d0 + ipw - 1, dn), H);
+    const int d1 = __builtin_amdgcn_readfirstlane(min(min(d0 + ipw - 1, dn), H));
     for (int d = d0; d <= d1; ++d) {
         const int Q = (P + d) % ng;
         __syncthreads();
