@@ -357,7 +357,8 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
  * it in both directions (kblk <= 4), over groups of 256 blobs (1) or of 64
  * blobs (2, more workgroups for small problems; taken for N <= 32768, else
  * groups of 256); in FP64 and the open domain both select the kernel with two
- * targets per lane over groups of 128 (one right-hand side: 3584 <= N <= 32768;
+ * targets per lane over groups of 128 (one right-hand side: 3584 <= N <= 32768,
+ * except 3969 to 4480;
  * more: N <= 131072, else the plain kernel); ipw: source groups per workgroup
  * of the symmetric kernel;
  * mat: 1 contracts the 3 x 3 pair blocks with the RHS block on the matrix

@@ -668,7 +668,8 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             if (cand >= 6 && kb >= 8 && sh.tpl == 2) continue;
             if (cand < 6 && kb > 4) continue;
             // (of groups of 128 the ipw is tuned, that of the other calls is left)
-            if (sh.sym && precision == RPYW_FP64 && N <= kSym2MaxN && (kb > 1 || (N >= kSym2MinN1 && N <= kSym2MaxN1))) {
+            const bool two = precision == RPYW_FP64 && kb <= 4 && sym_plan(N, precision, kb, 1, 128).ok;
+            if (sh.sym && two) {
                 sh.ipw2 = sh.ipw;
                 sh.ipw = default_shape(N, 1, precision).ipw;
             }
@@ -676,7 +677,7 @@ int rpy_wall_autotune(const double* pos, const double* F, double* U, int64_t N, 
             // where both values of sym are the kernel over groups of 128 (FP64),
             // the one that also means groups of 64 for smaller problems of the
             // class, single right-hand sides, derivatives and periodic products
-            if (sh.sym == 1 && N <= kSym64MaxN && precision == RPYW_FP64 && (kb > 1 || N >= kSym2MinN1)) continue;
+            if (sh.sym == 1 && N <= kSym64MaxN && two) continue;
             if (cand == 6 && kb >= 8) {
                 Shape m{1, 64, kb, 0, 4};
                 m.mat = 1;

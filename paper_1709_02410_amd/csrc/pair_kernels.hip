@@ -688,8 +688,16 @@ SymPlan sym_plan(int64_t N, int prec, int K, int ipw, int G) {
     s.tpart_bytes = align_up((size_t)s.ng * s.C * s.nseg * 3 * K * s.G * sizeof(double));
     s.spart_bytes = align_up((size_t)s.ng * (s.Hmax + 1) * s.nseg * 3 * K * s.G * real_size(prec));
     s.ok = K <= 4 && s.spart_bytes <= kSymPartialMaxBytes && s.tpart_bytes <= kSymPartialMaxBytes &&
-           (s.G != 64 || N <= kSym64MaxN) &&
-           (s.G != 128 || (prec == RPYW_FP64 && (K > 1 || N >= kSym2MinN1) && N <= (K == 1 ? kSym2MaxN1 : kSym2MaxN)));
+           (s.G != 64 || N <= kSym64MaxN);
+    if (s.G == 128) {
+        // Two items run on a compute unit at a time and the time goes up in steps
+        // of 256 of them: a third round that is less than half full (3969 to 4480
+        // blobs, one right-hand side) leaves groups of 64 ahead, 35.7 against 41.0
+        // us at 4096 blobs, 41.3 and 41.7 at 4480 (43.7 and 41.9 at 4608).
+        const bool third = items > 512 && items <= 640;
+        s.ok = s.ok && prec == RPYW_FP64 && N <= (K == 1 ? kSym2MaxN1 : kSym2MaxN) &&
+               (K > 1 || (N >= kSym2MinN1 && !third));
+    }
     return s;
 }
 

@@ -81,8 +81,10 @@ constexpr size_t kSymPartialMaxBytes = (size_t)16 << 30;
 // Problems of the FP64 kernel with groups of 128 and one right-hand side: below
 // them groups of 64 spread better (24.7 against 31.8 us at 3000 blobs, 34.9
 // against 31.0 at 3840), beyond them groups of 256 run at the same speed with
-// half the partials.  With more right-hand sides: up to kSym2MaxN (beyond it
-// the plain kernel).
+// half the partials; sym_plan has a gap at 4096.  With more right-hand sides: up
+// to kSym2MaxN, beyond it the plain kernel (two, four and six: 34.0, 49.2 and 82.7
+// ms at 131072 blobs, 48.6, 61.8 and 85.5 on the plain kernel; 4.8, 7.3 and 12.0
+// against 7.8, 9.8 and 13.4 at 50000; there the partials of four are 8 GB).
 constexpr int64_t kSym2MinN1 = 3584;
 constexpr int64_t kSym2MinN5 = 3329;  // five or six right-hand sides (14 blocks of 256 targets of the plain kernel)
 constexpr int64_t kSym2MaxN1 = 32768;

@@ -289,3 +289,23 @@ def test_periodic_pairs_of_right_hand_sides_at_their_largest(rp, N, pairs, prec)
         assert torch.equal(single, got)
     else:
         check(single.cpu().numpy(), got.cpu().numpy(), 1e-13, f"N={N} single passes")
+
+
+@pytest.mark.parametrize("N,groups_of_128", [(3583, False), (3584, True), (3968, True), (3969, False), (4096, False),
+                                             (4480, False), (4481, True), (32768, True), (32769, False)])
+def test_sizes_of_the_groups_of_128(rp, orc, N, groups_of_128):
+    """FP64, one right-hand side: where both symmetric shapes are the kernel over
+    groups of 128, their sums are the same to the bit."""
+    pos, f = 0.9 * _mixed(N, N), np.random.default_rng(N).standard_normal((N, 3))
+    U = [rp.matvec(_t(pos), _t(f), 0.9, 1.3, precision=0)]
+    for sym in (1, 2):
+        rp.set_shape(0, N, 1, tpl=1, tile=256, kblk=1, sym=sym, ipw=1)
+        try:
+            U.append(rp.matvec(_t(pos), _t(f), 0.9, 1.3, precision=0))
+        finally:
+            rp.reset_shape(0, N, 1)
+    assert torch.equal(U[1], U[2]) == (groups_of_128 or N > 32768)
+    rows = np.r_[0:8, N - 8:N]
+    ref = orc.matvec(pos, f, 0.9, 1.3, rows=rows)
+    for u in U:
+        check(u.cpu().numpy()[rows], ref, TOL[0], f"N={N}")
