@@ -775,7 +775,12 @@ size_t product_ws_bytes(int64_t N, int prec, int kblk) {
             // FP64 blocks of two and four have only groups of 128, and two
             // right-hand sides of a periodic product groups of 64
             if (prec == RPYW_FP64 && ((K > 1 && G == 256) || (K > 2 && G == 64))) continue;
-            const SymPlan sp = sym_plan(N, prec, K, 1, G);
+            // one item to a workgroup has the most partials; where these are too
+            // many for the kernel, two (FP32C, whose source partials are floats;
+            // of wider blocks, which only a fixed shape has, those that do not
+            // fit go to the plain kernel)
+            SymPlan sp = sym_plan(N, prec, K, 1, G);
+            if (!sp.ok && K == 1) sp = sym_plan(N, prec, K, 2, G);
             if (sp.ok) sb = std::max(sb, sp.rec_bytes + sp.tpart_bytes + sp.spart_bytes);
         }
     return std::max(b, sb) + 8 * kAlign;
@@ -900,7 +905,10 @@ int product_pass(const double* pos, const double* F, double* U, int64_t N, int k
     sh = normalized(sh, K, prec);
     if (sh.sym && K <= 4) {
         const SymPlan sp = sym_choose(N, prec, K, sh, Domain{});
-        if (sp.ok) return sym_pass(pos, F, U, N, kb, K, a, eta, prec, sp, ar, st);
+        if (sp.ok) {
+            const int rc = sym_pass(pos, F, U, N, kb, K, a, eta, prec, sp, ar, st);
+            if (rc != RPYW_ENOMEM) return rc;
+        }
     }
     const int rw = rec_width(prec, K);
     void* rec = ar.take((size_t)N * rw * real_size(prec));

@@ -361,7 +361,8 @@ size_t vjp_ws_bytes(int64_t N, int prec) {
     b += align_up((size_t)N * sizeof(double));
     b += align_up((size_t)splits * kQ * N * sizeof(double));
     for (int G : {256, 64}) {
-        const VjpPlan p = vjp_sym_plan(N, prec, 1, G);
+        VjpPlan p = vjp_sym_plan(N, prec, 1, G);
+        if (!p.ok) p = vjp_sym_plan(N, prec, 2, G);  // as for the product
         if (p.ok)
             b = std::max(b, align_up((size_t)p.ng * G * rec_width(prec, 2) * real_size(prec)) + p.tb + p.sb);
     }

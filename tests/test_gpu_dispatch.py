@@ -309,3 +309,23 @@ def test_sizes_of_the_groups_of_128(rp, orc, N, groups_of_128):
     ref = orc.matvec(pos, f, 0.9, 1.3, rows=rows)
     for u in U:
         check(u.cpu().numpy()[rows], ref, TOL[0], f"N={N}")
+
+
+def test_fp32c_calls_whose_target_partials_bound_the_kernel(rp, orc):
+    """FP32C products above 605000 blobs and VJPs above 349000 run on the
+    symmetric kernel with several items to a workgroup only; the workspace of the
+    query holds that (it did not, and the calls were refused)."""
+    N = 610000
+    rng = np.random.default_rng(N)
+    pos = np.column_stack([rng.uniform(0, 2000, N), rng.uniform(0, 2000, N), rng.uniform(0.4, 6.0, N)])
+    f, g = rng.standard_normal((2, N, 3))
+    rows = np.r_[0:4, N - 4:N]
+    U = rp.matvec_multi(_t(pos), _t(f[None]), precision=1)[0]
+    check(U.cpu().numpy()[rows], orc.matvec(pos, f, rows=rows), TOL[1], f"product N={N}")
+    N = 352000
+    gp, gf = rp.matvec_vjp(_t(pos[:N]), _t(f[:N]), _t(g[:N]), precision=1)
+    rows = np.r_[0:4, N - 4:N]
+    gp_ref, gf_ref = orc.vjp(pos[:N], f[:N], g[:N], rows=rows)
+    check(gp.cpu().numpy()[rows], gp_ref, TOL[1], f"vjp N={N} grad_pos")
+    check(gf.cpu().numpy()[rows], gf_ref, TOL[1], f"vjp N={N} grad_f")
+    torch.cuda.empty_cache()
