@@ -50,7 +50,9 @@ def krylov_path(rp, N, fused, prec=0):
     """fused: force the symmetric product for this size class, which makes
     the Lanczos and GMRES drivers take their fused four-launch steps (they
     do so whenever the product is symmetric); otherwise the size's default
-    shape (below 512 blobs the plain product, whose steps are not fused)."""
+    shape (below 512 blobs in FP32C the plain product, whose steps are not
+    fused; in FP64 the steps are fused as well, and test_gpu_unfused_krylov.py
+    has the other driver)."""
     if fused:
         rp.set_shape(prec, N, 1, tpl=1, tile=256, kblk=1, sym=2, ipw=1)
     try:

@@ -329,3 +329,19 @@ def test_fp32c_calls_whose_target_partials_bound_the_kernel(rp, orc):
     check(gp.cpu().numpy()[rows], gp_ref, TOL[1], f"vjp N={N} grad_pos")
     check(gf.cpu().numpy()[rows], gf_ref, TOL[1], f"vjp N={N} grad_f")
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,k", [(1, 2), (64, 3), (65, 4), (129, 7), (575, 5), (1025, 2), (1025, 8)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_plain_chunk_epilogue(rp, orc, N, k, prec):
+    """The plain kernel at the sizes of the chunk epilogue's edges: one chunk,
+    fewer than its shares, several rounds, a last wave of one blob."""
+    pos = 0.9 * _mixed(N, N)
+    F = np.random.default_rng(N + 1).standard_normal((k, N, 3))
+    rp.set_shape(prec, N, k, tpl=1, tile=64, kblk=2 if k == 2 else 4 if k <= 4 else 8, sym=0)
+    try:
+        U = rp.matvec_multi(_t(pos), _t(F), 0.9, 1.3, precision=prec).cpu().numpy()
+    finally:
+        rp.reset_shape(prec, N, k)
+    for j in range(k):
+        check(U[j], orc.matvec(pos, F[j], 0.9, 1.3), TOL[prec], f"plain N={N} k={k} rhs {j} prec={prec}")
