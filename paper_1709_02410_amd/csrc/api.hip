@@ -116,12 +116,12 @@ static bool direct_rule(int64_t N, int k, int prec) {
 // below ten thousand blobs (which leave the GPU underfilled) and still 5% at
 // 30000; wider RHS blocks are faster on the plain kernel, and FP32C blocks
 // of 8 or more are contracted on the matrix cores.  Groups of 256
-// take 4 or 6 items to a workgroup and end with chunks of one (sym_tail): 1.956
-// ms at 50000 blobs in FP32C against 1.974 with one item to each, 7.69 at 1e5
-// against 7.74 to 7.88 with four and no tail; six below 32768 items leave too
-// few workgroups (0.908 against 0.868 ms at 33000).  In FP64 two targets
-// per lane (sym_multi.h) make the symmetric kernel the faster one for up to
-// four right-hand sides as well; above kSym2MinN5 blobs 5 or 6 go in a block of 4
+// take 4 or 6 items to a workgroup and end with chunks of one (sym_tail): 1.918
+// ms at 50000 blobs in FP32C against 1.936 with one item to each, 7.58 at 1e5
+// against 7.79; six below 32768 items leave too few workgroups (0.908 against
+// 0.868 ms at 33000).  In FP64 two targets per lane (sym_multi.h) make the
+// symmetric kernel the faster one for up to four right-hand sides as well; from
+// kSym2MinN5 blobs on 5 or 6 go in a block of 4
 // and the rest (five: 76.7 us for one block of 8 on the plain kernel against 81.0
 // at 3300 blobs, 93.3 against 81.8 at 3400, 1.96 against 1.67 ms at 20000; six:
 // 78.5 and 91.0, 95.0 and 92.0, 1.99 and 1.85; 7 take longer).

@@ -27,7 +27,7 @@ __device__ __forceinline__ double uniform_value(double v) {
 // instructions once there are a few waves per SIMD, by latency and the launch
 // below.  The symmetric kernel halves the pairs but pays a second launch and
 // the traffic of its partial sums, the plain kernel a third launch.
-// One right-hand side (us a call): 26.4 -> 9.0 at 300 blobs (plain), 11 -> 8.7
+// One right-hand side (us a call): 26.4 -> 6.9 at 300 blobs (plain), 10.3 -> 6.8
 // at 1000, 17.3 against 14.8 at 2000, 21 against 21 at 2500 (symmetric); four:
 // 32 -> 10.4 at 1000 (plain), 31 against 29 at 2000.  Two targets per
 // workgroup: with one the loads weigh (16.7 at 2000), with four fewer waves
